@@ -126,7 +126,7 @@ int nif_model_get_grads(const nif_model* model, float* g_tables_dev, float* g_ml
                         nif_stream stream);
 int nif_model_zero_grads(nif_model* model, nif_stream stream);
 /* Allocates the training scratch for batches of up to max_batch samples (activations,
-   deltas, a [min(max_batch, 2^17)][E] encoding scratch for the backward's recomputation,
+   deltas, one [min(max_batch, 2^17)][E] encoding scratch (two above 2^17 samples),
    the table-gradient additions of a round of min(max_batch, 2^18) samples, weight-gradient
    partials and the spatially ordered copy of a batch); nif_backward and nif_train_step fail with NIF_E_STATE above it.  A later call
    with a larger max_batch frees and re-allocates everything, the stored encoding included. */
@@ -300,8 +300,8 @@ int nif_forward(const nif_model* model, const float* x0_dev, const float* x1_dev
  * the model's gradient accumulators (zeroed first unless accumulate != 0) and writes
  * dL/dx0, dL/dx1 (SoA, nullable).  Hand-written: MLP backward, hash-grid scatter-add with
  * the trilinear weights (additions grouped by table slice and summed in 64-bit fixed
- * point), PE chain rule.  Nothing is kept from nif_forward: the hidden activations are
- * recomputed, and the encoding is recomputed per chunk of 2^17 samples. */
+ * point), PE chain rule.  Nothing is kept from nif_forward: the call runs the forward again,
+ * chunk by chunk of 2^17 samples, and keeps a chunk's encoding until its weight gradient. */
 int nif_backward(nif_model* model, const float* x0_dev, const float* x1_dev, int64_t B,
                  const float* d_heads_dev, float* d_x0_dev, float* d_x1_dev, int32_t accumulate,
                  int32_t precision, nif_stream stream);
@@ -331,14 +331,13 @@ typedef struct {
     float loss_scale_init;      /* 0 = 1 for FP32/BF16, 32768 for FP16 */
     int32_t fixed_task_weights; /* 1 = ablation without uncertainty weighting: total = sum of
                                    the five task losses, s neither used nor updated */
-    int32_t store_encoding;     /* 0: the forward keeps no encoding; the backward recomputes it
-                                   (gathers again) per chunk of 2^17 samples for the first
-                                   layer's weight gradient, in a [2^17][E] FP32 scratch.
-                                   1: the forward stores the [B][E] FP32 encoding for the
-                                   backward (one gather pass less per step; max_batch E 4 bytes
-                                   more device memory, from nif_model_reserve_encoding; without
-                                   it the step fails with NIF_E_STATE).  The hidden activations
-                                   are stored in both cases. */
+    int32_t store_encoding;     /* 0: a chunk's encoding is kept in one of two [2^17][E] FP32
+                                   scratches from its forward to its first-layer weight gradient.
+                                   1: the forward stores the whole batch's [B][E] FP32 encoding
+                                   (max_batch E 4 bytes more device memory, from
+                                   nif_model_reserve_encoding; without it the step fails with
+                                   NIF_E_STATE).  Either way the table is gathered once per step
+                                   and the results are the same. */
     int32_t loss_scale_growth_interval; /* dynamic loss scaling (BF16/FP16): the scale doubles
                                    after this many clean steps in a row; 0 = 1000.  A step with
                                    a non-finite loss or gradient is skipped (no parameter,

@@ -64,7 +64,8 @@ struct nif_model {
     float* dz = nullptr;                // [max_batch][16] d loss / d heads (loss-scaled, padded)
     float* acts = nullptr;              // [hidden_layers][max_batch][hidden_width] post-ReLU
     float* delta = nullptr;             // [hidden_layers][max_batch][hidden_width] d loss / d pre-activation
-    float* enc = nullptr;               // [bwd_chunk][E] encoding recomputed for the first layer's dW
+    float* enc = nullptr;               // [1 or 2][bwd_chunk][E] a chunk's encoding, from its forward to its
+                                        //   first-layer dW (two scratches in turn with several chunks)
     float* enc_all = nullptr;           // [max_batch][E] stored encoding (store_encoding steps only;
                                         //   allocated by nif_model_reserve_encoding)
     int64_t bwd_chunk = 0;              // samples per training chunk (forward, MLP backward, one fill launch)
@@ -127,11 +128,6 @@ int forward_launch(const nif_model* m, const float* x0, const float* x1, int64_t
 // [n][E] local to the n rows).
 int forward_rows_launch(const nif_model* m, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
                         int32_t precision, float* acts, float* enc, hipStream_t st);
-// Encoding only of n pairs whose SoA rows have stride ld: enc[n][E], the values the forward
-// of the same precision feeds its first layer.
-int encode_pairs_launch(const nif_model* m, const float* x0, const float* x1, int64_t n, int64_t ld,
-                        int32_t precision, float* enc, hipStream_t st);
-
 // nif_train.hip
 int model_alloc(nif_model* m);
 void model_free(nif_model* m);

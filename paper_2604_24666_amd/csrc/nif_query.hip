@@ -477,26 +477,13 @@ __global__ void __launch_bounds__(256) k_encode(EncParams ep, const float* __res
     }
 }
 
-// Encoding of segments [seg_base, seg_base + 16*CB) into enc_out only (no MLP past the
-// first layer's accumulation, whose result is dropped).
-template <int HW, int CB, int PREC, bool GAMMA, int FD>
-__device__ __forceinline__ void enc_pass(const NetParams& np, const float* s_seg, int seg_base, int64_t seg_g0,
-                                         int64_t n_valid, float* enc_out) {
-    floatx4 acc[HW / 16][CB];
-    layer1_bias<HW, CB>(np, acc);
-    layer1_levels<HW, CB, PREC, FD>(np, s_seg, seg_base, 0, np.enc.L, acc, enc_out, seg_g0, n_valid);
-    if constexpr (GAMMA) layer1_gamma<HW, CB, PREC>(np, s_seg, seg_base, acc, enc_out, seg_g0, n_valid);
-}
-
 // Heads of point pairs.  Each wave evaluates tiles of 64 pairs; acts (nullable) receives the
 // hidden activations [layer][B][HW] and enc (nullable) the encoding [B][E], for the training
-// backward.  x0 / x1 are SoA with row stride ld >= B.  ENC_ONLY: only the encoding is written
-// (the backward's recomputation, per chunk of samples; heads and acts unused), in tiles of 16
-// pairs so that a chunk still spreads over many waves.  At width 128 each pass takes 16 of
+// backward.  x0 / x1 are SoA with row stride ld >= B.  At width 128 each pass takes 16 of
 // the tile's 64 points, which keeps the accumulators small enough for two waves per SIMD; with
 // spatially ordered batches that latency hiding outweighs streaming the first-layer weights
 // once per pass.
-template <int HW, int PREC, bool GAMMA = false, bool ENC_ONLY = false, int TILE = ENC_ONLY ? 16 : 64, int FD = 2>
+template <int HW, int PREC, bool GAMMA = false, int TILE = 64, int FD = 2>
 __global__ void __launch_bounds__(256, 2) k_forward(NetParams np, const float* __restrict__ x0, const float* __restrict__ x1,
                                                  int64_t B, int64_t ld, float* __restrict__ heads,
                                                  float* __restrict__ acts, float* __restrict__ enc) {
@@ -520,18 +507,12 @@ __global__ void __launch_bounds__(256, 2) k_forward(NetParams np, const float* _
             my[0] = my[1] = my[2] = my[4] = my[5] = my[6] = 0.5f;
         }
         wave_lds_sync();
-        if constexpr (ENC_ONLY) {
 #pragma unroll
-            for (int ps = 0; ps < PASSES; ++ps)
-                enc_pass<HW, CB, PREC, GAMMA, FD>(np, s_seg, ps * 16 * CB, tile * TILE + ps * 16 * CB, B, enc);
-        } else {
-#pragma unroll
-            for (int ps = 0; ps < PASSES; ++ps)
-                net_pass<HW, CB, PREC, GAMMA, FD>(np, s_seg, ps * 16 * CB, s_z, acts, B * HW, tile * TILE + ps * 16 * CB, B, enc);
-            wave_lds_sync();
-            if (lane < TILE && seg < B)
-                for (int h = 0; h < np.H; ++h) heads[seg * np.H + h] = s_z[lane * kZStride + h];
-        }
+        for (int ps = 0; ps < PASSES; ++ps)
+            net_pass<HW, CB, PREC, GAMMA, FD>(np, s_seg, ps * 16 * CB, s_z, acts, B * HW, tile * TILE + ps * 16 * CB, B, enc);
+        wave_lds_sync();
+        if (lane < TILE && seg < B)
+            for (int h = 0; h < np.H; ++h) heads[seg * np.H + h] = s_z[lane * kZStride + h];
         wave_lds_sync();
     }
 }
@@ -750,20 +731,15 @@ template <int HW, int PREC>
 static void launch_forward(const NetParams& np, const float* x0, const float* x1, int64_t B, int64_t ld, float* heads,
                            float* acts, float* enc, hipStream_t st) {
     // small launches (up to 2^17 pairs) take 16 pairs per wave so that they still fill the chip
-    const bool gamma = np.gamma_F >= 0, enc_only = heads == nullptr, small = B <= (1 << 17);
-    const int64_t tiles = enc_only || small || np.enc.Fd == 3 ? (B + 15) / 16 : (B + 63) / 64;
+    const bool gamma = np.gamma_F >= 0, small = B <= (1 << 17);
+    const int64_t tiles = small || np.enc.Fd == 3 ? (B + 15) / 16 : (B + 63) / 64;
     const int64_t blocks = std::min<int64_t>((tiles + 3) / 4, (int64_t)device_cus() * 8);
     const dim3 g((unsigned)std::max<int64_t>(blocks, 1)), b(256);
-    if (np.enc.Fd == 3) {            // three-feature entries: 16 pairs per wave throughout
-        if (enc_only) hipLaunchKernelGGL((k_forward<HW, PREC, false, true, 16, 3>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
-        else hipLaunchKernelGGL((k_forward<HW, PREC, false, false, 16, 3>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
-        return;
-    }
-    if (gamma && enc_only) hipLaunchKernelGGL((k_forward<HW, PREC, true, true>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
-    else if (gamma && small) hipLaunchKernelGGL((k_forward<HW, PREC, true, false, 16>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
+    if (np.enc.Fd == 3)              // three-feature entries: 16 pairs per wave throughout
+        hipLaunchKernelGGL((k_forward<HW, PREC, false, 16, 3>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
+    else if (gamma && small) hipLaunchKernelGGL((k_forward<HW, PREC, true, 16>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
     else if (gamma) hipLaunchKernelGGL((k_forward<HW, PREC, true>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
-    else if (enc_only) hipLaunchKernelGGL((k_forward<HW, PREC, false, true>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
-    else if (small) hipLaunchKernelGGL((k_forward<HW, PREC, false, false, 16>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
+    else if (small) hipLaunchKernelGGL((k_forward<HW, PREC, false, 16>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
     else hipLaunchKernelGGL((k_forward<HW, PREC>), g, b, 0, st, np, x0, x1, B, ld, heads, acts, enc);
 }
 
@@ -803,12 +779,6 @@ int forward_rows_launch(const nif_model* m, const float* x0, const float* x1, in
                         int32_t precision, float* acts, float* enc, hipStream_t st) {
     if (heads == nullptr || ld < n) return fail(NIF_E_INVALID_ARG, "forward needs a heads buffer and ld >= n");
     return forward_any(m, x0, x1, n, ld, heads, precision, acts, enc, st);
-}
-
-int encode_pairs_launch(const nif_model* m, const float* x0, const float* x1, int64_t n, int64_t ld, int32_t precision,
-                        float* enc, hipStream_t st) {
-    if (enc == nullptr || ld < n) return fail(NIF_E_INVALID_ARG, "pair encoding needs an output and ld >= n");
-    return forward_any(m, x0, x1, n, ld, nullptr, precision, nullptr, enc, st);
 }
 
 }  // namespace nif

@@ -9,12 +9,11 @@
 // is not named by the paper.
 //
 // Launch sequence of one step (all on the caller's stream, no host synchronisation):
-//   begin / count positives -> zero gradients -> forward (stores hidden activations) ->
-//   loss and d loss / d heads (loss-scaled) -> MLP backward on MFMA (transposed weights,
-//   deltas chained in registers) -> split-K dW GEMMs on MFMA -> encoding backward (the
-//   encoding is recomputed chunk by chunk, d enc = W0^T delta, the table-gradient additions
-//   with the trilinear weights grouped by table slice and summed in LDS, dW0) -> non-finite
-//   check -> finalize
+//   begin / count positives -> zero gradients -> per chunk: forward (stores hidden activations
+//   and the chunk's encoding) -> loss and d loss / d heads (loss-scaled) -> MLP backward on MFMA
+//   (transposed weights, deltas chained in registers) -> split-K dW GEMMs on MFMA -> encoding
+//   backward (d enc = W0^T delta, the table-gradient additions with the trilinear weights
+//   grouped by table slice and summed in LDS) -> non-finite check -> finalize
 //   (losses, d/ds, dynamic loss scale) -> Adam on all parameters (FP16 table copy refreshed
 //   in place) -> refresh of the MLP working copies.
 #include <algorithm>
@@ -39,11 +38,12 @@ constexpr int kRecFloats = 4;              // floats per table-gradient record (
 
 // Concatenated encoding: d x of the appended gamma values, d enc_v = (W0^T delta_0)_v times
 // d gamma_v / d x_a of the clamped coordinate (zero outside the cube), added to dx0 / dx1.
+// n rows; point arrays SoA with stride B.
 __global__ void __launch_bounds__(256) k_gamma_dx(const float* __restrict__ W0t, const float* __restrict__ delta0,
                                                   int HW, int E_phi, int GW, const float* __restrict__ x0,
-                                                  const float* __restrict__ x1, int64_t B, float* __restrict__ dx0,
+                                                  const float* __restrict__ x1, int64_t n, int64_t B, float* __restrict__ dx0,
                                                   float* __restrict__ dx1) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < B; i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const float* d = delta0 + i * HW;
         for (int p = 0; p < 2; ++p) {
             const float* xs = p ? x1 : x0;
@@ -174,7 +174,9 @@ int model_reserve(nif_model* m, int64_t B) {
     }
     const int64_t hw = m->desc.hidden_width, nh = m->desc.hidden_layers;
     const struct { float** p; int64_t n; } a[] = {{&m->zbuf, B * m->H}, {&m->dz, B * 16}, {&m->acts, B * hw * nh},
-                                                  {&m->delta, B * hw * nh}, {&m->enc, m->bwd_chunk * m->E}};
+                                                  {&m->delta, B * hw * nh},
+                                                  // two encoding scratches, used by the chunks in turn
+                                                  {&m->enc, (B > m->bwd_chunk ? 2 : 1) * m->bwd_chunk * m->E}};
     for (auto& x : a)
         if (hipMalloc((void**)x.p, sizeof(float) * (size_t)std::max<int64_t>(x.n, 1)) != hipSuccess) {
             (void)hipGetLastError();
@@ -798,7 +800,7 @@ __global__ void __launch_bounds__(64 * kDwSumGroups) k_dw_sum(DwArgs A, float* _
 // lanes on the same level.  d enc = W0^T delta_0 is formed on MFMA in the same layout: the
 // 16 output rows of one step are (combination 4u + r/4, features of the level pair), so
 // lane (q, j) receives exactly the four d enc values of its own combination and sample.
-// dW0 comes from the stored encoding (k_dw_part, k_dw_sum).  Samples are processed in chunks so the
+// dW0 comes from the forward's encoding (weight_grad).  Samples are processed in chunks so the
 // addition buffer stays bounded.
 
 struct EncBwdParams {
@@ -1687,71 +1689,104 @@ static void tg_end(nif_model* m, const TgRound& R, hipStream_t sd) {
     else tg_end_fd<2>(m, R, sd);
 }
 
-// Backward from m->dz.  enc_stored: the forward's encoding [B][E], or null to recompute it
-// per chunk of bwd_chunk samples for the first layer's weight gradient.
-static int backward_core(nif_model* m, const float* x0, const float* x1, int64_t B, float* dx0, float* dx1,
-                         int32_t precision, const float* enc_stored, hipStream_t st) {
-    const int hw = m->desc.hidden_width, nh = m->desc.hidden_layers;
+// Transposed weights of the affine layers past the first, in the MLP precision.
+static BwdParams mlp_bwd_params(const nif_model* m, int32_t precision) {
     BwdParams bp;
     memset(&bp, 0, sizeof(bp));
-    bp.n_hidden = nh;
+    bp.n_hidden = m->desc.hidden_layers;
     for (int i = 1; i < m->n_layers; ++i) {
         if (precision == NIF_PREC_FP32) bp.Wt[i] = m->mlp_pad_f32 + m->wt_off[i];
         else if (precision == NIF_PREC_BF16) bp.Wt[i] = m->mlp_pad_bf16 + m->wt_off[i];
         else bp.Wt[i] = m->mlp_pad_f16 + m->wt_off[i];
     }
-    int rc;
-    if (precision == NIF_PREC_FP32) rc = dispatch_mlp_bwd<P_FP32>(hw, bp, m->dz, m->acts, m->delta, B, st);
-    else if (precision == NIF_PREC_BF16) rc = dispatch_mlp_bwd<P_BF16>(hw, bp, m->dz, m->acts, m->delta, B, st);
-    else rc = dispatch_mlp_bwd<P_FP16>(hw, bp, m->dz, m->acts, m->delta, B, st);
-    if (rc) return rc;
-    // Fork: the table-gradient chain (reads delta[0], x0, x1; writes the table gradient and, by
-    // atomics, dx0 / dx1) runs on the model's side stream while this stream forms the weight
-    // gradients (reads the deltas, activations and the encoding; writes the MLP gradient); the
-    // two touch disjoint scratch.
-    hipStream_t sd = m->side;
-    if ((rc = check_hip(hipEventRecord(m->ev_fork, st), "backward fork"))) return rc;
-    if ((rc = check_hip(hipStreamWaitEvent(sd, m->ev_fork, 0), "backward fork"))) return rc;
-    // encoding backward (layer 0): count / scan / fill / reduce per round of samples
-    const EncBwdParams ep = table_grad_params(m, x0, x1, B, dx0, dx1);
-    for (int64_t c0 = 0; c0 < B; c0 += m->bwd_round) {
-        const int64_t n = std::min<int64_t>(m->bwd_round, B - c0);
-        const TgRound R = tg_begin(m, ep, c0, n, sd);
-        tg_fill(m, R, m->delta, 0, c0, n, sd);
-        tg_end(m, R, sd);
-    }
-    if ((rc = check_hip(hipEventRecord(m->ev_join, sd), "backward join"))) return rc;
-    // weight gradients of every layer (layer 0 from the stored or the recomputed encoding)
+    return bp;
+}
+
+// Forward and gradients of a batch, chunk by chunk of bwd_chunk samples: forward, d heads
+// (`heads(c0, n, z, dz)` enqueues the kernel that turns the chunk's heads z into dz), MLP
+// backward; then the chunk's table gradient goes to the model's side stream while this stream
+// forms its weight gradients and moves on to the next chunk.  Chunk c keeps its heads, d heads,
+// activations and deltas in rows of its own block of the batch-sized buffers, so the side stream
+// can still read chunk c's deltas meanwhile (it writes the table gradient and, by atomics,
+// dx0 / dx1: nothing this stream touches before the join).
+// The weight gradients of chunk c are issued after chunk c + 1's MLP backward, so the next fill
+// can start as early as possible.  The first layer's reads the encoding the chunk's forward
+// left: in its rows of enc_all [B][E] if given, else in one of two chunk scratches used in turn
+// (chunk c + 2's forward comes after chunk c's weight gradients on this stream).  A
+// 2^17-sample chunk's 436 MB cost about 0.2 ms to write and read; gathering the encoding again
+// for the weight gradient, as before, took 2.2 ms.
+// A table-gradient round (up to bwd_round samples, whole chunks) counts and scans its additions
+// as soon as it begins (the positions are known), fills once per chunk after that chunk's MLP
+// backward, and reduces after its last chunk.  On return both streams are joined.
+template <class Heads>
+static int gradient_chunks(nif_model* m, const float* x0, const float* x1, int64_t B, int32_t prec, float* enc_all,
+                           float* dx0, float* dx1, Heads heads, hipStream_t st) {
+    const int hw = m->desc.hidden_width, nh = m->desc.hidden_layers, H = m->H;
+    const BwdParams bp = mlp_bwd_params(m, prec);
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
-    for (int i = 0; i < m->n_layers; ++i) {
-        const bool out = i == m->n_layers - 1;
-        const float* d = out ? m->dz : m->delta + (size_t)i * B * hw;
-        const int ds = out ? 16 : hw;
-        if (rc) break;
-        if (i > 0) {
-            rc = weight_grad(m, i, d, ds, ds, m->acts + (size_t)(i - 1) * B * hw, B, cus, precision, st);
-        } else if (enc_stored) {
-            rc = weight_grad(m, 0, d, ds, ds, enc_stored, B, cus, precision, st);
-        } else {
-            for (int64_t c0 = 0; c0 < B && !rc; c0 += m->bwd_chunk) {
-                const int64_t n = std::min<int64_t>(m->bwd_chunk, B - c0);
-                if (!(rc = encode_pairs_launch(m, x0 + c0, x1 + c0, n, B, precision, m->enc, st)))
-                    rc = weight_grad(m, 0, d + (size_t)c0 * ds, ds, ds, m->enc, n, cus, precision, st);
-            }
+    const EncBwdParams ep = table_grad_params(m, x0, x1, B, dx0, dx1);
+    hipStream_t sd = m->side;
+    auto chunk_enc = [&](int64_t c0) {
+        return enc_all ? enc_all + (size_t)c0 * m->E : m->enc + (size_t)((c0 / m->bwd_chunk) & 1) * m->bwd_chunk * m->E;
+    };
+    auto chunk_weight_grads = [&](int64_t c0, int64_t n) {
+        const float* acts_c = m->acts + (size_t)c0 * nh * hw;
+        const float* delta_c = m->delta + (size_t)c0 * nh * hw;
+        int r = NIF_OK;
+        for (int i = 0; i < m->n_layers && !r; ++i) {
+            const bool out = i == m->n_layers - 1;
+            const float* d = out ? m->dz + (size_t)c0 * 16 : delta_c + (size_t)i * n * hw;
+            const int ds = out ? 16 : hw;
+            r = weight_grad(m, i, d, ds, ds, i > 0 ? acts_c + (size_t)(i - 1) * n * hw : chunk_enc(c0), n, cus, prec, st);
         }
+        return r;
+    };
+    int rc = NIF_OK;
+    bool forked = false, round_open = false;
+    int64_t prev_c0 = -1, prev_n = 0, round_end = 0;
+    TgRound R;
+    memset(&R, 0, sizeof(R));
+    auto fork = [&]() {
+        int r = check_hip(hipEventRecord(m->ev_fork, st), "gradient fork");
+        if (!r) r = check_hip(hipStreamWaitEvent(sd, m->ev_fork, 0), "gradient fork");
+        forked = forked || !r;
+        return r;
+    };
+    for (int64_t c0 = 0; c0 < B && !rc; c0 += m->bwd_chunk) {
+        const int64_t n = std::min<int64_t>(m->bwd_chunk, B - c0);
+        float* acts_c = m->acts + (size_t)c0 * nh * hw;      // [hidden layers][n][hw]
+        float* delta_c = m->delta + (size_t)c0 * nh * hw;
+        float* z_c = m->zbuf + (size_t)c0 * H;
+        float* dz_c = m->dz + (size_t)c0 * 16;
+        if (c0 >= round_end) {                  // a round begins with this chunk
+            if (round_open) tg_end(m, R, sd);
+            const int64_t rn = std::min<int64_t>(m->bwd_round, B - c0);
+            if ((rc = fork())) break;
+            R = tg_begin(m, ep, c0, rn, sd);
+            round_open = true;
+            round_end = c0 + rn;
+        }
+        if ((rc = forward_rows_launch(m, x0 + c0, x1 + c0, n, B, z_c, prec, acts_c, chunk_enc(c0), st))) break;
+        heads(c0, n, z_c, dz_c);
+        if (prec == NIF_PREC_FP32) rc = dispatch_mlp_bwd<P_FP32>(hw, bp, dz_c, acts_c, delta_c, n, st);
+        else if (prec == NIF_PREC_BF16) rc = dispatch_mlp_bwd<P_BF16>(hw, bp, dz_c, acts_c, delta_c, n, st);
+        else rc = dispatch_mlp_bwd<P_FP16>(hw, bp, dz_c, acts_c, delta_c, n, st);
+        if (rc || (rc = fork())) break;
+        tg_fill(m, R, delta_c, c0, c0, n, sd);     // layer 0 of the chunk's block
+        if (prev_c0 >= 0 && (rc = chunk_weight_grads(prev_c0, prev_n))) break;
+        prev_c0 = c0;
+        prev_n = n;
     }
-    // join before anything that reads the table gradient or dx
-    const int rc_join = check_hip(hipStreamWaitEvent(st, m->ev_join, 0), "backward join");
-    if (rc) return rc;
-    if (rc_join) return rc_join;
-    if (dx0 && m->GW > 0) {                  // concatenated encoding: d x through the raw gamma values
-        const int E_phi = 2 * m->S * m->desc.levels * m->desc.feat_dim;
-        hipLaunchKernelGGL(k_gamma_dx, dim3(grid_for(B)), dim3(256), 0, st, m->mlp_pad_f32 + m->wt_off[0], m->delta,
-                           hw, E_phi, m->GW, x0, x1, B, dx0, dx1);
+    if (!rc && round_open) tg_end(m, R, sd);
+    if (!rc && prev_c0 >= 0) rc = chunk_weight_grads(prev_c0, prev_n);
+    if (forked) {                               // join before the gradients are read
+        const int rj = check_hip(hipEventRecord(m->ev_join, sd), "gradient join");
+        const int rw = rj ? rj : check_hip(hipStreamWaitEvent(st, m->ev_join, 0), "gradient join");
+        if (!rc) rc = rw;
     }
-    return check_hip(hipGetLastError(), "backward launch");
+    return rc ? rc : check_hip(hipGetLastError(), "gradient launch");
 }
 
 // Zero the gradient accumulators with kernels (no memset nodes when the caller captures a graph).
@@ -1765,12 +1800,22 @@ int zero_grads_launch(nif_model* m, hipStream_t st) {
 int backward_launch(nif_model* m, const float* x0, const float* x1, int64_t B, const float* dh, int32_t, float* dx0,
                     float* dx1, int32_t precision, hipStream_t st) {
     if (B == 0) return NIF_OK;
-    int rc = forward_launch(m, x0, x1, B, m->zbuf, precision, m->acts, nullptr, st);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_pad_dz, dim3(grid_for(B * 16)), dim3(256), 0, st, dh, m->H, B, m->dz);
     if (dx0) hipLaunchKernelGGL(k_zero_f32, dim3(grid_for(3 * B)), dim3(256), 0, st, dx0, 3 * B);
     if (dx1) hipLaunchKernelGGL(k_zero_f32, dim3(grid_for(3 * B)), dim3(256), 0, st, dx1, 3 * B);
-    return backward_core(m, x0, x1, B, dx0, dx1, precision, nullptr, st);
+    const int rc = gradient_chunks(m, x0, x1, B, precision, nullptr, dx0, dx1, [&](int64_t c0, int64_t n, float*, float* dz) {
+        hipLaunchKernelGGL(k_pad_dz, dim3(grid_for(n * 16)), dim3(256), 0, st, dh + c0 * m->H, m->H, n, dz);
+    }, st);
+    if (rc) return rc;
+    if (dx0 && m->GW > 0) {                  // concatenated encoding: d x through the raw gamma values
+        const int hw = m->desc.hidden_width, nh = m->desc.hidden_layers;
+        const int E_phi = 2 * m->S * m->desc.levels * m->desc.feat_dim;
+        for (int64_t c0 = 0; c0 < B; c0 += m->bwd_chunk) {
+            const int64_t n = std::min<int64_t>(m->bwd_chunk, B - c0);
+            hipLaunchKernelGGL(k_gamma_dx, dim3(grid_for(n)), dim3(256), 0, st, m->mlp_pad_f32 + m->wt_off[0],
+                               m->delta + (size_t)c0 * nh * hw, hw, E_phi, m->GW, x0 + c0, x1 + c0, n, B, dx0 + c0, dx1 + c0);
+        }
+    }
+    return check_hip(hipGetLastError(), "backward launch");
 }
 
 int loss_launch(nif_model* m, const float* heads, int64_t B, const nif_batch* b, const float* s, int32_t fixed,
@@ -1805,98 +1850,13 @@ int train_step_launch(nif_model* m, const nif_batch* b_in, int64_t B, const nif_
     hipLaunchKernelGGL(k_count_pos, dim3(grid_for(B)), dim3(256), 0, st, b->hit, B, m->tcount);
     hipLaunchKernelGGL(k_zero_f32, dim3(grid_for(m->n_table)), dim3(256), 0, st, m->g_tables, m->n_table);
     hipLaunchKernelGGL(k_zero_f32, dim3(grid_for(m->n_mlp)), dim3(256), 0, st, m->g_mlp, m->n_mlp);
-    // The step runs per chunk of bwd_chunk samples: forward, loss rows (the means use the whole
-    // batch's size and positive count, known before), MLP backward; then the chunk's table
-    // gradient goes to the side stream while this stream forms its weight gradients (the first
-    // layer's from the encoding, recomputed unless stored) and moves on to the next chunk.
-    // Chunk c keeps its heads, d heads, activations and deltas in rows of its own block of the
-    // batch-sized buffers, so the side stream can still read chunk c's deltas meanwhile.
-    const int hw = m->desc.hidden_width, nh = m->desc.hidden_layers, H = m->H;
-    BwdParams bp;
-    memset(&bp, 0, sizeof(bp));
-    bp.n_hidden = nh;
-    for (int i = 1; i < m->n_layers; ++i) {
-        if (prec == NIF_PREC_FP32) bp.Wt[i] = m->mlp_pad_f32 + m->wt_off[i];
-        else if (prec == NIF_PREC_BF16) bp.Wt[i] = m->mlp_pad_bf16 + m->wt_off[i];
-        else bp.Wt[i] = m->mlp_pad_f16 + m->wt_off[i];
-    }
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus = 256;
-    EncBwdParams ep = table_grad_params(m, b->x0, b->x1, B, nullptr, nullptr);
-    hipStream_t sd = m->side;
-    int rc = NIF_OK;
-    bool forked = false;
-    // weight gradients of the chunk at rows [c0, c0 + n)
-    auto chunk_weight_grads = [&](int64_t c0, int64_t n) {
-        float* acts_c = m->acts + (size_t)c0 * nh * hw;
-        float* delta_c = m->delta + (size_t)c0 * nh * hw;
-        float* dz_c = m->dz + (size_t)c0 * 16;
-        float* enc_c = cfg->store_encoding ? m->enc_all + (size_t)c0 * m->E : nullptr;
-        int r = NIF_OK;
-        for (int i = 0; i < m->n_layers && !r; ++i) {
-            const bool out = i == m->n_layers - 1;
-            const float* d = out ? dz_c : delta_c + (size_t)i * n * hw;
-            const int ds = out ? 16 : hw;
-            if (i > 0) {
-                r = weight_grad(m, i, d, ds, ds, acts_c + (size_t)(i - 1) * n * hw, n, cus, prec, st);
-            } else if (enc_c) {
-                r = weight_grad(m, 0, d, ds, ds, enc_c, n, cus, prec, st);
-            } else if (!(r = encode_pairs_launch(m, b->x0 + c0, b->x1 + c0, n, B, prec, m->enc, st))) {
-                r = weight_grad(m, 0, d, ds, ds, m->enc, n, cus, prec, st);
-            }
-        }
-        return r;
-    };
-    // The weight gradients of chunk c are issued after chunk c + 1's MLP backward, so the next
-    // fill (the longer branch) can start as early as possible.  A table-gradient round (up to
-    // bwd_round samples, whole chunks) counts and scans its additions as soon as it begins (the
-    // positions are known), fills once per chunk after that chunk's MLP backward, and reduces
-    // after its last chunk.
-    int64_t prev_c0 = -1, prev_n = 0;
-    int64_t round_end = 0;
-    TgRound R;
-    memset(&R, 0, sizeof(R));
-    bool round_open = false;
-    for (int64_t c0 = 0; c0 < B && !rc; c0 += m->bwd_chunk) {
-        const int64_t n = std::min<int64_t>(m->bwd_chunk, B - c0);
-        float* acts_c = m->acts + (size_t)c0 * nh * hw;      // [hidden layers][n][hw]
-        float* delta_c = m->delta + (size_t)c0 * nh * hw;
-        float* z_c = m->zbuf + (size_t)c0 * H;
-        float* dz_c = m->dz + (size_t)c0 * 16;
-        float* enc_c = cfg->store_encoding ? m->enc_all + (size_t)c0 * m->E : nullptr;
-        if (c0 >= round_end) {                  // a round begins with this chunk
-            if (round_open) tg_end(m, R, sd);
-            const int64_t rn = std::min<int64_t>(m->bwd_round, B - c0);
-            if ((rc = check_hip(hipEventRecord(m->ev_fork, st), "train fork"))) break;
-            if ((rc = check_hip(hipStreamWaitEvent(sd, m->ev_fork, 0), "train fork"))) break;
-            forked = true;
-            R = tg_begin(m, ep, c0, rn, sd);
-            round_open = true;
-            round_end = c0 + rn;
-        }
-        if ((rc = forward_rows_launch(m, b->x0 + c0, b->x1 + c0, n, B, z_c, prec, acts_c, enc_c, st))) break;
-        hipLaunchKernelGGL(k_loss, dim3(grid_for(n)), dim3(256), 0, st, z_c, H, n, B, B, b->hit + c0, b->t + c0,
-                           b->n + c0, b->a + c0, b->m + c0, m->s, m->tcount, m->dacc, dz_c, 16, b->x0 + c0, b->x1 + c0,
+    // per chunk; the loss rows' means use the whole batch's size and positive count, known before
+    int rc = gradient_chunks(m, b->x0, b->x1, B, prec, cfg->store_encoding ? m->enc_all : nullptr, nullptr, nullptr,
+                             [&](int64_t c0, int64_t n, float* z, float* dz) {
+        hipLaunchKernelGGL(k_loss, dim3(grid_for(n)), dim3(256), 0, st, z, m->H, n, B, B, b->hit + c0, b->t + c0,
+                           b->n + c0, b->a + c0, b->m + c0, m->s, m->tcount, m->dacc, dz, 16, b->x0 + c0, b->x1 + c0,
                            m->desc.dist_head, cfg->fixed_task_weights);
-        if (prec == NIF_PREC_FP32) rc = dispatch_mlp_bwd<P_FP32>(hw, bp, dz_c, acts_c, delta_c, n, st);
-        else if (prec == NIF_PREC_BF16) rc = dispatch_mlp_bwd<P_BF16>(hw, bp, dz_c, acts_c, delta_c, n, st);
-        else rc = dispatch_mlp_bwd<P_FP16>(hw, bp, dz_c, acts_c, delta_c, n, st);
-        if (rc) break;
-        if ((rc = check_hip(hipEventRecord(m->ev_fork, st), "train fork"))) break;
-        if ((rc = check_hip(hipStreamWaitEvent(sd, m->ev_fork, 0), "train fork"))) break;
-        tg_fill(m, R, delta_c, c0, c0, n, sd);     // layer 0 of the chunk's block
-        if (prev_c0 >= 0 && (rc = chunk_weight_grads(prev_c0, prev_n))) break;
-        prev_c0 = c0;
-        prev_n = n;
-    }
-    if (!rc && round_open) tg_end(m, R, sd);
-    if (!rc && prev_c0 >= 0) rc = chunk_weight_grads(prev_c0, prev_n);
-    if (forked) {                               // join before the gradients are read
-        const int rj = check_hip(hipEventRecord(m->ev_join, sd), "train join");
-        const int rw = rj ? rj : check_hip(hipStreamWaitEvent(st, m->ev_join, 0), "train join");
-        if (!rc) rc = rw;
-    }
+    }, st);
     if (rc) return rc;
     hipLaunchKernelGGL(k_check_finite, dim3(grid_for(m->n_table)), dim3(256), 0, st, m->g_tables, m->n_table, m->tcount);
     hipLaunchKernelGGL(k_check_finite, dim3(grid_for(m->n_mlp)), dim3(256), 0, st, m->g_mlp, m->n_mlp, m->tcount);
