@@ -37,7 +37,8 @@ HBM_PEAK_GBS = 8000.0
 # plain 1 GiB device copy (bench.py --calibrate-copy).  They hold only for the kernel sources they
 # were taken on and the ray generator of the workload (SHA-256 of KQUERY_SOURCES); otherwise the
 # traffic is reported as null.
-KQUERY_SOURCES = ["paper_2604_24666_amd/csrc/nif_query.hip", "paper_2604_24666_amd/csrc/nif_net.hpp",
+KQUERY_SOURCES = ["paper_2604_24666_amd/csrc/nif_query.hip", "paper_2604_24666_amd/csrc/nif_query.hpp",
+                  "paper_2604_24666_amd/csrc/nif_query_fp32.hip", "paper_2604_24666_amd/csrc/nif_net.hpp",
                   "paper_2604_24666_amd/csrc/nif_trace.hpp", "paper_2604_24666_amd/csrc/nif_device.hpp",
                   "paper_2604_24666_amd/csrc/nif_internal.hpp", "paper_2604_24666_amd/build.py",
                   "nif_synth/__init__.py"]

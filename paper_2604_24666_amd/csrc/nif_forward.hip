@@ -1,0 +1,265 @@
+// The network on given rest-space points: nif_encode, nif_forward and the training forward.
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+#include "nif_internal.hpp"
+#include "nif_panels.hpp"
+
+namespace nif {
+
+// ------------------------------------------------------------------ network on given points
+
+// Full encoding of n points (lane per point): out[i][(s L + l) Fd + f].
+__global__ void __launch_bounds__(256) k_encode(EncParams ep, const float* __restrict__ x, int64_t n,
+                                                float* __restrict__ out) {
+    const int S = 1 + 2 * ep.F;
+    const int W = S * ep.L * ep.Fd;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        PEState pe;
+        pe_begin(pe, x[i], x[n + i], x[2 * n + i]);
+        for (int s = 0; s < S; ++s) {
+            double smp[3];
+            pe_sample(pe, s, smp);
+            for (int l = 0; l < ep.L; ++l) {
+                float* o = out + i * W + (s * ep.L + l) * ep.Fd;
+                if (ep.f16) grid_lookup_any<true>(ep, l, smp[0], smp[1], smp[2], set_offset(ep, s), o);
+                else grid_lookup_any<false>(ep, l, smp[0], smp[1], smp[2], set_offset(ep, s), o);
+            }
+        }
+    }
+}
+
+// Heads of point pairs for the method variants (concatenated encoding, three features), gathers
+// and MLP fused.  Each wave evaluates tiles of TILE pairs; acts (nullable) receives the hidden
+// activations [layer][B][HW] and enc (nullable) the encoding [B][E], for the training backward.
+// x0 / x1 are SoA with row stride ld >= B.
+template <int HW, int PREC, bool GAMMA, int TILE, int FD>
+__global__ void __launch_bounds__(256, 2) k_forward(NetParams np, const float* __restrict__ x0, const float* __restrict__ x1,
+                                                 int64_t B, int64_t ld, float* __restrict__ heads,
+                                                 float* __restrict__ acts, float* __restrict__ enc) {
+    constexpr int CB = TILE == 16 || HW >= 128 ? 1 : 4;
+    constexpr int PASSES = TILE / 16 / CB;
+    __shared__ float s_seg_all[4][64 * kSegStride];
+    __shared__ float s_z_all[4][64 * kZStride];
+    const int w = threadIdx.x >> 6;
+    const int lane = lane_id();
+    float* s_seg = s_seg_all[w];
+    float* s_z = s_z_all[w];
+    const int64_t n_tiles = (B + TILE - 1) / TILE;
+    const int64_t wave_g = (int64_t)blockIdx.x * 4 + w, n_waves = (int64_t)gridDim.x * 4;
+    for (int64_t tile = wave_g; tile < n_tiles; tile += n_waves) {
+        const int64_t seg = tile * TILE + lane;
+        float* my = s_seg + lane * kSegStride;
+        if (lane < TILE && seg < B) {
+            my[0] = x0[seg]; my[1] = x0[ld + seg]; my[2] = x0[2 * ld + seg];
+            my[4] = x1[seg]; my[5] = x1[ld + seg]; my[6] = x1[2 * ld + seg];
+        } else {
+            my[0] = my[1] = my[2] = my[4] = my[5] = my[6] = 0.5f;
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int ps = 0; ps < PASSES; ++ps)
+            net_pass<HW, CB, PREC, GAMMA, FD>(np, s_seg, ps * 16 * CB, s_z, acts, B * HW, tile * TILE + ps * 16 * CB, B, enc);
+        wave_lds_sync();
+        if (lane < TILE && seg < B)
+            for (int h = 0; h < np.H; ++h) heads[seg * np.H + h] = s_z[lane * kZStride + h];
+        wave_lds_sync();
+    }
+}
+
+// Heads of n point pairs from their panels: the first layer reads them as MFMA operands, the
+// rest of the MLP as in the fused kernels.  acts as in k_forward.  A wave takes 16 CB pairs, so
+// its first-layer weights (229 KB at width 64 in FP32, streamed through L1) serve CB columns.
+// Bound: at width 128 the FP32 MFMA rate (41 GFLOP per 2^17 pairs), in 16 bits the panels' bytes.
+template <int HW, int CB, int PREC>
+__global__ void __launch_bounds__(256, 2) k_mlp_panels(NetParams np, const float2* __restrict__ enc, int64_t n,
+                                                       float* __restrict__ heads, float* __restrict__ acts) {
+    __shared__ float s_z_all[4][16 * CB * kZStride];
+    const int w = threadIdx.x >> 6, lane = lane_id();
+    float* s_z = s_z_all[w];
+    const int64_t n_tiles = (n + 16 * CB - 1) / (16 * CB);
+    const int64_t n_waves = (int64_t)gridDim.x * 4;
+    for (int64_t tile = (int64_t)blockIdx.x * 4 + w; tile < n_tiles; tile += n_waves) {
+        const int64_t i0 = tile * 16 * CB;
+        floatx4 acc[HW / 16][CB];
+        layer1_bias<HW, CB>(np, acc);
+        layer1_panels<HW, CB, PREC>(np, enc, n, i0, acc);
+        mlp_tail<HW, CB, PREC>(np, acc, 0, s_z, acts, n * HW, i0, n);
+        wave_lds_sync();
+        if (lane < 16 * CB && i0 + lane < n)
+            for (int h = 0; h < np.H; ++h) heads[(i0 + lane) * np.H + h] = s_z[lane * kZStride + h];
+        wave_lds_sync();
+    }
+}
+
+// ------------------------------------------------------------------ host launchers
+
+NetParams make_net_params(const nif_model* m, int32_t precision) {
+    NetParams np;
+    memset(&np, 0, sizeof(np));
+    const nif_model_desc& d = m->desc;
+    np.enc.tab = d.table_dtype == NIF_TABLE_F16 ? (const void*)m->tables_h : (const void*)m->tables;
+    np.enc.f16 = d.table_dtype == NIF_TABLE_F16;
+    np.enc.L = d.levels;
+    np.enc.Fd = d.feat_dim;
+    np.enc.log2T = d.log2_table;
+    np.enc.F = d.concat_encoding ? 0 : d.pe_freqs;      // the grid sees x only in the concatenated form
+    np.gamma_F = d.concat_encoding ? d.pe_freqs : -1;
+    np.E_phi = 2 * m->S * d.levels * d.feat_dim;
+    np.enc.dense_mask = 0;
+    np.enc.set_stride = d.per_sample_tables ? ((int64_t)d.levels << d.log2_table) : 0;
+    for (int l = 0; l < d.levels; ++l) {
+        np.enc.res[l] = d.res[l];
+        const uint64_t n1 = (uint64_t)d.res[l] + 1;
+        if (n1 * n1 * n1 <= (1ull << d.log2_table)) np.enc.dense_mask |= 1u << l;
+    }
+    for (int i = 0; i < m->n_layers; ++i) {
+        if (precision == NIF_PREC_FP32) np.W[i] = m->mlp_pad_f32 + m->wp_off[i];
+        else if (precision == NIF_PREC_BF16) np.W[i] = m->mlp_pad_bf16 + m->wp_off[i];
+        else np.W[i] = m->mlp_pad_f16 + m->wp_off[i];
+        np.b[i] = m->mlp_pad_f32 + m->bp_off[i];
+    }
+    np.W0L = precision == NIF_PREC_FP32 ? (const void*)m->w0l_f32
+           : precision == NIF_PREC_BF16 ? (const void*)m->w0l_bf16 : (const void*)m->w0l_f16;
+    np.n_hidden = d.hidden_layers;
+    np.E = m->E;
+    np.H = m->H;
+    np.dist_head = d.dist_head;
+    return np;
+}
+
+int encode_launch(const nif_model* m, const float* x, int64_t n, float* out, hipStream_t st) {
+    if (n == 0) return NIF_OK;
+    const NetParams np = make_net_params(m, NIF_PREC_FP32);
+    const int64_t blocks = std::min<int64_t>((n + 255) / 256, (int64_t)device_cus() * 16);
+    hipLaunchKernelGGL(k_encode, dim3((unsigned)blocks), dim3(256), 0, st, np.enc, x, n, out);
+    return check_hip(hipGetLastError(), "k_encode launch");
+}
+
+// Items of the level-by-level encoding.  Two parts per level, dealt to the XCDs longest first: an
+// XCD then stays on one level for half of its lookups, and the waves of two levels overlap for a
+// small share of the time (2^17 ordered pairs: 0.72 ms; with every level spread over all XCDs,
+// where the levels overlap for a third of the time, 0.86; whole levels, unbalanced, 0.84).  A
+// hashed level counts twice a dense one (6 against 4 loads, fewer of them in L1).  Tables that
+// fit an L2 together need no such care: every level is spread evenly.
+static EncPlan encode_plan(const EncParams& ep, int64_t n) {
+    EncPlan P;
+    memset(&P, 0, sizeof(P));
+    const int C = 2 * (1 + 2 * ep.F);
+    P.tiles = (int32_t)((n + 255) / 256);
+    P.groups = (C + kEncKC - 1) / kEncKC;
+    const int64_t table_bytes = ((int64_t)ep.L << ep.log2T) * (ep.f16 ? 4 : 8);
+    P.parts = table_bytes <= (4 << 20) ? kEncXcds : 2;
+    P.per_item = (int32_t)(((int64_t)P.tiles * P.groups + P.parts - 1) / P.parts);
+    int load[kEncXcds] = {};
+    for (int pass = 0; pass < 2; ++pass)                // hashed levels first
+        for (int l = 0; l < ep.L; ++l) {
+            const bool dense = (ep.dense_mask >> l) & 1u;
+            if (dense != (pass == 1)) continue;
+            for (int k = 0; k < P.parts; ++k) {
+                int x = 0;
+                for (int y = 1; y < kEncXcds; ++y)
+                    if (load[y] < load[x]) x = y;
+                P.item[x][P.n_items[x]++] = (uint8_t)(l * P.parts + k);
+                load[x] += dense ? 1 : 2;
+            }
+        }
+    return P;
+}
+
+// Positions and panels of n pairs (SoA with stride ld).
+static void launch_panels(const NetParams& np, const float* x0, const float* x1, int64_t n, int64_t ld, uint32_t* pos,
+                          float* enc, hipStream_t st) {
+    const unsigned pb = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_positions, dim3(pb, 4), dim3(256), 0, st, np.enc.F, x0, x1, n, ld, pos);
+    const EncPlan P = encode_plan(np.enc, n);
+    int most = 0;
+    for (int x = 0; x < kEncXcds; ++x) most = std::max(most, (int)P.n_items[x]);
+    const dim3 g((unsigned)(kEncXcds * most * (int64_t)P.per_item));
+    if (np.enc.f16) hipLaunchKernelGGL((k_encode_levels<kEncKC, true>), g, dim3(256), 0, st, np.enc, P, pos, n, (float2*)enc);
+    else hipLaunchKernelGGL((k_encode_levels<kEncKC, false>), g, dim3(256), 0, st, np.enc, P, pos, n, (float2*)enc);
+}
+
+template <int HW, int CB, int PREC>
+static void launch_mlp(const NetParams& np, const float* enc, int64_t n, float* heads, float* acts, hipStream_t st) {
+    const int64_t tiles = (n + 16 * CB - 1) / (16 * CB);
+    const unsigned blocks = (unsigned)std::min<int64_t>((tiles + 3) / 4, (int64_t)device_cus() * 8);
+    hipLaunchKernelGGL((k_mlp_panels<HW, CB, PREC>), dim3(blocks), dim3(256), 0, st, np, (const float2*)enc, n, heads, acts);
+}
+
+// enc: panels of n pairs (panel_stride(n) E floats), or rows [n][E] (nullable) for the variants.
+template <int HW, int PREC>
+static void launch_forward(const NetParams& np, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
+                           float* acts, float* enc, uint32_t* pos, hipStream_t st) {
+    if (np.gamma_F < 0 && np.enc.Fd == 2) {
+        launch_panels(np, x0, x1, n, ld, pos, enc, st);
+        // 16 pairs per wave until two waves per SIMD are busy, then as many as the registers hold
+        constexpr int CB = HW >= 128 ? 2 : 4;
+        if (n < (int64_t)device_cus() * 8 * 16 * CB) launch_mlp<HW, 1, PREC>(np, enc, n, heads, acts, st);
+        else launch_mlp<HW, CB, PREC>(np, enc, n, heads, acts, st);
+        return;
+    }
+    // small launches (up to 2^17 pairs) take 16 pairs per wave so that they still fill the chip
+    const bool gamma = np.gamma_F >= 0, small = n <= (1 << 17);
+    const int64_t tiles = small || !gamma ? (n + 15) / 16 : (n + 63) / 64;
+    const int64_t blocks = std::min<int64_t>((tiles + 3) / 4, (int64_t)device_cus() * 8);
+    const dim3 g((unsigned)std::max<int64_t>(blocks, 1)), b(256);
+    if (!gamma)                      // three-feature entries: 16 pairs per wave throughout
+        hipLaunchKernelGGL((k_forward<HW, PREC, false, 16, 3>), g, b, 0, st, np, x0, x1, n, ld, heads, acts, enc);
+    else if (small) hipLaunchKernelGGL((k_forward<HW, PREC, true, 16, 2>), g, b, 0, st, np, x0, x1, n, ld, heads, acts, enc);
+    else hipLaunchKernelGGL((k_forward<HW, PREC, true, 64, 2>), g, b, 0, st, np, x0, x1, n, ld, heads, acts, enc);
+}
+
+template <int PREC>
+static int dispatch_forward(int hw, const NetParams& np, const float* x0, const float* x1, int64_t n, int64_t ld,
+                            float* heads, float* acts, float* enc, uint32_t* pos, hipStream_t st) {
+    switch (hw) {
+        case 16: launch_forward<16, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st); break;
+        case 32: launch_forward<32, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st); break;
+        case 64: launch_forward<64, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st); break;
+        case 128: launch_forward<128, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st); break;
+        default: return fail(NIF_E_UNSUPPORTED, "hidden_width must be 16, 32, 64 or 128");
+    }
+    return NIF_OK;
+}
+
+bool uses_panels(const nif_model* m) { return m->desc.feat_dim == 2 && !m->desc.concat_encoding; }
+
+int forward_rows_launch(const nif_model* m, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
+                        int32_t precision, float* acts, float* enc, uint32_t* pos, hipStream_t st) {
+    if (n == 0) return NIF_OK;
+    if (heads == nullptr || ld < n || (uses_panels(m) && (!enc || !pos)))
+        return fail(NIF_E_INVALID_ARG, "forward needs a heads buffer, ld >= n and its encoding scratch");
+    const NetParams np = make_net_params(m, precision);
+    const int hw = m->desc.hidden_width;
+    int rc;
+    if (precision == NIF_PREC_FP32) rc = dispatch_forward<P_FP32>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st);
+    else if (precision == NIF_PREC_BF16) rc = dispatch_forward<P_BF16>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st);
+    else rc = dispatch_forward<P_FP16>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st);
+    if (rc) return rc;
+    return check_hip(hipGetLastError(), "forward launch");
+}
+
+// Chunk of nif_forward: its panels stay within 128 MB, half of the Infinity Cache, so the MLP
+// reads them from there; 40,192 pairs at E = 832, at most 2^17.
+int64_t forward_chunk(const nif_model* m) {
+    const int64_t per = (int64_t)m->E * 4;
+    return std::max<int64_t>(4096, std::min<int64_t>(1 << 17, ((int64_t)1 << 27) / per / 256 * 256));
+}
+
+int forward_launch(const nif_model* m, const float* x0, const float* x1, int64_t B, float* heads, int32_t precision,
+                   hipStream_t st) {
+    if (!uses_panels(m)) return forward_rows_launch(m, x0, x1, B, B, heads, precision, nullptr, nullptr, nullptr, st);
+    const int64_t most = forward_chunk(m), parts = (B + most - 1) / most;
+    const int64_t chunk = parts > 0 ? ((B + parts - 1) / parts + 255) / 256 * 256 : 0;     // even chunks
+    for (int64_t c0 = 0; c0 < B; c0 += chunk) {
+        const int64_t n = std::min<int64_t>(chunk, B - c0);
+        const int rc = forward_rows_launch(m, x0 + c0, x1 + c0, n, B, heads + c0 * m->H, precision, nullptr,
+                                           m->fwd_enc, m->fwd_pos, st);
+        if (rc) return rc;
+    }
+    return NIF_OK;
+}
+
+}  // namespace nif

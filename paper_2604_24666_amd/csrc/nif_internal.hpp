@@ -66,6 +66,7 @@ struct nif_model {
     float* delta = nullptr;             // [hidden_layers][max_batch][hidden_width] d loss / d pre-activation
     float* enc = nullptr;               // [1 or 2][bwd_chunk][E] a chunk's encoding, from its forward to its
                                         //   first-layer dW (two scratches in turn with several chunks)
+    uint32_t* pos = nullptr;            // [6 S][bwd_chunk] a training chunk's positions (panels only)
     float* enc_all = nullptr;           // [max_batch][E] stored encoding (store_encoding steps only;
                                         //   allocated by nif_model_reserve_encoding)
     int64_t bwd_chunk = 0;              // samples per training chunk (forward, MLP backward, one fill launch)
@@ -84,6 +85,8 @@ struct nif_model {
     int32_t step = 0;
     bool params_set = false;
     int64_t* counters = nullptr;        // [8] query work counters
+    float* fwd_enc = nullptr;           // panels of one chunk of nif_forward (forward_chunk pairs)
+    uint32_t* fwd_pos = nullptr;        //   and their positions
 };
 
 namespace nif {
@@ -103,6 +106,7 @@ int voxelize_launch(int32_t scene_kind, const float* params_dev, int32_t N, uint
                     hipStream_t st);
 
 // nif_query.hip
+int device_cus();
 int trace_launch(const nif_grid* g, const nif_rays* r, int64_t n, int32_t max_seg,
                  const nif_segments* out, hipStream_t st);
 int query_launch(const nif_model* m, const nif_grid* g, const nif_rays* r, int64_t n,
@@ -112,7 +116,6 @@ int set_query_blocks_per_cu(int v);
 int set_query_rays_per_wave(int v);
 int autotune_query(const nif_model* m, const nif_grid* g, const nif_rays* r, int64_t n, const nif_hits* out,
                    int32_t precision, int32_t reps, int32_t* best, float* best_ms, hipStream_t st);
-int encode_launch(const nif_model* m, const float* x, int64_t n, float* out, hipStream_t st);
 int label_launch(int kind, const double* params_host, int32_t n_params, int force_march, const float* x0,
                  const float* x1, int64_t n, uint8_t* hit, float* t, float* nrm, float* alb, int32_t* mat,
                  hipStream_t st);
@@ -122,12 +125,19 @@ constexpr int32_t kLabelScratchDoubles = 4104;
 int label_launch_noalloc(int kind, const double* params_host, int32_t n_params, int force_march, const float* x0,
                          const float* x1, int64_t n, uint8_t* hit, float* t, float* nrm, float* alb, int32_t* mat,
                          hipStream_t st);
+
+// nif_forward.hip
+int encode_launch(const nif_model* m, const float* x, int64_t n, float* out, hipStream_t st);
+// Whether the model's encodings go through level panels (nif_panels.hpp); else rows [n][E].
+bool uses_panels(const nif_model* m);
+int64_t forward_chunk(const nif_model* m);
 int forward_launch(const nif_model* m, const float* x0, const float* x1, int64_t B, float* heads,
-                   int32_t precision, float* acts, float* enc, hipStream_t st);
-// Forward of n pairs whose SoA rows have stride ld (heads [n][H], acts [layers][n][HW] and enc
-// [n][E] local to the n rows).
+                   int32_t precision, hipStream_t st);
+// Forward of n pairs whose SoA rows have stride ld (heads [n][H], acts [layers][n][HW] local to
+// the n rows); enc: panels of the n pairs or rows [n][E]; pos: 6 S panel_stride(n) words, panels only.
 int forward_rows_launch(const nif_model* m, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
-                        int32_t precision, float* acts, float* enc, hipStream_t st);
+                        int32_t precision, float* acts, float* enc, uint32_t* pos, hipStream_t st);
+
 // nif_train.hip
 int model_alloc(nif_model* m);
 void model_free(nif_model* m);

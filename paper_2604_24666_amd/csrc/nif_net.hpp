@@ -24,6 +24,8 @@
 #pragma once
 #include "nif_device.hpp"
 
+struct nif_model;
+
 namespace nif {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -68,6 +70,8 @@ struct NetParams {
     int32_t gamma_F;             // concatenated encoding: PE frequencies of the appended gamma (-1: none)
     int32_t E_phi;               // encoding columns of the grid part (the gamma part follows)
 };
+
+NetParams make_net_params(const nif_model* m, int32_t precision);
 
 __device__ __forceinline__ uint16_t f2bf(float x) {
     uint32_t u = __float_as_uint(x);

@@ -1,0 +1,263 @@
+// The encoding of many point pairs, table level by table level.
+//
+// The fused kernels walk, per 16 segments, every PE combination and level, so the tables of all
+// levels (32 MiB at 16 levels of 2^19 FP16 entries) pass through each XCD's 4 MB L2 together and
+// most corner loads miss it: random gathers from 32 MiB run at 65 G/s on this GPU, from up to
+// 4 MiB at 264 G/s.  Here all segments of a chunk are encoded at one level before the next, so
+// the level's table (2 MiB) stays in every L2, and the features go to memory as panels that the
+// MLP kernels read back with full lines.
+//
+// Panels: enc[g][i][2], g = l C + c: the two features of level l, PE combination c (point-major,
+// C = 2 S of them) of segment i; rows of panel_stride(n) segments, so that pairs of segments are
+// 16-byte aligned.  Positions: pos[c][axis][i], 32-bit fixed point, the same row length.
+// Both hold exactly the values the fused kernels form in registers.
+#pragma once
+#include <type_traits>
+
+#include "nif_net.hpp"
+
+namespace nif {
+
+__host__ __device__ inline int64_t panel_stride(int64_t n) { return (n + 15) & ~(int64_t)15; }
+
+// Interpolated features of KC fixed-point positions at one (wave-uniform) level: the lookup of
+// lookup_levels with the roles of levels and positions exchanged, the same arithmetic in the
+// same order.
+template <int KC, bool F16>
+__device__ __forceinline__ void lookup_points(const EncParams& ep, int l, const uint32_t (&f)[KC][3],
+                                              const uint32_t (&set_off)[KC], float2 (&out)[KC]) {
+    using E = typename TabTypes<F16>::E;
+    using Pr = typename TabTypes<F16>::Pr;
+    const E* tab = reinterpret_cast<const E*>(ep.tab);
+    const uint32_t mask = (1u << ep.log2T) - 1u;
+    const uint32_t N = (uint32_t)ep.res[l];
+    const bool dense = (ep.dense_mask >> l) & 1u;
+    Pr A[KC][4];
+    E B[KC][4];
+    uint32_t swp[KC], odd[KC];
+    float wx[KC], wy[KC], wz[KC];
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+        uint32_t ix, iy, iz;
+        fix_axis(f[k][0], N, ix, wx[k]);
+        fix_axis(f[k][1], N, iy, wy[k]);
+        fix_axis(f[k][2], N, iz, wz[k]);
+        swp[k] = odd[k] = 0u;
+        const E* tl = tab + (set_off[k] + ((uint32_t)l << ep.log2T));
+        if (dense) {
+            const uint32_t n1 = N + 1u;
+#pragma unroll
+            for (int pp = 0; pp < 4; ++pp) {
+                const uint32_t e = ix + n1 * ((iy + (pp & 1)) + n1 * (iz + (pp >> 1)));
+                __builtin_memcpy(&A[k][pp], tl + e, sizeof(Pr));
+            }
+        } else {
+            odd[k] = ix & 1u;
+#pragma unroll
+            for (int pp = 0; pp < 4; ++pp) {
+                const uint32_t hyz = ((iy + (pp & 1)) * 2654435761u) ^ ((iz + (pp >> 1)) * 805459861u);
+                const uint32_t h0 = (ix ^ hyz) & mask;
+                swp[k] |= (h0 & 1u) << pp;
+                __builtin_memcpy(&A[k][pp], tl + (h0 & ~1u), sizeof(Pr));
+            }
+            if (odd[k]) {
+#pragma unroll
+                for (int pp = 0; pp < 4; ++pp) {
+                    const uint32_t hyz = ((iy + (pp & 1)) * 2654435761u) ^ ((iz + (pp >> 1)) * 805459861u);
+                    B[k][pp] = tl[((ix + 1u) ^ hyz) & mask];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+        float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int pp = 0; pp < 4; ++pp) {
+            E lo, hi;
+            pair_split(A[k][pp], lo, hi);
+            const bool swap = (swp[k] >> pp) & 1u;
+            const E e0 = sel(swap, hi, lo);
+            const E e1 = odd[k] ? B[k][pp] : sel(swap, lo, hi);
+#pragma unroll
+            for (int cx = 0; cx < 2; ++cx) {
+                const int c = 2 * pp + cx;
+                const float wt = (cx ? wx[k] : 1.f - wx[k]) * (((c >> 1) & 1) ? wy[k] : 1.f - wy[k]) *
+                                 (((c >> 2) & 1) ? wz[k] : 1.f - wz[k]);
+                const float2 v = entry_f2(cx ? e1 : e0);
+                acc.x = fmaf(wt, v.x, acc.x);
+                acc.y = fmaf(wt, v.y, acc.y);
+            }
+        }
+        out[k] = acc;
+    }
+}
+
+// Fixed-point PE samples of n point pairs (SoA, stride ld): pos[c][axis][i].  One thread per
+// (pair, quarter of the combinations), the runs of layer1_levels, so that the double-angle
+// recurrence starts where it does there.
+__global__ void __launch_bounds__(256) k_positions(int F, const float* __restrict__ x0, const float* __restrict__ x1,
+                                                   int64_t n, int64_t ld, uint32_t* __restrict__ pos) {
+    const int S = 1 + 2 * F, C = 2 * S, U = (C + 3) >> 2;
+    const int q = blockIdx.y;
+    const int64_t pn = panel_stride(n);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const float sp[8] = {x0[i], x0[ld + i], x0[2 * ld + i], 0.f, x1[i], x1[ld + i], x1[2 * ld + i], 0.f};
+        PEWalk w;
+        w.p = -1;
+        w.k = -1;
+        for (int u = 0; u < U; ++u) {
+            const int c = q * U + u;
+            if (c >= C) break;
+            double v[3];
+            pe_walk(sp, c, S, w, v);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) pos[((int64_t)c * 3 + a) * pn + i] = to_fix32(v[a]);
+        }
+    }
+}
+
+// Work of k_encode_levels: which (level, part) items each XCD goes through, in order.  A part is
+// a share of the level's (combination group, segment tile) workgroups.  Workgroup b runs on XCD
+// b mod 8 (round-robin dispatch; only the speed depends on it).
+constexpr int kEncXcds = 8, kEncMaxItems = 16;
+constexpr int kEncKC = 2;           // combinations per thread
+struct EncPlan {
+    int32_t tiles;                  // 256-segment tiles
+    int32_t groups;                 // groups of kEncKC combinations
+    int32_t parts;                  // parts per level
+    int32_t per_item;               // workgroups of one part
+    uint8_t n_items[kEncXcds];
+    uint8_t item[kEncXcds][kEncMaxItems];   // level * parts + part
+};
+
+// Bound: the rate at which L1 and L2 take the lanes' corner requests (about 5 distinct lines per
+// lookup on hashed levels).  2^17 spatially ordered pairs at 16 levels of 2^19 FP16 entries:
+// 0.72 ms (75 G lookups/s); the fused forward of the same pairs took 1.44 ms, 4,096 pairs 41
+// against 277 us.  Two combinations per thread keep 8 to 16 loads in flight; one takes 0.75 ms,
+// four (fewer waves) 0.84.
+template <int KC, bool F16>
+__global__ void __launch_bounds__(256) k_encode_levels(EncParams ep, EncPlan plan, const uint32_t* __restrict__ pos,
+                                                       int64_t n, float2* __restrict__ enc) {
+    const int S = 1 + 2 * ep.F, C = 2 * S;
+    const int x = (int)(blockIdx.x % kEncXcds), v = (int)(blockIdx.x / kEncXcds);
+    const int it = v / plan.per_item;
+    if (it >= plan.n_items[x]) return;
+    const int item = plan.item[x][it];
+    const int l = item / plan.parts;
+    const int b = (item % plan.parts) * plan.per_item + v % plan.per_item;    // workgroup within the level
+    const int grp = b / plan.tiles;
+    if (grp >= plan.groups) return;
+    const int64_t i = (int64_t)(b % plan.tiles) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int64_t pn = panel_stride(n);
+    uint32_t f[KC][3], so[KC];
+    float2 o[KC];
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+        const int c = min(grp * KC + k, C - 1);
+        so[k] = combo_set_offset(ep, c, S);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) f[k][a] = pos[((int64_t)c * 3 + a) * pn + i];
+    }
+    lookup_points<KC, F16>(ep, l, f, so, o);
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+        const int c = grp * KC + k;
+        if (c < C) enc[((int64_t)l * C + c) * pn + i] = o[k];
+    }
+}
+
+// First layer of segments i0 .. i0 + 16 CB - 1 (of n) from their panels, added to acc: the MFMA
+// steps of layer1_levels in the same order on the same values (lane (q, j) supplies combination
+// q U + u of segment j, level batches of 4), with the next batch's features and weights in flight
+// while this batch multiplies (FP32 at width 128 and CB > 1: features only; a batch's MFMAs take
+// 4,096 cycles there and the weights' registers are the accumulators').
+template <int HW, int CB, int PREC>
+__device__ __forceinline__ void layer1_panels(const NetParams& np, const float2* __restrict__ enc, int64_t n, int64_t i0,
+                                              floatx4 (&acc)[HW / 16][CB]) {
+    constexpr int OB = HW / 16;
+    constexpr bool AHEAD = PREC != P_FP32 || CB == 1 || HW < 128;
+    using W = typename std::conditional<PREC == P_FP32, float4, shortx4>::type;     // half a lane's weights of a batch
+    const int lane = lane_id(), q = lane >> 4, j = lane & 15;
+    const int L = np.enc.L, C = 2 * (1 + 2 * np.enc.F), U = (C + 3) >> 2, NLB = L >> 2;
+    const int64_t pn = panel_stride(n);
+    const W* w0 = reinterpret_cast<const W*>(np.W0L) + lane;
+    int64_t row[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) row[cb] = min(i0 + cb * 16 + j, n - 1);
+    auto load = [&](int t, float2 (&f)[CB][4]) {           // batch t = u NLB + lb
+        const int u = t / NLB, lb = t - u * NLB;
+        const int c = q * U + u;
+        const bool live = c < C;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float2* p = enc + ((int64_t)(4 * lb + k) * C + (live ? c : 0)) * pn;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                f[cb][k] = p[row[cb]];
+                if (!live) f[cb][k] = make_float2(0.f, 0.f);
+            }
+        }
+    };
+    const int T = U * NLB;
+    auto weights = [&](int t, W (&w)[OB][2]) {
+#pragma unroll
+        for (int ob = 0; ob < OB; ++ob) {
+            const W* p = w0 + ((size_t)ob * T + t) * 128;
+            w[ob][0] = p[0];
+            w[ob][1] = p[64];
+        }
+    };
+    float2 nx[CB][4];
+    W wn[OB][2];
+    load(0, nx);
+    if constexpr (AHEAD) weights(0, wn);
+    for (int t = 0; t < T; ++t) {
+        float2 f[CB][4];
+        W w[OB][2];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f[cb][k] = nx[cb][k];
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int ob = 0; ob < OB; ++ob) { w[ob][0] = wn[ob][0]; w[ob][1] = wn[ob][1]; }
+        } else {
+            weights(t, w);
+        }
+        if (t + 1 < T) {
+            load(t + 1, nx);
+            if constexpr (AHEAD) weights(t + 1, wn);
+        }
+        if constexpr (PREC == P_FP32) {
+#pragma unroll
+            for (int ob = 0; ob < OB; ++ob) {
+                const float wf[8] = {w[ob][0].x, w[ob][0].y, w[ob][0].z, w[ob][0].w,
+                                     w[ob][1].x, w[ob][1].y, w[ob][1].z, w[ob][1].w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) acc[ob][cb] = mfma32(wf[2 * k], f[cb][k].x, acc[ob][cb]);
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) acc[ob][cb] = mfma32(wf[2 * k + 1], f[cb][k].y, acc[ob][cb]);
+                }
+            }
+        } else {
+            shortx4 pk[CB][2];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    pk[cb][h] = pack4<PREC>(f[cb][2 * h].x, f[cb][2 * h].y, f[cb][2 * h + 1].x, f[cb][2 * h + 1].y);
+#pragma unroll
+            for (int ob = 0; ob < OB; ++ob)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) acc[ob][cb] = mfma16<PREC>(w[ob][h], pk[cb][h], acc[ob][cb]);
+        }
+    }
+}
+
+}  // namespace nif

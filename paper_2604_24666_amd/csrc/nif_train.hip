@@ -25,8 +25,6 @@
 
 namespace nif {
 
-NetParams make_net_params(const nif_model* m, int32_t precision);
-
 enum { TC_NPOS = 0, TC_STEP = 1, TC_GOOD = 2, TC_NONFINITE = 3, TC_SKIP = 4 };
 enum { DA_SUM = 0, DA_SCALE = 5, DA_SCALE_USED = 6, DA_C1 = 7, DA_C2 = 8 };
 constexpr float kDistEps = 1e-4f;
@@ -78,6 +76,8 @@ struct DwArgs {
     int n_cb, ks;                // column tiles of 64, K slices per chunk
     float* part;                 // [slot][M_pad][N] then [slot][M_pad] bias sums
     int64_t n_slots;
+    int32_t panel_C, panel_L;    // h in panels (nif_panels.hpp): combinations and levels, hstride the row length;
+                                 //   column 2g + f of the partials is feature f of panel g = l C + c
 };
 
 constexpr int64_t kDwMinK = 512;
@@ -139,11 +139,14 @@ static int64_t dw_part_floats_max(int M_pad, int N, int cus) {
     return need;
 }
 
+// Encoding of one chunk: rows, or panels whose rows are padded to a multiple of 16 segments.
+static int64_t chunk_enc_floats(const nif_model* m) { return ((m->bwd_chunk + 15) & ~(int64_t)15) * m->E; }
+
 int model_reserve(nif_model* m, int64_t B) {
     if (B <= m->max_batch) return NIF_OK;
     for (float** p : {&m->zbuf, &m->dz, &m->acts, &m->delta, &m->enc, &m->enc_all})
         if (*p) { (void)hipFree(*p); *p = nullptr; }
-    for (void** p : {(void**)&m->bwd_cnt, (void**)&m->bwd_scan, (void**)&m->bwd_val})
+    for (void** p : {(void**)&m->bwd_cnt, (void**)&m->bwd_scan, (void**)&m->bwd_val, (void**)&m->pos})
         if (*p) { (void)hipFree(*p); *p = nullptr; }
     m->max_batch = 0;
     {
@@ -176,7 +179,8 @@ int model_reserve(nif_model* m, int64_t B) {
     const struct { float** p; int64_t n; } a[] = {{&m->zbuf, B * m->H}, {&m->dz, B * 16}, {&m->acts, B * hw * nh},
                                                   {&m->delta, B * hw * nh},
                                                   // two encoding scratches, used by the chunks in turn
-                                                  {&m->enc, (B > m->bwd_chunk ? 2 : 1) * m->bwd_chunk * m->E}};
+                                                  {&m->enc, (B > m->bwd_chunk ? 2 : 1) * chunk_enc_floats(m)},
+                                                  {(float**)&m->pos, uses_panels(m) ? 6 * m->S * ((m->bwd_chunk + 15) & ~15LL) : 1}};
     for (auto& x : a)
         if (hipMalloc((void**)x.p, sizeof(float) * (size_t)std::max<int64_t>(x.n, 1)) != hipSuccess) {
             (void)hipGetLastError();
@@ -215,7 +219,7 @@ int model_reserve(nif_model* m, int64_t B) {
 int model_reserve_encoding(nif_model* m) {
     if (m->max_batch <= 0) return fail(NIF_E_STATE, "nif_model_reserve must come first");
     if (m->enc_all) return NIF_OK;
-    if (hipMalloc((void**)&m->enc_all, sizeof(float) * (size_t)m->max_batch * m->E) != hipSuccess) {
+    if (hipMalloc((void**)&m->enc_all, sizeof(float) * (size_t)(m->max_batch + 16) * m->E) != hipSuccess) {
         (void)hipGetLastError();
         m->enc_all = nullptr;
         return fail(NIF_E_OOM, "stored-encoding allocation failed");
@@ -486,7 +490,7 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(BwdParams bp, const float* __re
 // columns; when the layer has fewer than 4 column tiles, the spare waves take further
 // slices of the chunk.  Partials (and the bias sums of column group 0) go to a scratch slot
 // per (chunk, slice); k_dw_sum adds the slots into the gradient, without atomics.
-template <int MT, int PREC>
+template <int MT, int PREC, bool PANEL>
 __global__ void __launch_bounds__(256) k_dw_part(DwArgs A) {
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
     const int cb = A.ks > 1 ? w % A.n_cb : (int)blockIdx.y * 4 + w;      // column tile
@@ -528,8 +532,16 @@ __global__ void __launch_bounds__(256) k_dw_part(DwArgs A) {
 #pragma unroll
                     for (int t = 0; t < MT; ++t) a[r][t] = dr[t];
                 }
-                const float* hr = A.h + k * A.hstride + n0 + 4 * j;
-                if (ncol_ok) {
+                const float* hr = PANEL ? nullptr : A.h + k * A.hstride + n0 + 4 * j;
+                if constexpr (PANEL) {              // N is a multiple of 8: columns come in whole panels
+                    const int g = (n0 + 4 * j) >> 1;
+                    float2 v0 = make_float2(0.f, 0.f), v1 = v0;
+                    if (ncol_ok) {
+                        v0 = *reinterpret_cast<const float2*>(A.h + ((int64_t)g * A.hstride + k) * 2);
+                        v1 = *reinterpret_cast<const float2*>(A.h + ((int64_t)(g + 1) * A.hstride + k) * 2);
+                    }
+                    b[r][0] = v0.x; b[r][1] = v0.y; b[r][2] = v1.x; b[r][3] = v1.y;
+                } else if (ncol_ok) {
                     const float4 v = *reinterpret_cast<const float4*>(hr);
                     b[r][0] = v.x; b[r][1] = v.y; b[r][2] = v.z; b[r][3] = v.w;
                 } else {
@@ -605,7 +617,8 @@ __global__ void __launch_bounds__(256) k_dw_part(DwArgs A) {
 // row is fetched once per block.  LDS rows are padded by 4 floats, so the column reads of the
 // four lane quarters (4 rows apart) fall in distinct banks.  Partials (and the bias sums, by
 // the waves of column tile 0) go to slot x; k_dw_sum adds the slots.  Needs N % 4 == 0.
-template <int RW, int CT, int PREC>
+// PANEL: h in panels; a float4 holds a panel's features of two neighbouring samples.
+template <int RW, int CT, int PREC, bool PANEL>
 __global__ void __launch_bounds__(64 * RW * CT) __attribute__((amdgpu_waves_per_eu(3))) k_dw_tile(DwArgs A) {
     constexpr int NT = 64 * RW * CT;
     constexpr int M = 64 * RW, LDD = M + 4;
@@ -633,10 +646,20 @@ __global__ void __launch_bounds__(64 * RW * CT) __attribute__((amdgpu_waves_per_
                 const int64_t k = kt + r;
                 if (k < kc1) v = *reinterpret_cast<const float4*>(A.d + k * A.dstride + 4 * c4);
             } else if (idx < F4D + F4H) {
-                const int h = idx - F4D, r = h / (NC / 4), c4 = h % (NC / 4);
-                const int64_t k = kt + r;
-                const int col = col0 + 4 * c4;
-                if (k < kc1 && col < A.N) v = *reinterpret_cast<const float4*>(A.h + k * A.hstride + col);
+                const int h = idx - F4D;
+                if constexpr (PANEL) {
+                    const int gl = h / (kDwKT / 2), r = 2 * (h % (kDwKT / 2));
+                    const int64_t k = kt + r;
+                    if (k < kc1 && col0 + 2 * gl < A.N) {
+                        v = *reinterpret_cast<const float4*>(A.h + ((int64_t)(col0 / 2 + gl) * A.hstride + k) * 2);
+                        if (k + 1 >= kc1) v.z = v.w = 0.f;
+                    }
+                } else {
+                    const int r = h / (NC / 4), c4 = h % (NC / 4);
+                    const int64_t k = kt + r;
+                    const int col = col0 + 4 * c4;
+                    if (k < kc1 && col < A.N) v = *reinterpret_cast<const float4*>(A.h + k * A.hstride + col);
+                }
             }
             reg[i] = v;
         }
@@ -649,8 +672,15 @@ __global__ void __launch_bounds__(64 * RW * CT) __attribute__((amdgpu_waves_per_
                 const int r = idx / (M / 4), c4 = idx % (M / 4);
                 *reinterpret_cast<float4*>(&sD[buf][r * LDD + 4 * c4]) = reg[i];
             } else if (idx < F4D + F4H) {
-                const int h = idx - F4D, r = h / (NC / 4), c4 = h % (NC / 4);
-                *reinterpret_cast<float4*>(&sH[buf][r * LDH + 4 * c4]) = reg[i];
+                const int h = idx - F4D;
+                if constexpr (PANEL) {
+                    const int gl = h / (kDwKT / 2), r = 2 * (h % (kDwKT / 2));
+                    *reinterpret_cast<float2*>(&sH[buf][r * LDH + 2 * gl]) = make_float2(reg[i].x, reg[i].y);
+                    *reinterpret_cast<float2*>(&sH[buf][(r + 1) * LDH + 2 * gl]) = make_float2(reg[i].z, reg[i].w);
+                } else {
+                    const int r = h / (NC / 4), c4 = h % (NC / 4);
+                    *reinterpret_cast<float4*>(&sH[buf][r * LDH + 4 * c4]) = reg[i];
+                }
             }
         }
     };
@@ -776,8 +806,16 @@ __global__ void __launch_bounds__(64 * kDwSumGroups) k_dw_sum(DwArgs A, float* _
         float v = 0.f;
 #pragma unroll
         for (int k = 0; k < G; ++k) v += red[k][o];
-        if (is_w) gW[(i / A.N) * ldw + i % A.N] += v;
-        else gb[i - n_out] += v;
+        if (is_w) {
+            int64_t col = i % A.N;
+            if (A.panel_C > 0) {             // canonical column (c L + l) 2 + f
+                const int g = (int)(col >> 1);
+                col = ((int64_t)(g % A.panel_C) * A.panel_L + g / A.panel_C) * 2 + (col & 1);
+            }
+            gW[(i / A.N) * ldw + col] += v;
+        } else {
+            gb[i - n_out] += v;
+        }
     }
 }
 
@@ -1514,61 +1552,56 @@ static int dispatch_mlp_bwd(int hw, const BwdParams& bp, const float* dz, const 
     return NIF_OK;
 }
 
-// Backward from dz (already in m->dz) to the gradient accumulators; activations in m->acts.
-// One layer's weight gradient over rows [0, B) of d (stride dstride) and h (stride hstride),
-// added to gW / gb: K-sliced MFMA partials, then a sum per output.
-template <int PREC>
+// One layer's weight gradient over rows [0, B) of d (stride dstride) and h, added to gW / gb:
+// K-sliced MFMA partials, then a sum per output.
+template <int PREC, bool PANEL>
 static void launch_dw_part(const DwArgs& A, dim3 grid, hipStream_t st) {
     switch (A.M_pad / 16) {
-        case 1: hipLaunchKernelGGL((k_dw_part<1, PREC>), grid, dim3(256), 0, st, A); break;
-        case 2: hipLaunchKernelGGL((k_dw_part<2, PREC>), grid, dim3(256), 0, st, A); break;
-        case 4: hipLaunchKernelGGL((k_dw_part<4, PREC>), grid, dim3(256), 0, st, A); break;
-        default: hipLaunchKernelGGL((k_dw_part<8, PREC>), grid, dim3(256), 0, st, A); break;
+        case 1: hipLaunchKernelGGL((k_dw_part<1, PREC, PANEL>), grid, dim3(256), 0, st, A); break;
+        case 2: hipLaunchKernelGGL((k_dw_part<2, PREC, PANEL>), grid, dim3(256), 0, st, A); break;
+        case 4: hipLaunchKernelGGL((k_dw_part<4, PREC, PANEL>), grid, dim3(256), 0, st, A); break;
+        default: hipLaunchKernelGGL((k_dw_part<8, PREC, PANEL>), grid, dim3(256), 0, st, A); break;
     }
+}
+
+template <int PREC, bool PANEL>
+static void launch_dw_tile(const DwArgs& A, dim3 grid, hipStream_t st) {
+    if (A.M_pad == 128) hipLaunchKernelGGL((k_dw_tile<2, 2, PREC, PANEL>), grid, dim3(256), 0, st, A);
+    else hipLaunchKernelGGL((k_dw_tile<1, 4, PREC, PANEL>), grid, dim3(256), 0, st, A);
+}
+
+template <int PREC>
+static void launch_dw(bool tiled, const DwArgs& A, dim3 grid, hipStream_t st) {
+    if (tiled) A.panel_C ? launch_dw_tile<PREC, true>(A, grid, st) : launch_dw_tile<PREC, false>(A, grid, st);
+    else A.panel_C ? launch_dw_part<PREC, true>(A, grid, st) : launch_dw_part<PREC, false>(A, grid, st);
 }
 
 // Weight gradient of one layer; with BF16/FP16 MLP arithmetic its operands are rounded to that
-// precision as in the forward and the MLP backward (FP32 accumulation either way).
-template <int PREC>
-static void launch_dw_tile(const DwArgs& A, dim3 grid, hipStream_t st) {
-    if (A.M_pad == 128) hipLaunchKernelGGL((k_dw_tile<2, 2, PREC>), grid, dim3(256), 0, st, A);
-    else hipLaunchKernelGGL((k_dw_tile<1, 4, PREC>), grid, dim3(256), 0, st, A);
-}
-
+// precision as in the forward and the MLP backward (FP32 accumulation either way).  h: rows
+// [B][N], or for the first layer of a model that uses them the panels of the B samples.
 static int weight_grad(nif_model* m, int layer, const float* d, int dstride, int M_pad, const float* h, int64_t B,
                        int cus, int32_t precision, hipStream_t st) {
     const int N = m->dims[layer];
-    if (dw_tiled(M_pad, N) && dstride % 4 == 0) {
-        DwArgs A = dw_tile_shape(M_pad, N, B, cus);
-        A.d = d;
-        A.dstride = dstride;
-        A.M_real = m->dims[layer + 1];
-        A.h = h;
-        A.hstride = N;
-        A.part = m->dw_part;
-        if (dw_part_floats(A) > m->dw_part_n) return fail(NIF_E_STATE, "weight-gradient scratch too small");
-        const int ct = dw_tile_ct(M_pad);
-        const dim3 grid((unsigned)A.n_slots, (unsigned)((A.n_cb + ct - 1) / ct));
-        if (precision == NIF_PREC_BF16) launch_dw_tile<P_BF16>(A, grid, st);
-        else if (precision == NIF_PREC_FP16) launch_dw_tile<P_FP16>(A, grid, st);
-        else launch_dw_tile<P_FP32>(A, grid, st);
-        const int64_t n_out = (int64_t)A.M_real * A.N + A.M_real;
-        hipLaunchKernelGGL(k_dw_sum, dim3((unsigned)((n_out + 63) / 64)), dim3(64 * kDwSumGroups), 0, st, A,
-                           m->g_mlp + m->w_off[layer], A.N, m->g_mlp + m->b_off[layer]);
-        return NIF_OK;
-    }
-    DwArgs A = dw_shape(M_pad, N, B, cus);
+    const bool tiled = dw_tiled(M_pad, N) && dstride % 4 == 0;
+    DwArgs A = tiled ? dw_tile_shape(M_pad, N, B, cus) : dw_shape(M_pad, N, B, cus);
     A.d = d;
     A.dstride = dstride;
     A.M_real = m->dims[layer + 1];
     A.h = h;
-    A.hstride = m->dims[layer];
+    A.hstride = N;
+    if (layer == 0 && uses_panels(m)) {
+        A.hstride = (int)((B + 15) & ~(int64_t)15);
+        A.panel_C = 2 * m->S;
+        A.panel_L = m->desc.levels;
+    }
     A.part = m->dw_part;
     if (dw_part_floats(A) > m->dw_part_n) return fail(NIF_E_STATE, "weight-gradient scratch too small");
-    const dim3 grid((unsigned)((B + A.Kc - 1) / A.Kc), (unsigned)(A.ks > 1 ? 1 : (A.n_cb + 3) / 4));
-    if (precision == NIF_PREC_BF16) launch_dw_part<P_BF16>(A, grid, st);
-    else if (precision == NIF_PREC_FP16) launch_dw_part<P_FP16>(A, grid, st);
-    else launch_dw_part<P_FP32>(A, grid, st);
+    const int ct = dw_tile_ct(M_pad);
+    const dim3 grid = tiled ? dim3((unsigned)A.n_slots, (unsigned)((A.n_cb + ct - 1) / ct))
+                            : dim3((unsigned)((B + A.Kc - 1) / A.Kc), (unsigned)(A.ks > 1 ? 1 : (A.n_cb + 3) / 4));
+    if (precision == NIF_PREC_BF16) launch_dw<P_BF16>(tiled, A, grid, st);
+    else if (precision == NIF_PREC_FP16) launch_dw<P_FP16>(tiled, A, grid, st);
+    else launch_dw<P_FP32>(tiled, A, grid, st);
     const int64_t n_out = (int64_t)A.M_real * A.N + A.M_real;
     hipLaunchKernelGGL(k_dw_sum, dim3((unsigned)((n_out + 63) / 64)), dim3(64 * kDwSumGroups), 0, st, A,
                        m->g_mlp + m->w_off[layer], A.N, m->g_mlp + m->b_off[layer]);
@@ -1729,7 +1762,7 @@ static int gradient_chunks(nif_model* m, const float* x0, const float* x1, int64
     const EncBwdParams ep = table_grad_params(m, x0, x1, B, dx0, dx1);
     hipStream_t sd = m->side;
     auto chunk_enc = [&](int64_t c0) {
-        return enc_all ? enc_all + (size_t)c0 * m->E : m->enc + (size_t)((c0 / m->bwd_chunk) & 1) * m->bwd_chunk * m->E;
+        return enc_all ? enc_all + (size_t)c0 * m->E : m->enc + (size_t)((c0 / m->bwd_chunk) & 1) * chunk_enc_floats(m);
     };
     auto chunk_weight_grads = [&](int64_t c0, int64_t n) {
         const float* acts_c = m->acts + (size_t)c0 * nh * hw;
@@ -1768,7 +1801,7 @@ static int gradient_chunks(nif_model* m, const float* x0, const float* x1, int64
             round_open = true;
             round_end = c0 + rn;
         }
-        if ((rc = forward_rows_launch(m, x0 + c0, x1 + c0, n, B, z_c, prec, acts_c, chunk_enc(c0), st))) break;
+        if ((rc = forward_rows_launch(m, x0 + c0, x1 + c0, n, B, z_c, prec, acts_c, chunk_enc(c0), m->pos, st))) break;
         heads(c0, n, z_c, dz_c);
         if (prec == NIF_PREC_FP32) rc = dispatch_mlp_bwd<P_FP32>(hw, bp, dz_c, acts_c, delta_c, n, st);
         else if (prec == NIF_PREC_BF16) rc = dispatch_mlp_bwd<P_BF16>(hw, bp, dz_c, acts_c, delta_c, n, st);
