@@ -68,6 +68,30 @@ __global__ void __launch_bounds__(256, 2) k_forward(NetParams np, const float* _
     }
 }
 
+// Fixed-point PE samples of n point pairs (SoA, stride ld): pos[c][axis][i].  One thread per
+// (pair, quarter of the combinations), the runs of layer1_levels, so that the double-angle
+// recurrence starts where it does there.
+__global__ void __launch_bounds__(256) k_positions(int F, const float* __restrict__ x0, const float* __restrict__ x1,
+                                                   int64_t n, int64_t ld, uint32_t* __restrict__ pos) {
+    const int S = 1 + 2 * F, C = 2 * S, U = (C + 3) >> 2;
+    const int q = blockIdx.y;
+    const int64_t pn = panel_stride(n);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const float sp[8] = {x0[i], x0[ld + i], x0[2 * ld + i], 0.f, x1[i], x1[ld + i], x1[2 * ld + i], 0.f};
+        PEWalk w;
+        w.p = -1;
+        w.k = -1;
+        for (int u = 0; u < U; ++u) {
+            const int c = q * U + u;
+            if (c >= C) break;
+            double v[3];
+            pe_walk(sp, c, S, w, v);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) pos[((int64_t)c * 3 + a) * pn + i] = to_fix32(v[a]);
+        }
+    }
+}
+
 // Heads of n point pairs from their panels: the first layer reads them as MFMA operands, the
 // rest of the MLP as in the fused kernels.  acts as in k_forward.  A wave takes 16 CB pairs, so
 // its first-layer weights (229 KB at width 64 in FP32, streamed through L1) serve CB columns.
@@ -137,46 +161,14 @@ int encode_launch(const nif_model* m, const float* x, int64_t n, float* out, hip
     return check_hip(hipGetLastError(), "k_encode launch");
 }
 
-// Items of the level-by-level encoding.  Two parts per level, dealt to the XCDs longest first: an
-// XCD then stays on one level for half of its lookups, and the waves of two levels overlap for a
-// small share of the time (2^17 ordered pairs: 0.72 ms; with every level spread over all XCDs,
-// where the levels overlap for a third of the time, 0.86; whole levels, unbalanced, 0.84).  A
-// hashed level counts twice a dense one (6 against 4 loads, fewer of them in L1).  Tables that
-// fit an L2 together need no such care: every level is spread evenly.
-static EncPlan encode_plan(const EncParams& ep, int64_t n) {
-    EncPlan P;
-    memset(&P, 0, sizeof(P));
-    const int C = 2 * (1 + 2 * ep.F);
-    P.tiles = (int32_t)((n + 255) / 256);
-    P.groups = (C + kEncKC - 1) / kEncKC;
-    const int64_t table_bytes = ((int64_t)ep.L << ep.log2T) * (ep.f16 ? 4 : 8);
-    P.parts = table_bytes <= (4 << 20) ? kEncXcds : 2;
-    P.per_item = (int32_t)(((int64_t)P.tiles * P.groups + P.parts - 1) / P.parts);
-    int load[kEncXcds] = {};
-    for (int pass = 0; pass < 2; ++pass)                // hashed levels first
-        for (int l = 0; l < ep.L; ++l) {
-            const bool dense = (ep.dense_mask >> l) & 1u;
-            if (dense != (pass == 1)) continue;
-            for (int k = 0; k < P.parts; ++k) {
-                int x = 0;
-                for (int y = 1; y < kEncXcds; ++y)
-                    if (load[y] < load[x]) x = y;
-                P.item[x][P.n_items[x]++] = (uint8_t)(l * P.parts + k);
-                load[x] += dense ? 1 : 2;
-            }
-        }
-    return P;
-}
-
 // Positions and panels of n pairs (SoA with stride ld).
 static void launch_panels(const NetParams& np, const float* x0, const float* x1, int64_t n, int64_t ld, uint32_t* pos,
                           float* enc, hipStream_t st) {
     const unsigned pb = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
     hipLaunchKernelGGL(k_positions, dim3(pb, 4), dim3(256), 0, st, np.enc.F, x0, x1, n, ld, pos);
-    const EncPlan P = encode_plan(np.enc, n);
-    int most = 0;
-    for (int x = 0; x < kEncXcds; ++x) most = std::max(most, (int)P.n_items[x]);
-    const dim3 g((unsigned)(kEncXcds * most * (int64_t)P.per_item));
+    const int C = 2 * (1 + 2 * np.enc.F);
+    const EncPlan P = level_plan(np.enc, (n + 255) / 256, (C + kEncKC - 1) / kEncKC);
+    const dim3 g(plan_blocks(P));
     if (np.enc.f16) hipLaunchKernelGGL((k_encode_levels<kEncKC, true>), g, dim3(256), 0, st, np.enc, P, pos, n, (float2*)enc);
     else hipLaunchKernelGGL((k_encode_levels<kEncKC, false>), g, dim3(256), 0, st, np.enc, P, pos, n, (float2*)enc);
 }

@@ -66,6 +66,9 @@ struct nif_model {
     float* delta = nullptr;             // [hidden_layers][max_batch][hidden_width] d loss / d pre-activation
     float* enc = nullptr;               // [1 or 2][bwd_chunk][E] a chunk's encoding, from its forward to its
                                         //   first-layer dW (two scratches in turn with several chunks)
+    float* denc = nullptr;              // d enc panels of one training chunk (two features)
+    unsigned long long* dir_acc = nullptr;  // 64-bit sums of the levels summed without records
+    float* dx_part = nullptr;           // [L][6][bwd_chunk] point gradients per level (two features)
     uint32_t* pos = nullptr;            // [6 S][bwd_chunk] a training chunk's positions (panels only)
     float* enc_all = nullptr;           // [max_batch][E] stored encoding (store_encoding steps only;
                                         //   allocated by nif_model_reserve_encoding)

@@ -12,6 +12,8 @@
 // 16-byte aligned.  Positions: pos[c][axis][i], 32-bit fixed point, the same row length.
 // Both hold exactly the values the fused kernels form in registers.
 #pragma once
+#include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 #include "nif_net.hpp"
@@ -93,43 +95,66 @@ __device__ __forceinline__ void lookup_points(const EncParams& ep, int l, const 
     }
 }
 
-// Fixed-point PE samples of n point pairs (SoA, stride ld): pos[c][axis][i].  One thread per
-// (pair, quarter of the combinations), the runs of layer1_levels, so that the double-angle
-// recurrence starts where it does there.
-__global__ void __launch_bounds__(256) k_positions(int F, const float* __restrict__ x0, const float* __restrict__ x1,
-                                                   int64_t n, int64_t ld, uint32_t* __restrict__ pos) {
-    const int S = 1 + 2 * F, C = 2 * S, U = (C + 3) >> 2;
-    const int q = blockIdx.y;
-    const int64_t pn = panel_stride(n);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float sp[8] = {x0[i], x0[ld + i], x0[2 * ld + i], 0.f, x1[i], x1[ld + i], x1[2 * ld + i], 0.f};
-        PEWalk w;
-        w.p = -1;
-        w.k = -1;
-        for (int u = 0; u < U; ++u) {
-            const int c = q * U + u;
-            if (c >= C) break;
-            double v[3];
-            pe_walk(sp, c, S, w, v);
-#pragma unroll
-            for (int a = 0; a < 3; ++a) pos[((int64_t)c * 3 + a) * pn + i] = to_fix32(v[a]);
-        }
-    }
-}
-
-// Work of k_encode_levels: which (level, part) items each XCD goes through, in order.  A part is
+// Work of a level-by-level pass: which (level, part) items each XCD goes through, in order.  A part is
 // a share of the level's (combination group, segment tile) workgroups.  Workgroup b runs on XCD
 // b mod 8 (round-robin dispatch; only the speed depends on it).
 constexpr int kEncXcds = 8, kEncMaxItems = 16;
 constexpr int kEncKC = 2;           // combinations per thread
 struct EncPlan {
-    int32_t tiles;                  // 256-segment tiles
-    int32_t groups;                 // groups of kEncKC combinations
+    int32_t tiles;                  // segment tiles
+    int32_t groups;                 // groups of combinations
     int32_t parts;                  // parts per level
     int32_t per_item;               // workgroups of one part
+    int32_t most;                   // items of the fullest XCD
     uint8_t n_items[kEncXcds];
     uint8_t item[kEncXcds][kEncMaxItems];   // level * parts + part
 };
+
+// Items of a level-by-level pass.  Two parts per level, dealt to the XCDs longest first: an
+// XCD then stays on one level for half of its lookups, and the waves of two levels overlap for a
+// small share of the time (2^17 ordered pairs: 0.72 ms; with every level spread over all XCDs,
+// where the levels overlap for a third of the time, 0.86; whole levels, unbalanced, 0.84).  A
+// hashed level counts twice a dense one (6 against 4 loads, fewer of them in L1).  Tables that
+// fit an L2 together need no such care: every level is spread evenly.
+inline EncPlan level_plan(const EncParams& ep, int64_t tiles, int groups) {
+    EncPlan P;
+    memset(&P, 0, sizeof(P));
+    P.tiles = (int32_t)tiles;
+    P.groups = groups;
+    const int64_t table_bytes = ((int64_t)ep.L << ep.log2T) * (ep.f16 ? 4 : 8);
+    P.parts = table_bytes <= (4 << 20) ? kEncXcds : 2;
+    P.per_item = (int32_t)(((int64_t)P.tiles * P.groups + P.parts - 1) / P.parts);
+    int load[kEncXcds] = {};
+    for (int pass = 0; pass < 2; ++pass)                // hashed levels first
+        for (int l = 0; l < ep.L; ++l) {
+            const bool dense = (ep.dense_mask >> l) & 1u;
+            if (dense != (pass == 1)) continue;
+            for (int k = 0; k < P.parts; ++k) {
+                int x = 0;
+                for (int y = 1; y < kEncXcds; ++y)
+                    if (load[y] < load[x]) x = y;
+                P.item[x][P.n_items[x]++] = (uint8_t)(l * P.parts + k);
+                load[x] += dense ? 1 : 2;
+            }
+        }
+    P.most = 0;
+    for (int x = 0; x < kEncXcds; ++x) P.most = std::max<int32_t>(P.most, P.n_items[x]);
+    return P;
+}
+inline unsigned plan_blocks(const EncPlan& P) { return (unsigned)(kEncXcds * P.most * (int64_t)P.per_item); }
+
+// The (level, combination group, tile) of this workgroup; false if it has none.
+__device__ __forceinline__ bool plan_item(const EncPlan& P, int& l, int& grp, int& tile) {
+    const int x = (int)(blockIdx.x % kEncXcds), v = (int)(blockIdx.x / kEncXcds);
+    const int it = v / P.per_item;
+    if (it >= P.n_items[x]) return false;
+    const int item = P.item[x][it];
+    l = item / P.parts;
+    const int b = (item % P.parts) * P.per_item + v % P.per_item;       // workgroup within the level
+    grp = b / P.tiles;
+    tile = b % P.tiles;
+    return grp < P.groups;
+}
 
 // Bound: the rate at which L1 and L2 take the lanes' corner requests (about 5 distinct lines per
 // lookup on hashed levels).  2^17 spatially ordered pairs at 16 levels of 2^19 FP16 entries:
@@ -140,15 +165,9 @@ template <int KC, bool F16>
 __global__ void __launch_bounds__(256) k_encode_levels(EncParams ep, EncPlan plan, const uint32_t* __restrict__ pos,
                                                        int64_t n, float2* __restrict__ enc) {
     const int S = 1 + 2 * ep.F, C = 2 * S;
-    const int x = (int)(blockIdx.x % kEncXcds), v = (int)(blockIdx.x / kEncXcds);
-    const int it = v / plan.per_item;
-    if (it >= plan.n_items[x]) return;
-    const int item = plan.item[x][it];
-    const int l = item / plan.parts;
-    const int b = (item % plan.parts) * plan.per_item + v % plan.per_item;    // workgroup within the level
-    const int grp = b / plan.tiles;
-    if (grp >= plan.groups) return;
-    const int64_t i = (int64_t)(b % plan.tiles) * 256 + threadIdx.x;
+    int l, grp, tile;
+    if (!plan_item(plan, l, grp, tile)) return;
+    const int64_t i = (int64_t)tile * 256 + threadIdx.x;
     if (i >= n) return;
     const int64_t pn = panel_stride(n);
     uint32_t f[KC][3], so[KC];

@@ -21,7 +21,7 @@
 #include <cstring>
 
 #include "nif_internal.hpp"
-#include "nif_net.hpp"
+#include "nif_panels.hpp"
 
 namespace nif {
 
@@ -140,11 +140,14 @@ static int64_t dw_part_floats_max(int M_pad, int N, int cus) {
 }
 
 // Encoding of one chunk: rows, or panels whose rows are padded to a multiple of 16 segments.
-static int64_t chunk_enc_floats(const nif_model* m) { return ((m->bwd_chunk + 15) & ~(int64_t)15) * m->E; }
+static int64_t chunk_enc_floats(const nif_model* m) { return panel_stride(m->bwd_chunk) * m->E; }
+
+static int64_t tg_block_samples(int feat_dim);
+static int reserve_direct(nif_model* m);
 
 int model_reserve(nif_model* m, int64_t B) {
     if (B <= m->max_batch) return NIF_OK;
-    for (float** p : {&m->zbuf, &m->dz, &m->acts, &m->delta, &m->enc, &m->enc_all})
+    for (float** p : {&m->zbuf, &m->dz, &m->acts, &m->delta, &m->enc, &m->denc, &m->dx_part, &m->enc_all})
         if (*p) { (void)hipFree(*p); *p = nullptr; }
     for (void** p : {(void**)&m->bwd_cnt, (void**)&m->bwd_scan, (void**)&m->bwd_val, (void**)&m->pos})
         if (*p) { (void)hipFree(*p); *p = nullptr; }
@@ -159,7 +162,7 @@ int model_reserve(nif_model* m, int64_t B) {
         const int64_t per = 2 * (int64_t)m->S * L * 8;
         int64_t round = std::min<int64_t>(std::max<int64_t>(B, 1), chunk * kEncBwdRoundChunks);
         while (round > chunk && round * per > INT32_MAX) round -= chunk;
-        const int64_t n_blk = ((round + 15) / 16 + kBwdTilesPerBlock - 1) / kBwdTilesPerBlock;
+        const int64_t per_blk = tg_block_samples(m->desc.feat_dim), n_blk = (round + per_blk - 1) / per_blk;
         const int64_t n_add = round * per;
         const int64_t n_cnt = n_buckets * n_blk;
         const size_t sz[3] = {sizeof(int32_t) * (size_t)n_cnt,
@@ -175,12 +178,16 @@ int model_reserve(nif_model* m, int64_t B) {
         m->bwd_chunk = chunk;
         m->bwd_round = round;
     }
-    const int64_t hw = m->desc.hidden_width, nh = m->desc.hidden_layers;
+    const int64_t hw = m->desc.hidden_width, nh = m->desc.hidden_layers, pn = panel_stride(m->bwd_chunk);
+    const bool fd2 = m->desc.feat_dim == 2;
     const struct { float** p; int64_t n; } a[] = {{&m->zbuf, B * m->H}, {&m->dz, B * 16}, {&m->acts, B * hw * nh},
                                                   {&m->delta, B * hw * nh},
                                                   // two encoding scratches, used by the chunks in turn
                                                   {&m->enc, (B > m->bwd_chunk ? 2 : 1) * chunk_enc_floats(m)},
-                                                  {(float**)&m->pos, uses_panels(m) ? 6 * m->S * ((m->bwd_chunk + 15) & ~15LL) : 1}};
+                                                  // d enc panels of one chunk and the levels' point gradients
+                                                  {&m->denc, fd2 ? 4 * m->S * m->desc.levels * pn : 1},
+                                                  {&m->dx_part, fd2 ? 6 * m->desc.levels * pn : 1},
+                                                  {(float**)&m->pos, uses_panels(m) ? 6 * m->S * pn : 1}};
     for (auto& x : a)
         if (hipMalloc((void**)x.p, sizeof(float) * (size_t)std::max<int64_t>(x.n, 1)) != hipSuccess) {
             (void)hipGetLastError();
@@ -212,6 +219,7 @@ int model_reserve(nif_model* m, int64_t B) {
         }
         m->dw_part_n = need;
     }
+    if (const int rc = reserve_direct(m)) return rc;
     m->max_batch = B;
     return NIF_OK;
 }
@@ -833,13 +841,13 @@ __global__ void __launch_bounds__(64 * kDwSumGroups) k_dw_sum(DwArgs A, float* _
 //            the slice, value pair) into its ranges (LDS cursors, no global atomics);
 //   reduce - one block per part of a slice sums its additions in LDS and adds them to the
 //            FP32 table gradient.
-// Lanes are assigned as in the forward's first layer: lane (q, j) takes sample j of a
-// 16-sample tile and PE combination c = 4u + q; the wave walks the levels in pairs, all
-// lanes on the same level.  d enc = W0^T delta_0 is formed on MFMA in the same layout: the
-// 16 output rows of one step are (combination 4u + r/4, features of the level pair), so
-// lane (q, j) receives exactly the four d enc values of its own combination and sample.
 // dW0 comes from the forward's encoding (weight_grad).  Samples are processed in chunks so the
 // addition buffer stays bounded.
+//
+// Three features: lanes as in the fused first layer, lane (q, j) takes sample j of a 16-sample
+// tile and PE combination c = 4u + q.  d enc = W0^T delta_0 is formed on MFMA in the same layout:
+// the 16 output rows of one step are (combination 4u + r/4, features of the level), so lane
+// (q, j) receives exactly the d enc values of its own combination and sample.
 
 struct EncBwdParams {
     EncParams enc;
@@ -857,14 +865,16 @@ struct EncBwdParams {
     int64_t n;           // samples in this round
     int32_t SB;          // log2 entries per bucket
     int32_t NBL;         // buckets per level
-    int32_t n_buckets;   // L * NBL
+    int32_t n_lev;       // levels whose additions go through records (all but the direct ones)
+    uint8_t lev[16];     //   which, ascending
+    int32_t n_buckets;   // sets * n_lev * NBL
     int32_t n_blk;       // blocks of the round's grid
     int32_t blk0;        // fill: the launch's first block within the round
     int32_t* cnt;        // [n_buckets][n_blk] counts, then exclusive offsets
     float* val;          // table-gradient records, kRecFloats floats each (see below)
     int32_t w_lds;       // fill: the block's first-layer weight rows staged in LDS
     int64_t cap;         // capacity of val, in records
-    uint32_t* vmax;      // bits of a bound on the round's |additions| (+inf if one is not finite)
+    uint32_t* vmax;      // bits of a bound on the round's |additions| so far (+inf if one is not finite)
 };
 
 
@@ -932,16 +942,10 @@ __device__ __forceinline__ bool tile_sample(const EncBwdParams& P, int64_t tile,
 // memory for every tile).
 constexpr size_t kFillLdsMax = 60 * 1024;
 
-// Levels per block row of the count and fill passes: two with two features per entry (the
-// four (level, feature) rows of a PE combination), one with three.
-template <int FD> constexpr int kLevelGroup = FD == 2 ? 2 : 1;
-
-// Buckets of one level group: table set s (one per PE sample with per-sample tables, else one),
-// level lp + k, slice: local index (s LG + k) NBL + slice, global ((s L + lp + k) NBL + slice).
-template <int LG>
-__device__ __forceinline__ int64_t group_bucket_global(const EncBwdParams& P, int lp, int i) {
-    const int s = i / (LG * P.NBL), r = i % (LG * P.NBL);
-    return ((int64_t)s * P.enc.L + lp + r / P.NBL) * P.NBL + r % P.NBL;
+// Buckets of record level y: table set s (one per PE sample with per-sample tables, else one),
+// slice: local index s NBL + slice, global ((s n_lev + y) NBL + slice).
+__device__ __forceinline__ int64_t level_bucket_global(const EncBwdParams& P, int y, int i) {
+    return ((int64_t)(i / P.NBL) * P.n_lev + y) * P.NBL + i % P.NBL;
 }
 __device__ __forceinline__ int n_table_sets(const EncBwdParams& P) { return P.enc.set_stride ? P.S : 1; }
 // Table set of PE combination c (point-major).
@@ -949,15 +953,13 @@ __device__ __forceinline__ int combo_set(const EncBwdParams& P, int c) {
     return P.enc.set_stride ? (c >= P.S ? c - P.S : c) : 0;
 }
 
-// Block (x, y): the samples of tile group x, the levels of level group y (as the fill below).
-template <int FD>
-__global__ void __launch_bounds__(256) k_enc_bwd_count(EncBwdParams P) {
-    constexpr int LG = kLevelGroup<FD>;
-    extern __shared__ int32_t s_h[];    // [sets][LG][NBL]
+// Three features.  Block (x, y): the samples of tile group x, level y (as the fill below).
+__global__ void __launch_bounds__(256) k_enc_bwd_count3(EncBwdParams P) {
+    extern __shared__ int32_t s_h[];    // [sets][NBL]
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, q = lane >> 4, j = lane & 15;
     const int n_comb = 2 * P.S;
-    const int lp = (int)blockIdx.y * LG;
-    const int nloc = LG * P.NBL * n_table_sets(P);
+    const int l = (int)blockIdx.y;
+    const int nloc = P.NBL * n_table_sets(P);
     for (int i = tid; i < nloc; i += 256) s_h[i] = 0;
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *P.vmax = 0u;
     __syncthreads();
@@ -973,46 +975,34 @@ __global__ void __launch_bounds__(256) k_enc_bwd_count(EncBwdParams P) {
             double smp[3];
             float dsdx[3], inside[3];
             pe_combo_grad(xs, live ? c : 0, P.S, smp, dsdx, inside);
-            const int sb = combo_set(P, live ? c : 0) * LG;
-            for (int k = 0; k < LG; ++k) {
-                uint32_t idx[8];
-                float wt[3];
-                level_corners(P.enc, lp + k, smp, idx, wt);
-                if (!live) continue;
-                int32_t* h = s_h + (sb + k) * P.NBL;
-                if constexpr (FD == 2) {
+            uint32_t idx[8];
+            float wt[3];
+            level_corners(P.enc, l, smp, idx, wt);
+            if (!live) continue;
+            int32_t* h = s_h + combo_set(P, c) * P.NBL;
 #pragma unroll
-                    for (int pr = 0; pr < 4; ++pr) {
-                        const int b0 = (int)(idx[2 * pr] >> P.SB), b1 = (int)(idx[2 * pr + 1] >> P.SB);
-                        atomicAdd(&h[b0], 1);
-                        if (b1 != b0) atomicAdd(&h[b1], 1);
-                    }
-                } else {
-#pragma unroll
-                    for (int cc = 0; cc < 8; ++cc) atomicAdd(&h[(int)(idx[cc] >> P.SB)], 1);
-                }
-            }
+            for (int cc = 0; cc < 8; ++cc) atomicAdd(&h[(int)(idx[cc] >> P.SB)], 1);
         }
     }
     __syncthreads();
-    for (int i = tid; i < nloc; i += 256) P.cnt[group_bucket_global<LG>(P, lp, i) * P.n_blk + blockIdx.x] = s_h[i];
+    for (int i = tid; i < nloc; i += 256) P.cnt[level_bucket_global(P, l, i) * P.n_blk + blockIdx.x] = s_h[i];
 }
 
-// Block (x, y): the samples of tile group x, the LG levels of level group y only, so that a
-// block writes into the LG NBL buckets of those levels: the lines it leaves partly written at
-// any time stay few enough to complete in L2 before eviction.
-template <int HW, int FD>
-__global__ void __launch_bounds__(256) k_enc_bwd_fill(EncBwdParams P) {
+// Three features.  Block (x, y): the samples of tile group x, level y only, so that a block writes
+// into the NBL buckets of that level: the lines it leaves partly written at any time stay few
+// enough to complete in L2 before eviction.
+template <int HW>
+__global__ void __launch_bounds__(256) k_enc_bwd_fill3(EncBwdParams P) {
+    constexpr int FD = 3, LG = 1;
     constexpr int KQ = HW / 4;                 // MFMA k-steps: lane quarter q covers [q KQ, (q+1) KQ)
-    constexpr int LG = kLevelGroup<FD>;
-    extern __shared__ int32_t s_cur[];         // [sets][LG][NBL]: this block's next output slot per bucket
+    extern __shared__ int32_t s_cur[];         // [sets][NBL]: this block's next output slot per bucket
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, q = lane >> 4, j = lane & 15;
     const int L = P.enc.L, n_comb = 2 * P.S;
-    const int lp = (int)blockIdx.y * LG;       // first level of this block's group
+    const int lp = (int)blockIdx.y;            // this block's level
     const uint32_t kmask = (1u << P.SB) - 1u;
-    const int nloc = LG * P.NBL * n_table_sets(P);
+    const int nloc = P.NBL * n_table_sets(P);
     const int bx = (int)blockIdx.x + P.blk0;   // block within the round
-    for (int i = tid; i < nloc; i += 256) s_cur[i] = P.cnt[group_bucket_global<LG>(P, lp, i) * P.n_blk + bx];
+    for (int i = tid; i < nloc; i += 256) s_cur[i] = P.cnt[level_bucket_global(P, lp, i) * P.n_blk + bx];
     // The W0 rows this block multiplies (combination c, (level, feature) r of its group: row
     // 4c + r, zero where r >= LG FD), staged once in LDS with rows padded by 4 floats, so the
     // MFMA's A operand is read from LDS rather than fetched again for every tile.
@@ -1081,51 +1071,23 @@ __global__ void __launch_bounds__(256) k_enc_bwd_fill(EncBwdParams P) {
 #pragma unroll
                     for (int f = 0; f < FD; ++f) gf[f] = acc[FD * k + f];
                     float dl[3] = {0.f, 0.f, 0.f};
-                    int32_t* cur = s_cur + (combo_set(P, c) * LG + l - lp) * P.NBL;
+                    int32_t* cur = s_cur + combo_set(P, c) * P.NBL;
                     float amax = 0.f;
                     bool fin = true;
-                    if constexpr (FD == 2) {
 #pragma unroll
-                        for (int pr = 0; pr < 4; ++pr) {
-                            const int cl = 2 * pr;                 // lower-x corner; cl + 1 the upper
-                            const float A = (((cl >> 1) & 1) ? wt[1] : 1.f - wt[1]) * (((cl >> 2) & 1) ? wt[2] : 1.f - wt[2]);
-                            const float a0 = A * gf[0], a1 = A * gf[1];
-                            const uint32_t k0 = idx[cl] & kmask, k1 = idx[cl + 1] & kmask;
-                            const int b0 = (int)(idx[cl] >> P.SB), b1 = (int)(idx[cl + 1] >> P.SB);
-                            fin = fin && isfinite(a0) && isfinite(a1);
-                            amax = fmaxf(amax, fmaxf(fabsf(a0), fabsf(a1)));
-                            if (b0 == b1) {
-                                const int32_t slot = atomicAdd(&cur[b0], 1);
-                                if (slot < P.cap)      // always true: the count pass saw the same records
-                                    *reinterpret_cast<float4*>(P.val + (size_t)slot * kRecFloats) =
-                                        make_float4(a0, a1, wt[0], __uint_as_float(pair_key(k0, k1)));
-                            } else {
-                                const float w0 = 1.f - wt[0];
-                                const int32_t s0 = atomicAdd(&cur[b0], 1), s1 = atomicAdd(&cur[b1], 1);
-                                if (s0 < P.cap)
-                                    *reinterpret_cast<float4*>(P.val + (size_t)s0 * kRecFloats) =
-                                        make_float4(w0 * a0, w0 * a1, 0.f, __uint_as_float(pair_key(k0, k0)));
-                                if (s1 < P.cap)
-                                    *reinterpret_cast<float4*>(P.val + (size_t)s1 * kRecFloats) =
-                                        make_float4(wt[0] * a0, wt[0] * a1, 0.f, __uint_as_float(pair_key(k1, k1)));
-                            }
+                    for (int cc = 0; cc < 8; ++cc) {
+                        const float cw = corner_weight(wt, cc);
+                        const int32_t slot = atomicAdd(&cur[(int)(idx[cc] >> P.SB)], 1);
+                        float v[FD];
+#pragma unroll
+                        for (int f = 0; f < FD; ++f) {
+                            v[f] = cw * gf[f];
+                            fin = fin && isfinite(v[f]);
+                            amax = fmaxf(amax, fabsf(v[f]));
                         }
-                    } else {
-#pragma unroll
-                        for (int cc = 0; cc < 8; ++cc) {
-                            const float cw = corner_weight(wt, cc);
-                            const int32_t slot = atomicAdd(&cur[(int)(idx[cc] >> P.SB)], 1);
-                            float v[FD];
-#pragma unroll
-                            for (int f = 0; f < FD; ++f) {
-                                v[f] = cw * gf[f];
-                                fin = fin && isfinite(v[f]);
-                                amax = fmaxf(amax, fabsf(v[f]));
-                            }
-                            if (slot < P.cap)
-                                *reinterpret_cast<float4*>(P.val + (size_t)slot * kRecFloats) =
-                                    make_float4(v[0], v[1], v[2], __uint_as_float(idx[cc] & kmask));
-                        }
+                        if (slot < P.cap)
+                            *reinterpret_cast<float4*>(P.val + (size_t)slot * kRecFloats) =
+                                make_float4(v[0], v[1], v[2], __uint_as_float(idx[cc] & kmask));
                     }
                     vmx = fin ? fmaxf(vmx, amax) : INFINITY;
                     if (P.dx0) {
@@ -1169,6 +1131,524 @@ __global__ void __launch_bounds__(256) k_enc_bwd_fill(EncBwdParams P) {
             }
         for (int off = 32; off > 0; off >>= 1) vmx = fmaxf(vmx, __shfl_xor(vmx, off));
         if (lane == 0 && vmx > 0.f) atomicMax(P.vmax, __float_as_uint(vmx));   // non-negative: bits order as values
+    }
+}
+
+// ------------------------------------------------------------------ two features
+// The same count / fill / reduce with lane = sample and the samples' PE combinations walked in
+// order (one FP64 sincos per point and the double-angle recurrence), each block on one level.
+// d enc comes in panels (nif_panels.hpp), formed beforehand for the whole chunk by a plain MFMA
+// pass, so the fill keeps few registers and its scattered stores have many waves behind them.
+constexpr int kTgBlock = 512;              // samples per block
+
+// Barrier that orders LDS accesses only: global loads and stores in flight stay so (a plain
+// __syncthreads waits for them, and the sorted stores of a batch would drain before the next).
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+constexpr int kTgBatch = 2;                // combinations per sorted batch
+
+// d enc = W0^T delta_0 of n samples (delta0 [n][HW]) in panels, FP32 MFMA.  A wave holds the
+// deltas of 16 CB samples and multiplies tiles of 16 (panel, feature) rows of W0^T; y splits the
+// tiles where there are few samples.  Bound: the FP32 MFMA rate (27.9 GFLOP per 2^17 samples at
+// E = 832, width 128: 0.2 ms).
+template <int HW, int CB>
+__global__ void __launch_bounds__(256, 2) k_denc_panels(const float* __restrict__ W0t, int L, int C, const float* __restrict__ delta0,
+                                                        int64_t n, float2* __restrict__ dE, uint32_t* __restrict__ vmax) {
+    constexpr int KQ = HW / 4;
+    const int lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
+    const int64_t pn = panel_stride(n);
+    const int64_t i0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16 * CB;
+    if (i0 >= n) return;
+    float bd[CB][KQ];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int64_t i = i0 + cb * 16 + j;
+#pragma unroll
+        for (int t = 0; t < KQ; t += 4) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (i < n) v = *reinterpret_cast<const float4*>(delta0 + i * HW + q * KQ + t);
+            bd[cb][t] = v.x; bd[cb][t + 1] = v.y; bd[cb][t + 2] = v.z; bd[cb][t + 3] = v.w;
+        }
+    }
+    const int NT = L * C / 8;                                  // 8 panels (16 rows) per tile
+    const int per = (NT + (int)gridDim.y - 1) / (int)gridDim.y;
+    const int t0 = (int)blockIdx.y * per, t1 = min(NT, t0 + per);
+    float vmx = 0.f;                                           // bound on |d enc| (inf if one is not finite)
+    for (int ft = t0; ft < t1; ++ft) {
+        const int g = ft * 8 + (j >> 1), l = g / C, c = g - l * C;
+        const float* wr = W0t + (size_t)((c * L + l) * 2 + (j & 1)) * HW + q * KQ;
+        float4 av[KQ / 4];
+#pragma unroll
+        for (int t = 0; t < KQ / 4; ++t) av[t] = *reinterpret_cast<const float4*>(wr + 4 * t);
+        floatx4 acc[CB];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < KQ / 4; ++t) {
+            const float a4[4] = {av[t].x, av[t].y, av[t].z, av[t].w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[cb] = mfma32(a4[r], bd[cb][4 * t + r], acc[cb]);
+        }
+        // lane (q, j): rows 4q .. 4q + 3 = panels 2q, 2q + 1 of the tile, sample j
+        float2* o = dE + (int64_t)(ft * 8 + 2 * q) * pn;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            const int64_t i = i0 + cb * 16 + j;
+            if (i < n) {
+                o[i] = make_float2(acc[cb][0], acc[cb][1]);
+                o[pn + i] = make_float2(acc[cb][2], acc[cb][3]);
+                const float m = fmaxf(fmaxf(fabsf(acc[cb][0]), fabsf(acc[cb][1])), fmaxf(fabsf(acc[cb][2]), fabsf(acc[cb][3])));
+                const float z = (acc[cb][0] - acc[cb][0]) + (acc[cb][1] - acc[cb][1]) + (acc[cb][2] - acc[cb][2]) +
+                                (acc[cb][3] - acc[cb][3]);     // NaN unless all four are finite
+                vmx = z == 0.f ? fmaxf(vmx, m) : INFINITY;
+            }
+        }
+    }
+    if (!vmax) return;
+    for (int off = 32; off > 0; off >>= 1) vmx = fmaxf(vmx, __shfl_xor(vmx, off));
+    if (lane == 0 && vmx > 0.f) atomicMax(vmax, __float_as_uint(vmx));   // non-negative: bits order as values
+}
+
+// The four x-neighbour corner pairs of one level at smp: the entry e of each pair's lower corner
+// (y neighbour pr & 1, z neighbour pr >> 1) within the level; the upper corner's is e ^ flip in a
+// hashed level (flip = x ^ (x + 1)), e + 1 in a dense one (flip = 0).  The values of level_corners
+// with two multiplications in place of sixteen.
+struct Pairs {
+    uint32_t e[4], flip;
+    __device__ __forceinline__ uint32_t upper(int pr, uint32_t mask) const { return flip ? (e[pr] ^ flip) & mask : e[pr] + 1u; }
+    // whether the corners fall into different buckets of kmask + 1 entries
+    __device__ __forceinline__ bool straddles(int pr, uint32_t kmask) const { return flip ? flip > kmask : (e[pr] & kmask) == kmask; }
+};
+__device__ __forceinline__ void level_pairs(const EncParams& ep, int l, const double smp[3], Pairs& o, float wt[3]) {
+    const int N = ep.res[l];
+    uint32_t ix, iy, iz;
+    grid_axis(smp[0], N, ix, wt[0]);
+    grid_axis(smp[1], N, iy, wt[1]);
+    grid_axis(smp[2], N, iz, wt[2]);
+    if ((ep.dense_mask >> l) & 1u) {
+        const uint32_t n1 = (uint32_t)N + 1u;
+        o.flip = 0u;
+        o.e[0] = ix + n1 * (iy + n1 * iz);
+        o.e[1] = o.e[0] + n1;
+        o.e[2] = o.e[0] + n1 * n1;
+        o.e[3] = o.e[2] + n1;
+    } else {
+        const uint32_t mask = (1u << ep.log2T) - 1u;
+        const uint32_t y0 = iy * 2654435761u, z0 = iz * 805459861u, y1 = y0 + 2654435761u, z1 = z0 + 805459861u;
+        o.flip = ix ^ (ix + 1u);
+        o.e[0] = (ix ^ y0 ^ z0) & mask;
+        o.e[1] = (ix ^ y1 ^ z0) & mask;
+        o.e[2] = (ix ^ y0 ^ z1) & mask;
+        o.e[3] = (ix ^ y1 ^ z1) & mask;
+    }
+}
+
+// Whether a level's entries fall into few buckets, so that the lanes of a wave mostly share one
+// and one LDS atomic per distinct bucket is cheaper than one per lane (which the same address
+// serialises): true up to 4 buckets.
+__device__ __forceinline__ bool few_buckets(const EncBwdParams& P, int l) {
+    const uint32_t n1 = (uint32_t)P.enc.res[l] + 1u;
+    return P.NBL <= 4 || (((P.enc.dense_mask >> l) & 1u) && (n1 * n1 * n1 - 1u) >> P.SB < 4u);
+}
+
+// Next slot of bucket b for every active lane (all lanes of the wave call it); lanes of one bucket
+// get consecutive slots in lane order when `few`.
+__device__ __forceinline__ int32_t take_slot(int32_t* cur, int b, bool active, bool few) {
+    if (!few) return active ? atomicAdd(&cur[b], 1) : 0;
+    int32_t slot = 0;
+    uint64_t todo = ballot(active);
+    while (todo) {
+        const int leader = __ffsll((unsigned long long)todo) - 1;
+        const int bl = __shfl(b, leader);
+        const bool mine = active && b == bl;
+        const uint64_t m = ballot(mine);
+        int32_t base = 0;
+        if (lane_id() == leader) base = atomicAdd(&cur[bl], popc64(m));
+        base = __shfl(base, leader);
+        if (mine) slot = base + rank_below(m);
+        todo &= ~m;
+    }
+    return slot;
+}
+
+// Block (x, y): samples [kTgBlock x, + kTgBlock) of the round, record level y.
+__global__ void __launch_bounds__(kTgBlock) k_tg_count(EncBwdParams P) {
+    extern __shared__ int32_t s_h[];    // [sets][NBL]
+    const int tid = threadIdx.x, y = (int)blockIdx.y, l = P.lev[y];
+    const int nloc = P.NBL * n_table_sets(P);
+    for (int i = tid; i < nloc; i += kTgBlock) s_h[i] = 0;
+    __syncthreads();
+    const int64_t r = (int64_t)blockIdx.x * kTgBlock + tid;
+    const bool valid = r < P.n, few = few_buckets(P, l);
+    const uint32_t tmask = (1u << P.enc.log2T) - 1u, kmask = (1u << P.SB) - 1u;
+    const int64_t seg = P.c0 + (valid ? r : 0);
+    for (int p = 0; p < 2; ++p) {
+        const float* xs = p ? P.x1 : P.x0;
+        PEState pe;
+        pe_begin(pe, xs[seg], xs[P.B + seg], xs[2 * P.B + seg]);
+        for (int s = 0; s < P.S; ++s) {
+            double smp[3];
+            pe_sample(pe, s, smp);
+            Pairs pq;
+            float wt[3];
+            level_pairs(P.enc, l, smp, pq, wt);
+            int32_t* h = s_h + (P.enc.set_stride ? s : 0) * P.NBL;
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) {
+                const int b0 = (int)(pq.e[pr] >> P.SB);
+                (void)take_slot(h, b0, valid, few);
+                if (valid && pq.straddles(pr, kmask)) atomicAdd(&h[(int)(pq.upper(pr, tmask) >> P.SB)], 1);
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < nloc; i += kTgBlock) P.cnt[level_bucket_global(P, y, i) * P.n_blk + blockIdx.x] = s_h[i];
+}
+
+// Block (x, y): samples [kTgBlock (blk0 + x), + kTgBlock) of the round, record level y.  dE: panels of the chunk that
+// starts at sample drow0 of the batch, rows of pn samples.
+// A batch of KB combinations makes 4 kTgBlock KB records; they are sorted by bucket in LDS (rank in the
+// bucket from an LDS atomic, a scan over the buckets) and then stored in that order, so that a
+// wave's stores cover a few runs of records instead of 64 places.  The upper record of a pair
+// that straddles two buckets takes a slot from the end of the block's range and is stored directly.
+template <int KB>
+__global__ void __launch_bounds__(kTgBlock) k_tg_fill(EncBwdParams P, const int32_t* __restrict__ total,
+                                                 const float2* __restrict__ dE, int64_t pn) {
+    constexpr int NR = 4 * kTgBlock * KB;
+    // [2][sets][NBL]: first free slot per bucket, end of the free slots; then the batch's buckets:
+    // [nh] records, [nh] (first sorted place, first slot)
+    extern __shared__ int32_t s_dyn[];
+    __shared__ float4 s_rec[NR];
+    __shared__ uint16_t s_bkt[NR];
+    __shared__ int32_t s_n;
+    const int tid = threadIdx.x, y = (int)blockIdx.y, l = P.lev[y];
+    const int bx = (int)blockIdx.x + P.blk0;
+    const bool sets = P.enc.set_stride != 0;
+    const int nloc = P.NBL * n_table_sets(P), nh = sets ? KB * P.NBL : P.NBL;
+    const uint32_t kmask = (1u << P.SB) - 1u, tmask = (1u << P.enc.log2T) - 1u;
+    int32_t* s_cur = s_dyn;
+    int32_t* s_end = s_dyn + nloc;
+    int32_t* s_hist = s_end + nloc;
+    int2* s_at = reinterpret_cast<int2*>(s_hist + nh);
+    const int64_t n_cnt = (int64_t)P.n_buckets * P.n_blk;
+    for (int i = tid; i < nloc; i += kTgBlock) {
+        const int64_t k = level_bucket_global(P, y, i) * P.n_blk + bx;
+        s_cur[i] = P.cnt[k];
+        s_end[i] = k + 1 < n_cnt ? P.cnt[k + 1] : *total;
+    }
+    for (int i = tid; i < nh; i += kTgBlock) s_hist[i] = 0;
+    __syncthreads();
+    const int64_t r = (int64_t)bx * kTgBlock + tid;
+    const bool valid = r < P.n, few = few_buckets(P, l);
+    const int64_t seg = P.c0 + (valid ? r : 0);
+    const float2* de = dE + (int64_t)l * 2 * P.S * pn + (valid ? seg - P.drow0 : 0);
+    float vmx = 0.f;                       // largest |addition| of this lane (inf if not finite)
+    const int C = 2 * P.S;
+    PEState pe;
+    float2 gn = de[0];
+    for (int c0 = 0; c0 < C; c0 += KB) {
+        float4 rec[KB][4];
+        int bk[KB][4], rk[KB][4];
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            const int c = c0 + k;
+            const bool live = valid && c < C;
+            if (c < C) {
+                const int pt = c >= P.S ? 1 : 0, s = c - pt * P.S;
+                if (s == 0) {
+                    const float* xs = pt ? P.x1 : P.x0;
+                    pe_begin(pe, xs[seg], xs[P.B + seg], xs[2 * P.B + seg]);
+                }
+                const float2 g = gn;
+                if (c + 1 < C) gn = de[(int64_t)(c + 1) * pn];
+                double smp[3];
+                pe_sample(pe, s, smp);
+                Pairs pq;
+                float wt[3];
+                level_pairs(P.enc, l, smp, pq, wt);
+                const int set0 = sets ? s * P.NBL : 0;
+                // the largest of the four pairs' |A g| (products of the larger factors: rounding is monotonic)
+                const float Am = fmaxf(wt[1], 1.f - wt[1]) * fmaxf(wt[2], 1.f - wt[2]);
+                const bool fin = (g.x - g.x) + (g.y - g.y) == 0.f;
+                if (live) vmx = fin ? fmaxf(vmx, Am * fmaxf(fabsf(g.x), fabsf(g.y))) : INFINITY;
+                const uint32_t flipk = pq.flip ? pq.flip & kmask : 0u;
+#pragma unroll
+                for (int pr = 0; pr < 4; ++pr) {
+                    const float A = ((pr & 1) ? wt[1] : 1.f - wt[1]) * ((pr >> 1) ? wt[2] : 1.f - wt[2]);
+                    const float a0 = A * g.x, a1 = A * g.y;
+                    const uint32_t k0 = pq.e[pr] & kmask, k1 = flipk ? k0 ^ flipk : k0 + 1u;
+                    rec[k][pr] = make_float4(a0, a1, wt[0], __uint_as_float(pair_key(k0, k1)));
+                    if (pq.straddles(pr, kmask)) {
+                        const float w0 = 1.f - wt[0];
+                        rec[k][pr] = make_float4(w0 * a0, w0 * a1, 0.f, __uint_as_float(pair_key(k0, k0)));
+                        if (live) {
+                            const uint32_t e1 = pq.upper(pr, tmask), q1 = e1 & kmask;
+                            const int32_t s1 = atomicSub(&s_end[set0 + (int)(e1 >> P.SB)], 1) - 1;
+                            if (s1 < P.cap)      // always: the count pass saw the same records
+                                *reinterpret_cast<float4*>(P.val + (size_t)s1 * kRecFloats) =
+                                    make_float4(wt[0] * a0, wt[0] * a1, 0.f, __uint_as_float(pair_key(q1, q1)));
+                        }
+                    }
+                    bk[k][pr] = (sets ? k * P.NBL : 0) + (int)(pq.e[pr] >> P.SB);
+                    rk[k][pr] = take_slot(s_hist, bk[k][pr], live, few);
+                }
+            }
+        }
+        lds_barrier();
+        // exclusive scan of the batch's bucket counts; the block's cursors move on
+        if (tid < 64) {
+            const int per = (nh + 63) / 64;
+            int32_t sum = 0;
+            for (int t = 0; t < per; ++t) {
+                const int i = tid * per + t;
+                if (i < nh) sum += s_hist[i];
+            }
+            int32_t inc = sum;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int32_t v = __shfl_up(inc, o);
+                if (tid >= o) inc += v;
+            }
+            int32_t run = inc - sum;
+            for (int t = 0; t < per; ++t) {
+                const int i = tid * per + t;
+                if (i < nh) {
+                    const int32_t h = s_hist[i];
+                    int2 at = make_int2(run, 0);
+                    run += h;
+                    const int cb = c0 + i / P.NBL;                                  // combination of set bucket i
+                    const int ci = sets ? (cb >= P.S ? cb - P.S : cb) * P.NBL + i % P.NBL : i;
+                    if (!sets || cb < C) {
+                        at.y = s_cur[ci];
+                        s_cur[ci] += h;
+                    }
+                    s_at[i] = at;
+                    s_hist[i] = 0;
+                }
+            }
+            if (tid == 63) s_n = inc;
+        }
+        lds_barrier();
+#pragma unroll
+        for (int k = 0; k < KB; ++k)
+            if (valid && c0 + k < C)
+#pragma unroll
+                for (int pr = 0; pr < 4; ++pr) {
+                    const int at = s_at[bk[k][pr]].x + rk[k][pr];
+                    s_rec[at] = rec[k][pr];
+                    s_bkt[at] = (uint16_t)bk[k][pr];
+                }
+        lds_barrier();
+        const int nr = s_n;
+        for (int i = tid; i < nr; i += kTgBlock) {
+            const int2 at = s_at[s_bkt[i]];
+            const int32_t d = at.y + (i - at.x);
+            if (d < P.cap) *reinterpret_cast<float4*>(P.val + (size_t)d * kRecFloats) = s_rec[i];
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) vmx = fmaxf(vmx, __shfl_xor(vmx, off));
+    if (lane_id() == 0 && vmx > 0.f) atomicMax(P.vmax, __float_as_uint(vmx));   // non-negative: bits order as values
+}
+
+// Levels whose table (or dense grid) is small enough to be summed in LDS as it is: no records.  A
+// level of up to kDirectWindows windows of kDirectWindow entries (64-bit fixed-point sums of both
+// features) is taken.  A block goes through its share of the chunk's samples for one window of one
+// level, skipping cells outside, and adds its sums to the level's in memory (64-bit integers: exact,
+// in any order).  The levels get equal numbers of blocks, whatever their windows (the atomics are
+// the same, a further window costs another walk over the positions), and the lanes of a wave take
+// samples far apart: neighbours in a spatially ordered batch share cells, and LDS atomics on one
+// address go one after the other.
+constexpr int kDirectWindow = 9600, kDirectWindows = 8;
+struct DirectPlan {
+    int32_t n;                        // levels
+    uint8_t lev[16], win[16];         // level, its windows
+    uint16_t shares[16];              // blocks per window
+    int32_t entries[16], off[16];     // entries used, first entry in acc
+    int64_t total;                    // entries of all levels
+};
+
+// Scale exponent of the 64-bit sums of at most n additions below vmax (any sum stays below 2^62).
+__device__ __forceinline__ int fixed_scale(float vmax, int64_t n) {
+    int ev = 0, nb = 0;
+    if (vmax > 0.f && isfinite(vmax)) (void)frexpf(vmax, &ev);          // vmax < 2^ev
+    while (nb < 40 && ((int64_t)1 << nb) < n + 1) ++nb;
+    return 62 - ev - nb;
+}
+
+// v 2^sc (below 2^62 in magnitude) rounded to a 64-bit integer: the same as through double, in FP32
+// steps that are all exact after the rounding (|v| has 24 bits, and floor splits them at 2^32).
+__device__ __forceinline__ unsigned long long to_fixed(float v, int sc) {
+    const float x = rintf(ldexpf(fabsf(v), sc));
+    const float hi = floorf(x * 0x1p-32f);
+    const float lo = fmaf(hi, -0x1p32f, x);                    // in [0, 2^32)
+    const unsigned long long u = ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
+    return v < 0.f ? 0ull - u : u;
+}
+
+__global__ void __launch_bounds__(1024) k_tg_direct(EncBwdParams P, DirectPlan D, const float2* __restrict__ dE, int64_t n,
+                                                    int64_t pn, unsigned long long* __restrict__ acc) {
+    extern __shared__ unsigned long long s_sum[];       // [2][window]: a feature's sums over all banks
+    const int tid = threadIdx.x;
+    int k = 0, b = (int)blockIdx.x;
+    while (b >= D.win[k] * D.shares[k]) { b -= D.win[k] * D.shares[k]; ++k; }
+    const int l = D.lev[k], W = D.win[k], G = D.shares[k], w = b / G, x = b % G;
+    const uint32_t wn = (uint32_t)((D.entries[k] + W - 1) / W), w0 = (uint32_t)w * wn;
+    for (int i = tid; i < 2 * (int)wn; i += 1024) s_sum[i] = 0ull;
+    const int sc = fixed_scale(__uint_as_float(*P.vmax), n * 2 * P.S * 8);
+    __syncthreads();
+    const int64_t i0 = n * (int64_t)x / G, i1 = n * (int64_t)(x + 1) / G;
+    const int run = (int)((i1 - i0 + 1023) / 1024);               // samples per thread, neighbours
+    const int64_t ib = i0 + (int64_t)((tid & 63) * 16 + (tid >> 6)) * run, ie = std::min<int64_t>(ib + run, i1);
+    const int C = 2 * P.S;
+    const uint32_t N = (uint32_t)P.enc.res[l], n1 = N + 1u, tmask = (1u << P.enc.log2T) - 1u;
+    const bool dense = (P.enc.dense_mask >> l) & 1u;
+    for (int64_t i = ib; i < ie; ++i) {
+        const int64_t seg = P.drow0 + i;
+        const float2* de = dE + (int64_t)l * C * pn + i;
+        float2 gn = de[0];
+        for (int p = 0; p < 2; ++p) {
+            const float* xs = p ? P.x1 : P.x0;
+            PEState pe;
+            pe_begin(pe, xs[seg], xs[P.B + seg], xs[2 * P.B + seg]);
+            for (int s = 0; s < P.S; ++s) {
+                const float2 g = gn;
+                if (p == 0 || s + 1 < P.S) gn = de[(int64_t)(p * P.S + s + 1) * pn];
+                double smp[3];
+                pe_sample(pe, s, smp);
+                Pairs pq;
+                float wt[3];
+                level_pairs(P.enc, l, smp, pq, wt);
+                if (dense && (pq.e[3] + 1u < w0 || pq.e[0] >= w0 + wn)) continue;
+#pragma unroll
+                for (int pr = 0; pr < 4; ++pr) {
+                    const float A = ((pr & 1) ? wt[1] : 1.f - wt[1]) * ((pr >> 1) ? wt[2] : 1.f - wt[2]);
+                    const float a[2] = {A * g.x, A * g.y};
+#pragma unroll
+                    for (int cx = 0; cx < 2; ++cx) {
+                        const uint32_t e = (cx ? pq.upper(pr, tmask) : pq.e[pr]) - w0;
+                        if (e >= wn) continue;
+                        const float wx = cx ? wt[0] : 1.f - wt[0];
+#pragma unroll
+                        for (int f = 0; f < 2; ++f)
+                            atomicAdd(&s_sum[f * wn + e], to_fixed(wx * a[f], sc));
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    unsigned long long* o = acc + 2 * ((int64_t)D.off[k] + w0);
+    const int lim = 2 * (int)min(wn, (uint32_t)D.entries[k] - min((uint32_t)D.entries[k], w0));
+    for (int i = tid; i < lim; i += 1024)
+        if (const unsigned long long v = s_sum[(i & 1) * wn + (i >> 1)]) atomicAdd(&o[i], v);
+}
+
+// Adds the direct levels' sums to the table gradient and clears them.  A non-finite addition
+// poisons the levels, so the step's finiteness check skips the update.
+__global__ void __launch_bounds__(256) k_tg_direct_add(EncBwdParams P, DirectPlan D, int64_t n, unsigned long long* __restrict__ acc) {
+    const float vmax = __uint_as_float(*P.vmax);
+    const bool finite = isfinite(vmax);
+    const int sc = fixed_scale(vmax, n * 2 * P.S * 8);
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < 2 * D.total; i += (int64_t)gridDim.x * 256) {
+        int k = 0;
+        while (k + 1 < D.n && i >= 2 * (int64_t)D.off[k + 1]) ++k;
+        const unsigned long long v = acc[i];
+        if (v == 0ull && finite) continue;
+        acc[i] = 0ull;
+        P.g_tables[((size_t)D.lev[k] << P.enc.log2T) * 2 + (i - 2 * (int64_t)D.off[k])] += finite ? (float)ldexp((double)(long long)v, -sc) : NAN;
+    }
+}
+
+// Point gradients through the grid, level by level (the table in L2, as k_encode_levels): block =
+// 64 samples x 4 quarters of the combinations; part[l][6][i] = d x of sample i through level l
+// (point 0's axes, then point 1's).  Summed by k_points_sum in level order.
+template <bool F16>
+__global__ void __launch_bounds__(256) k_points_levels(EncParams ep, EncPlan plan, const float* __restrict__ x0,
+                                                       const float* __restrict__ x1, int64_t n, int64_t ld,
+                                                       const float2* __restrict__ dE, float* __restrict__ part) {
+    __shared__ float s_d[4][6][64];
+    int l, grp, tile;
+    if (!plan_item(plan, l, grp, tile)) return;
+    const int S = 1 + 2 * ep.F, C = 2 * S, U = (C + 3) >> 2;
+    const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t pn = panel_stride(n);
+    const int64_t i = (int64_t)tile * 64 + lane;
+    float d[2][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+    if (i < n) {
+        const float sp[8] = {x0[i], x0[ld + i], x0[2 * ld + i], 0.f, x1[i], x1[ld + i], x1[2 * ld + i], 0.f};
+        const float res = (float)ep.res[l];
+        PEWalk w;
+        w.p = -1;
+        w.k = -1;
+        for (int u = 0; u < U; ++u) {
+            const int c = q * U + u;
+            if (c >= C) break;
+            const int p = c >= S ? 1 : 0, s = c - p * S;
+            double smp[3];
+            pe_walk(sp, c, S, w, smp);
+            Pairs pq;
+            float wt[3];
+            level_pairs(ep, l, smp, pq, wt);
+            const float2 g = dE[((int64_t)l * C + c) * pn + i];
+            const size_t base = (size_t)combo_set_offset(ep, c, S) + ((size_t)l << ep.log2T);
+            float2 v[4][2];
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr)
+#pragma unroll
+                for (int cx = 0; cx < 2; ++cx) {
+                    const size_t e = base + (cx ? pq.upper(pr, (1u << ep.log2T) - 1u) : pq.e[pr]);
+                    if constexpr (F16) v[pr][cx] = entry_f2(reinterpret_cast<const uint32_t*>(ep.tab)[e]);
+                    else v[pr][cx] = entry_f2(reinterpret_cast<const uint2*>(ep.tab)[e]);
+                }
+            float dl[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr)
+#pragma unroll
+                for (int cx = 0; cx < 2; ++cx) {
+                    const float gd = fmaf(g.y, v[pr][cx].y, g.x * v[pr][cx].x);
+                    const float fx = cx ? wt[0] : 1.f - wt[0];
+                    const float fy = (pr & 1) ? wt[1] : 1.f - wt[1];
+                    const float fz = (pr >> 1) ? wt[2] : 1.f - wt[2];
+                    dl[0] += gd * (cx ? 1.f : -1.f) * fy * fz;
+                    dl[1] += gd * ((pr & 1) ? 1.f : -1.f) * fx * fz;
+                    dl[2] += gd * ((pr >> 1) ? 1.f : -1.f) * fx * fy;
+                }
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float xv = sp[4 * p + a];
+                float ds = 1.f;
+                if (s > 0) {
+                    const double f = 0.5 * (double)(1 << ((s - 1) >> 1));
+                    ds = (float)((s & 1) ? f * w.cs[a] : -f * w.sn[a]);
+                }
+                const float t = xv >= 0.f && xv <= 1.f ? dl[a] * res * ds : 0.f;
+                if (p) d[1][a] += t; else d[0][a] += t;
+            }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) s_d[q][a][lane] = d[a / 3][a % 3];
+    __syncthreads();
+    for (int t = threadIdx.x; t < 6 * 64; t += 256) {
+        const int a = t >> 6, k = t & 63;
+        const int64_t ii = (int64_t)tile * 64 + k;
+        if (ii < n) part[((int64_t)l * 6 + a) * pn + ii] = (s_d[0][a][k] + s_d[1][a][k]) + (s_d[2][a][k] + s_d[3][a][k]);
+    }
+}
+
+__global__ void __launch_bounds__(256) k_points_sum(const float* __restrict__ part, int L, int64_t n, int64_t ld,
+                                                    float* __restrict__ dx0, float* __restrict__ dx1) {
+    const int64_t pn = panel_stride(n);
+    const int a = (int)blockIdx.y;
+    float* o = a < 3 ? dx0 : dx1;
+    if (!o) return;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        float v = 0.f;
+        for (int l = 0; l < L; ++l) v += part[((int64_t)l * 6 + a) * pn + i];
+        o[(int64_t)(a % 3) * ld + i] = v;
     }
 }
 
@@ -1278,8 +1758,10 @@ template <int FD> constexpr int kLog2Window = FD == 2 ? 12 : 11;
 // the scale 2^s, s = 62 - e - ceil(log2 N), keeps every partial sum below 2^62 while the unit
 // is 2^-31 to 2^-32 of the largest addition (2^18 samples per round); the sum is exact in
 // that unit and independent of order.
+constexpr int kReduceThreads = 512;
+constexpr int kReduceRun = 16;
 template <int FD>
-__global__ void __launch_bounds__(256) k_enc_bwd_reduce(EncBwdParams P, const int32_t* __restrict__ total,
+__global__ void __launch_bounds__(kReduceThreads) k_enc_bwd_reduce(EncBwdParams P, const int32_t* __restrict__ total,
                                                         const int32_t* __restrict__ parts) {
     constexpr int LW = kLog2Window<FD>, WN = 1 << LW;
     __shared__ unsigned long long s_acc[FD * WN];
@@ -1293,93 +1775,57 @@ __global__ void __launch_bounds__(256) k_enc_bwd_reduce(EncBwdParams P, const in
     const int b = lo;
     const int n_parts = parts[b + 1] - parts[b], part = i - parts[b];
     const int wn = P.SB < LW ? (1 << P.SB) : WN;     // entries per window
-    for (int k = threadIdx.x; k < FD * wn; k += 256) s_acc[k] = 0ull;
+    for (int k = threadIdx.x; k < FD * WN; k += kReduceThreads) s_acc[k] = 0ull;
     const float vmax = __uint_as_float(*P.vmax);
     const bool finite = isfinite(vmax);
-    int ev = 0;
-    if (vmax > 0.f && finite) (void)frexpf(vmax, &ev);          // vmax < 2^ev
-    int nb = 0;
-    while (nb < 40 && ((int64_t)1 << nb) < (int64_t)*total + 1) ++nb;
-    const int sc = 62 - ev - nb;
-    __syncthreads();
     const int64_t b_start = P.cnt[(int64_t)b * P.n_blk];
     const int64_t b_end = b + 1 < P.n_buckets ? (int64_t)P.cnt[(int64_t)(b + 1) * P.n_blk] : (int64_t)*total;
     const int64_t start = b_start + (int64_t)part * kReducePart;
     const int64_t end = std::min<int64_t>(b_end, start + kReducePart);
-    // Thread t takes 16 consecutive records per step (16-byte loads, coalesced across the
-    // wave): records next to each other come from neighbouring samples and often hit the same
-    // entries, so runs of equal keys are summed in registers before the LDS atomics, and the
-    // lanes of a wave work 16 records apart.  Every record adds at most |a| < 2^e in all (its
-    // two parts split a by weights summing to 1), so N counts records in the scale above.
-    const int64_t g0 = start >> 4, g1 = (end + 15) >> 4;      // aligned groups of 16
+    const int sc = fixed_scale(vmax, *total);
+    __syncthreads();
+    // One record per lane, neighbouring lanes on neighbouring records (a wave's load is one
+    // contiguous KiB); four steps in flight.  Every record adds at most |a| < 2^e in all (its two
+    // parts split a by weights summing to 1), so N counts records in the scale above.
     auto add_fixed = [&](uint32_t e, const float* r) {       // e: entry within the bucket
         if ((int)(e >> LW) != w) return;
         const int k = (int)(e & (WN - 1));
 #pragma unroll
-        for (int f = 0; f < FD; ++f)
-            if (r[f] != 0.f) atomicAdd(&s_acc[FD * k + f], (unsigned long long)llrint(ldexp((double)r[f], sc)));
+        for (int f = 0; f < FD; ++f) atomicAdd(&s_acc[f * WN + k], to_fixed(r[f], sc));
     };
-    for (int64_t g = g0 + threadIdx.x; g < g1; g += 256) {
-        const int64_t base = g << 4;
-        float vv[16 * kRecFloats];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float4 t = *reinterpret_cast<const float4*>(P.val + (base + r) * kRecFloats);
-            vv[4 * r] = t.x; vv[4 * r + 1] = t.y; vv[4 * r + 2] = t.z; vv[4 * r + 3] = t.w;
+    auto add_record = [&](const float4& t) {
+        const uint32_t key = __float_as_uint(t.w);
+        if constexpr (FD == 2) {
+            const float wl = 1.f - t.z;
+            const float lo[2] = {wl * t.x, wl * t.y}, hi[2] = {t.z * t.x, t.z * t.y};
+            add_fixed(key & 0xffffu, lo);
+            add_fixed(key >> 16, hi);
+        } else {
+            const float v[3] = {t.x, t.y, t.z};
+            add_fixed(key, v);
         }
-        bool have = false;
-        uint32_t cur = 0;
-        float r0[FD], r1[FD];
+    };
+    const float4* rec = reinterpret_cast<const float4*>(P.val);
+    const int64_t g0 = start / kReduceRun, g1 = (end + kReduceRun - 1) / kReduceRun;
+    for (int64_t g = g0 + threadIdx.x; g < g1; g += kReduceThreads) {
+        const int64_t base = g * kReduceRun;
+        float4 t[kReduceRun];
 #pragma unroll
-        for (int f = 0; f < FD; ++f) r0[f] = r1[f] = 0.f;
-        auto flush = [&]() {
-            if (!have) return;
-            if constexpr (FD == 2) {
-                add_fixed(cur & 0xffffu, r0);
-                add_fixed(cur >> 16, r1);
-            } else {
-                add_fixed(cur, r0);
-            }
-        };
+        for (int r = 0; r < kReduceRun; ++r) t[r] = rec[base + r];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t k = base + r;
-            if (k < start || k >= end) continue;
-            const float* rec = vv + kRecFloats * r;
-            const uint32_t key = __float_as_uint(rec[3]);
-            float c0[FD], c1[FD];
-            if constexpr (FD == 2) {
-                const float wx = rec[2];
-                const float wl = 1.f - wx;
-#pragma unroll
-                for (int f = 0; f < FD; ++f) { c0[f] = wl * rec[f]; c1[f] = wx * rec[f]; }
-            } else {
-#pragma unroll
-                for (int f = 0; f < FD; ++f) { c0[f] = rec[f]; c1[f] = 0.f; }
-            }
-            if (!have || key != cur) {
-                flush();
-                have = true;
-                cur = key;
-#pragma unroll
-                for (int f = 0; f < FD; ++f) { r0[f] = c0[f]; r1[f] = c1[f]; }
-            } else {
-#pragma unroll
-                for (int f = 0; f < FD; ++f) { r0[f] += c0[f]; r1[f] += c1[f]; }
-            }
-        }
-        flush();
+        for (int r = 0; r < kReduceRun; ++r)
+            if (base + r >= start && base + r < end) add_record(t[r]);
     }
     __syncthreads();
-    const int l = b / P.NBL, slice = b % P.NBL;
-    float* g = P.g_tables + (((size_t)l << P.enc.log2T) + ((size_t)slice << P.SB) + ((size_t)w << LW)) * FD;
+    const int set = b / (P.NBL * P.n_lev), l = P.lev[b / P.NBL % P.n_lev], slice = b % P.NBL;
+    float* g = P.g_tables + (((size_t)(set * P.enc.L + l) << P.enc.log2T) + ((size_t)slice << P.SB) + ((size_t)w << LW)) * FD;
     // a non-finite addition poisons the window, so the step's finiteness check skips the update
-    auto value = [&](int k) { return finite ? (float)ldexp((double)(long long)s_acc[k], -sc) : NAN; };
+    auto value = [&](int k) { return finite ? (float)ldexp((double)(long long)s_acc[k % FD * WN + k / FD], -sc) : NAN; };
     if (n_parts == 1) {
-        for (int k = threadIdx.x; k < FD * wn; k += 256) g[k] += value(k);
+        for (int k = threadIdx.x; k < FD * wn; k += kReduceThreads) g[k] += value(k);
     } else {
-        for (int k = threadIdx.x; k < FD * wn; k += 256)
-            if (s_acc[k] != 0ull || !finite) unsafeAtomicAdd(&g[k], value(k));
+        for (int k = threadIdx.x; k < FD * wn; k += kReduceThreads)
+            if (s_acc[k % FD * WN + k / FD] != 0ull || !finite) unsafeAtomicAdd(&g[k], value(k));
     }
 }
 
@@ -1590,7 +2036,7 @@ static int weight_grad(nif_model* m, int layer, const float* d, int dstride, int
     A.h = h;
     A.hstride = N;
     if (layer == 0 && uses_panels(m)) {
-        A.hstride = (int)((B + 15) & ~(int64_t)15);
+        A.hstride = (int)panel_stride(B);
         A.panel_C = 2 * m->S;
         A.panel_L = m->desc.levels;
     }
@@ -1606,6 +2052,28 @@ static int weight_grad(nif_model* m, int layer, const float* d, int dstride, int
     hipLaunchKernelGGL(k_dw_sum, dim3((unsigned)((n_out + 63) / 64)), dim3(64 * kDwSumGroups), 0, st, A,
                        m->g_mlp + m->w_off[layer], A.N, m->g_mlp + m->b_off[layer]);
     return NIF_OK;
+}
+
+// The levels summed in LDS without records: two features, one table set, few enough entries.
+static DirectPlan direct_plan(const nif_model* m, const EncParams& ep) {
+    DirectPlan D;
+    memset(&D, 0, sizeof(D));
+    if (m->desc.feat_dim != 2 || m->desc.per_sample_tables) return D;
+    for (int l = 0; l < m->desc.levels; ++l) {
+        const int64_t n1 = (int64_t)m->desc.res[l] + 1;
+        const int64_t e = (ep.dense_mask >> l) & 1u ? n1 * n1 * n1 : (int64_t)1 << m->desc.log2_table;
+        if (e > (int64_t)kDirectWindow * kDirectWindows) {           // records for every level, then
+            memset(&D, 0, sizeof(D));
+            return D;
+        }
+        D.lev[D.n] = (uint8_t)l;
+        D.win[D.n] = (uint8_t)((e + kDirectWindow - 1) / kDirectWindow);
+        D.entries[D.n] = (int32_t)e;
+        D.off[D.n] = (int32_t)D.total;
+        D.total += e;
+        ++D.n;
+    }
+    return D;
 }
 
 // Table-gradient parameters of a batch (points SoA with stride B, delta rows from drow0).
@@ -1625,7 +2093,13 @@ static EncBwdParams table_grad_params(nif_model* m, const float* x0, const float
     ep.SB = log2T <= 12 ? log2T : std::max(12, log2T - 8);
     ep.NBL = 1 << (log2T - ep.SB);
     const int n_sets = m->desc.per_sample_tables ? m->S : 1;
-    ep.n_buckets = m->desc.levels * n_sets * ep.NBL;
+    const DirectPlan D = direct_plan(m, ep.enc);
+    ep.n_lev = 0;
+    for (int l = 0, k = 0; l < m->desc.levels; ++l) {
+        if (k < D.n && D.lev[k] == l) { ++k; continue; }
+        ep.lev[ep.n_lev++] = (uint8_t)l;
+    }
+    ep.n_buckets = ep.n_lev * n_sets * ep.NBL;
     ep.cnt = m->bwd_cnt; ep.val = m->bwd_val;
     ep.cap = m->bwd_round * 2 * m->S * m->desc.levels * 8;
     ep.vmax = nullptr;
@@ -1642,14 +2116,27 @@ struct TgRound {
     int32_t* parts;
 };
 
-template <int FD>
-static TgRound tg_begin_fd(nif_model* m, EncBwdParams ep, int64_t c0, int64_t n, hipStream_t sd) {
-    constexpr int LG = kLevelGroup<FD>;
+// The direct levels' sums, zero between chunks.
+static int reserve_direct(nif_model* m) {
+    if (m->dir_acc) return NIF_OK;
+    const size_t bytes = sizeof(unsigned long long) * 2 * (size_t)direct_plan(m, make_net_params(m, NIF_PREC_FP32).enc).total;
+    if (bytes == 0) return NIF_OK;
+    if (hipMalloc((void**)&m->dir_acc, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        m->dir_acc = nullptr;
+        return fail(NIF_E_OOM, "table-gradient sums allocation failed");
+    }
+    return check_hip(hipMemset(m->dir_acc, 0, bytes), "zero table-gradient sums");
+}
+
+static int64_t tg_block_samples(int feat_dim) { return feat_dim == 2 ? kTgBlock : 16 * kBwdTilesPerBlock; }
+
+static TgRound tg_begin(nif_model* m, EncBwdParams ep, int64_t c0, int64_t n, hipStream_t sd) {
     ep.c0 = c0;
     ep.n = n;
     ep.blk0 = 0;
-    const int64_t n_tiles = (ep.n + 15) / 16;
-    ep.n_blk = (int32_t)((n_tiles + kBwdTilesPerBlock - 1) / kBwdTilesPerBlock);
+    const int64_t per_blk = tg_block_samples(m->desc.feat_dim);
+    ep.n_blk = (int32_t)((n + per_blk - 1) / per_blk);
     const int64_t n_cnt = (int64_t)ep.n_buckets * ep.n_blk;
     const int n_chunks = (int)((n_cnt + 4095) / 4096);
     int32_t* sums = m->bwd_scan;
@@ -1658,44 +2145,91 @@ static TgRound tg_begin_fd(nif_model* m, EncBwdParams ep, int64_t c0, int64_t n,
     R.parts = R.total + 1;
     ep.vmax = reinterpret_cast<uint32_t*>(R.parts + ep.n_buckets + 1);
     const int n_sets = m->desc.per_sample_tables ? m->S : 1;
-    const dim3 fg((unsigned)ep.n_blk, (unsigned)(m->desc.levels / LG));
-    const size_t lds_f = sizeof(int32_t) * LG * (size_t)ep.NBL * n_sets;
-    hipLaunchKernelGGL(k_enc_bwd_count<FD>, fg, dim3(256), lds_f, sd, ep);
+    R.ep = ep;
+    if (m->desc.feat_dim == 2) hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(64), 0, sd, reinterpret_cast<float*>(ep.vmax), (int64_t)1);
+    if (ep.n_lev == 0) return R;
+    const dim3 fg((unsigned)ep.n_blk, (unsigned)ep.n_lev);
+    const size_t lds_f = sizeof(int32_t) * (size_t)ep.NBL * n_sets;
+    if (m->desc.feat_dim == 2) hipLaunchKernelGGL(k_tg_count, fg, dim3(kTgBlock), lds_f, sd, ep);
+    else hipLaunchKernelGGL(k_enc_bwd_count3, fg, dim3(256), lds_f, sd, ep);
     hipLaunchKernelGGL(k_scan_sums, dim3(n_chunks), dim3(256), 0, sd, ep.cnt, n_cnt, sums);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, sd, sums, n_chunks, R.total);
     hipLaunchKernelGGL(k_scan_apply, dim3(n_chunks), dim3(256), 0, sd, ep.cnt, n_cnt, sums);
-    R.ep = ep;
     return R;
 }
 
-// Fill of the round's samples [c0, c0 + n) (whole blocks of the round: c0 - round start is a
-// multiple of 16 kBwdTilesPerBlock, or n reaches the round's end); delta rows of sample seg at
-// delta + (seg - drow0) HW.
-template <int FD>
-static void tg_fill_fd(nif_model* m, const TgRound& R, const float* delta, int64_t drow0, int64_t c0, int64_t n,
-                       hipStream_t sd) {
-    constexpr int LG = kLevelGroup<FD>;
+template <int HW>
+static void launch_denc(const EncBwdParams& ep, int L, const float* delta, int64_t n, int cus, float* dE, hipStream_t sd) {
+    constexpr int CB = 4;
+    const int64_t blocks = (n + 64 * CB - 1) / (64 * CB);
+    // two waves per SIMD before each wave walks all tiles
+    const unsigned y = (unsigned)std::max<int64_t>(1, std::min<int64_t>(16, 2LL * cus / blocks));
+    hipLaunchKernelGGL((k_denc_panels<HW, CB>), dim3((unsigned)blocks, y), dim3(256), 0, sd, ep.W0t, L, 2 * ep.S, delta, n,
+                       (float2*)dE, ep.n_lev == 0 ? ep.vmax : nullptr);     // the fill bounds the records itself
+}
+
+// Fill of the round's samples [c0, c0 + n), a chunk of the batch (whole blocks of the round: c0 -
+// round start is a multiple of the block's samples, or n reaches the round's end); delta: the
+// chunk's first-layer deltas [n][HW].
+static void tg_fill(nif_model* m, const TgRound& R, const float* delta, int64_t c0, int64_t n, hipStream_t sd) {
     EncBwdParams ep = R.ep;
     ep.delta0 = delta;
-    ep.drow0 = drow0;
-    const int64_t per_blk = 16 * kBwdTilesPerBlock;
+    ep.drow0 = c0;
+    const int64_t per_blk = tg_block_samples(m->desc.feat_dim);
     ep.blk0 = (int32_t)((c0 - ep.c0) / per_blk);
     const int64_t blk1 = std::min<int64_t>(ep.n_blk, (c0 + n - ep.c0 + per_blk - 1) / per_blk);
     const int hw = m->desc.hidden_width;
     const int n_sets = m->desc.per_sample_tables ? m->S : 1;
-    const dim3 fg((unsigned)(blk1 - ep.blk0), (unsigned)(m->desc.levels / LG));
-    // the fill's staged first-layer rows: 4 per PE combination, hw + 4 floats each (up to 60 KiB)
-    const int nloc = LG * ep.NBL * n_sets;
+    const dim3 fg((unsigned)(blk1 - ep.blk0), (unsigned)ep.n_lev);
+    const int nloc = ep.NBL * n_sets;
     const size_t lds_f = sizeof(int32_t) * (size_t)nloc;
+    if (m->desc.feat_dim == 2) {
+        switch (hw) {
+            case 16: launch_denc<16>(ep, m->desc.levels, delta, n, cus(), m->denc, sd); break;
+            case 32: launch_denc<32>(ep, m->desc.levels, delta, n, cus(), m->denc, sd); break;
+            case 64: launch_denc<64>(ep, m->desc.levels, delta, n, cus(), m->denc, sd); break;
+            default: launch_denc<128>(ep, m->desc.levels, delta, n, cus(), m->denc, sd); break;
+        }
+        const float2* dE = (const float2*)m->denc;
+        if (ep.dx0 || ep.dx1) {
+            const EncPlan plan = level_plan(ep.enc, (n + 63) / 64, 1);
+            if (ep.enc.f16)
+                hipLaunchKernelGGL(k_points_levels<true>, dim3(plan_blocks(plan)), dim3(256), 0, sd, ep.enc, plan, ep.x0 + c0,
+                                   ep.x1 + c0, n, ep.B, dE, m->dx_part);
+            else
+                hipLaunchKernelGGL(k_points_levels<false>, dim3(plan_blocks(plan)), dim3(256), 0, sd, ep.enc, plan, ep.x0 + c0,
+                                   ep.x1 + c0, n, ep.B, dE, m->dx_part);
+            hipLaunchKernelGGL(k_points_sum, dim3(grid_for(n), 6), dim3(256), 0, sd, m->dx_part, m->desc.levels, n, ep.B,
+                               ep.dx0 ? ep.dx0 + c0 : nullptr, ep.dx1 ? ep.dx1 + c0 : nullptr);
+        }
+        DirectPlan D = direct_plan(m, ep.enc);
+        if (D.n > 0) {
+            // one block per compute unit in all, each with at least one sample per thread
+            int most = 0, blocks = 0;
+            for (int k = 0; k < D.n; ++k) {
+                most = std::max(most, (D.entries[k] + D.win[k] - 1) / D.win[k]);
+                D.shares[k] = (uint16_t)std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, cus() / (D.n * D.win[k])));
+                blocks += D.win[k] * D.shares[k];
+            }
+            hipLaunchKernelGGL(k_tg_direct, dim3((unsigned)blocks), dim3(1024), sizeof(unsigned long long) * 2 * most, sd, ep, D, dE,
+                               n, panel_stride(n), m->dir_acc);
+            hipLaunchKernelGGL(k_tg_direct_add, dim3(grid_for(2 * D.total)), dim3(256), 0, sd, ep, D, n, m->dir_acc);
+        }
+        if (ep.n_lev > 0)
+            hipLaunchKernelGGL(k_tg_fill<kTgBatch>, fg, dim3(kTgBlock),
+                               2 * lds_f + sizeof(int32_t) * 3 * (size_t)ep.NBL * (n_sets > 1 ? kTgBatch : 1), sd, ep, R.total, dE, panel_stride(n));
+        return;
+    }
+    // three features: the staged first-layer rows, 4 per PE combination, hw + 4 floats each
     const size_t w_bytes = sizeof(float) * 4 * (size_t)(2 * m->S) * (size_t)(hw + 4);
     const size_t cur_bytes = sizeof(int32_t) * (size_t)((nloc + 3) & ~3);
     ep.w_lds = cur_bytes + w_bytes <= kFillLdsMax ? 1 : 0;
     const size_t lds_fill = ep.w_lds ? cur_bytes + w_bytes : lds_f;
     switch (hw) {
-        case 16: hipLaunchKernelGGL((k_enc_bwd_fill<16, FD>), fg, dim3(256), lds_fill, sd, ep); break;
-        case 32: hipLaunchKernelGGL((k_enc_bwd_fill<32, FD>), fg, dim3(256), lds_fill, sd, ep); break;
-        case 64: hipLaunchKernelGGL((k_enc_bwd_fill<64, FD>), fg, dim3(256), lds_fill, sd, ep); break;
-        default: hipLaunchKernelGGL((k_enc_bwd_fill<128, FD>), fg, dim3(256), lds_fill, sd, ep); break;
+        case 16: hipLaunchKernelGGL((k_enc_bwd_fill3<16>), fg, dim3(256), lds_fill, sd, ep); break;
+        case 32: hipLaunchKernelGGL((k_enc_bwd_fill3<32>), fg, dim3(256), lds_fill, sd, ep); break;
+        case 64: hipLaunchKernelGGL((k_enc_bwd_fill3<64>), fg, dim3(256), lds_fill, sd, ep); break;
+        default: hipLaunchKernelGGL((k_enc_bwd_fill3<128>), fg, dim3(256), lds_fill, sd, ep); break;
     }
 }
 
@@ -1705,19 +2239,12 @@ static void tg_end_fd(nif_model* m, const TgRound& R, hipStream_t sd) {
     const EncBwdParams& ep = R.ep;
     const unsigned n_win = ep.SB > LW ? 1u << (ep.SB - LW) : 1u;
     hipLaunchKernelGGL(k_enc_bwd_parts, dim3(1), dim3(1024), 0, sd, ep, R.total, R.parts);
-    const int64_t max_parts = ep.n_buckets + (ep.n * 2 * m->S * m->desc.levels * 8) / kReducePart + 1;
-    hipLaunchKernelGGL(k_enc_bwd_reduce<FD>, dim3((unsigned)max_parts, n_win), dim3(256), 0, sd, ep, R.total, R.parts);
+    const int64_t max_parts = ep.n_buckets + (ep.n * 2 * m->S * ep.n_lev * 8) / kReducePart + 1;
+    hipLaunchKernelGGL(k_enc_bwd_reduce<FD>, dim3((unsigned)max_parts, n_win), dim3(kReduceThreads), 0, sd, ep, R.total, R.parts);
 }
 
-static TgRound tg_begin(nif_model* m, const EncBwdParams& ep, int64_t c0, int64_t n, hipStream_t sd) {
-    return m->desc.feat_dim == 3 ? tg_begin_fd<3>(m, ep, c0, n, sd) : tg_begin_fd<2>(m, ep, c0, n, sd);
-}
-static void tg_fill(nif_model* m, const TgRound& R, const float* delta, int64_t drow0, int64_t c0, int64_t n,
-                    hipStream_t sd) {
-    if (m->desc.feat_dim == 3) tg_fill_fd<3>(m, R, delta, drow0, c0, n, sd);
-    else tg_fill_fd<2>(m, R, delta, drow0, c0, n, sd);
-}
 static void tg_end(nif_model* m, const TgRound& R, hipStream_t sd) {
+    if (R.ep.n_lev == 0) return;
     if (m->desc.feat_dim == 3) tg_end_fd<3>(m, R, sd);
     else tg_end_fd<2>(m, R, sd);
 }
@@ -1807,7 +2334,7 @@ static int gradient_chunks(nif_model* m, const float* x0, const float* x1, int64
         else if (prec == NIF_PREC_BF16) rc = dispatch_mlp_bwd<P_BF16>(hw, bp, dz_c, acts_c, delta_c, n, st);
         else rc = dispatch_mlp_bwd<P_FP16>(hw, bp, dz_c, acts_c, delta_c, n, st);
         if (rc || (rc = fork())) break;
-        tg_fill(m, R, delta_c, c0, c0, n, sd);     // layer 0 of the chunk's block
+        tg_fill(m, R, delta_c, c0, n, sd);     // layer 0 of the chunk's block
         if (prev_c0 >= 0 && (rc = chunk_weight_grads(prev_c0, prev_n))) break;
         prev_c0 = c0;
         prev_n = n;
