@@ -187,6 +187,99 @@ __global__ void __launch_bounds__(256) k_encode_levels(EncParams ep, EncPlan pla
     }
 }
 
+// Levels whose entries fit an LDS: encoded from there.  A block of 1024 threads copies the level's
+// table (at most kLdsTableBytes) and looks up its share of the (combination, segment) pairs; the
+// corners cost LDS reads instead of L2 requests, which bound k_encode_levels (16,212 pairs at 8
+// levels of 2^14 FP32 entries: 58 us there).
+constexpr int kLdsTableBytes = 152 * 1024;
+struct LdsPlan {
+    int32_t n;                  // levels
+    uint8_t lev[16];
+    uint16_t blocks[16];        // blocks of each
+    int32_t entries[16];        // entries in use
+    int32_t total, bytes;       // blocks in all, largest table
+};
+inline LdsPlan lds_plan(const EncParams& ep, int64_t n, int cus) {
+    LdsPlan P;
+    memset(&P, 0, sizeof(P));
+    if (ep.set_stride) return P;                        // one table set per sample: too many tables
+    const int size = ep.f16 ? 4 : 8;
+    for (int l = 0; l < ep.L; ++l) {
+        const int64_t n1 = ep.res[l] + 1;
+        const int64_t e = (ep.dense_mask >> l) & 1u ? n1 * n1 * n1 : (int64_t)1 << ep.log2T;
+        if (e * size > kLdsTableBytes) continue;
+        P.lev[P.n] = (uint8_t)l;
+        P.entries[P.n] = (int32_t)e;
+        P.bytes = std::max<int32_t>(P.bytes, (int32_t)((e * size + 15) / 16 * 16));
+        ++P.n;
+    }
+    const int64_t lookups = 2 * (1 + 2 * (int64_t)ep.F) * n;
+    for (int k = 0; k < P.n; ++k) {
+        // one block per compute unit over all levels, each with enough lookups to pay for the copy
+        const int64_t least = std::max<int64_t>(4096, P.entries[k] / 2);
+        P.blocks[k] = (uint16_t)std::max<int64_t>(1, std::min<int64_t>(lookups / least, cus / P.n));
+        P.total += P.blocks[k];
+    }
+    return P;
+}
+
+template <bool F16>
+__global__ void __launch_bounds__(1024) k_encode_lds(EncParams ep, LdsPlan plan, const uint32_t* __restrict__ pos, uint32_t n,
+                                                     float2* __restrict__ enc) {
+    using E = typename TabTypes<F16>::E;
+    extern __shared__ uint4 s_raw[];
+    E* s_tab = reinterpret_cast<E*>(s_raw);
+    int k = 0, b = (int)blockIdx.x;
+    while (b >= plan.blocks[k]) b -= plan.blocks[k++];
+    const int l = plan.lev[k], G = plan.blocks[k];
+    const E* tab = reinterpret_cast<const E*>(ep.tab) + ((size_t)l << ep.log2T);
+    for (int e = threadIdx.x; e < plan.entries[k]; e += 1024) s_tab[e] = tab[e];
+    __syncthreads();
+    const uint32_t C = 2 * (1 + 2 * ep.F), all = C * n;
+    const int64_t pn = panel_stride(n);
+    const uint32_t f0 = (uint32_t)((uint64_t)all * b / G), f1 = (uint32_t)((uint64_t)all * (b + 1) / G);
+    const uint32_t N = (uint32_t)ep.res[l], n1 = N + 1u, mask = (1u << ep.log2T) - 1u;
+    const bool dense = (ep.dense_mask >> l) & 1u;
+    for (uint32_t f = f0 + threadIdx.x; f < f1; f += 1024) {
+        const uint32_t c = f / n, i = f - c * n;
+        const uint32_t* p = pos + (int64_t)c * 3 * pn + i;
+        uint32_t ix, iy, iz;
+        float wx, wy, wz;
+        fix_axis(p[0], N, ix, wx);
+        fix_axis(p[pn], N, iy, wy);
+        fix_axis(p[2 * pn], N, iz, wz);
+        E v[4][2];
+        if (dense) {
+            const uint32_t e = ix + n1 * (iy + n1 * iz);
+#pragma unroll
+            for (int pp = 0; pp < 4; ++pp) {
+                const uint32_t o = e + ((pp & 1) ? n1 : 0u) + ((pp >> 1) ? n1 * n1 : 0u);
+                v[pp][0] = s_tab[o];
+                v[pp][1] = s_tab[o + 1];
+            }
+        } else {
+            const uint32_t y0 = iy * 2654435761u, z0 = iz * 805459861u;
+#pragma unroll
+            for (int pp = 0; pp < 4; ++pp) {
+                const uint32_t hyz = (y0 + ((pp & 1) ? 2654435761u : 0u)) ^ (z0 + ((pp >> 1) ? 805459861u : 0u));
+                v[pp][0] = s_tab[(ix ^ hyz) & mask];
+                v[pp][1] = s_tab[((ix + 1u) ^ hyz) & mask];
+            }
+        }
+        float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int pp = 0; pp < 4; ++pp)
+#pragma unroll
+            for (int cx = 0; cx < 2; ++cx) {
+                const float wt = (cx ? wx : 1.f - wx) * ((pp & 1) ? wy : 1.f - wy) * ((pp >> 1) ? wz : 1.f - wz);
+                const float2 e = entry_f2(v[pp][cx]);
+                acc.x = fmaf(wt, e.x, acc.x);
+                acc.y = fmaf(wt, e.y, acc.y);
+            }
+        enc[((int64_t)l * C + c) * pn + i] = acc;
+    }
+}
+
 // First layer of segments i0 .. i0 + 16 CB - 1 (of n) from their panels, added to acc: the MFMA
 // steps of layer1_levels in the same order on the same values (lane (q, j) supplies combination
 // q U + u of segment j, level batches of 4), with the next batch's features and weights in flight
