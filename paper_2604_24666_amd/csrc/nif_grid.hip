@@ -234,15 +234,16 @@ __global__ void k_bin_fill(const PoseDev* __restrict__ poses, const float4* __re
     const int32_t* st = start + P.bin_off;
     int32_t* cur = cursor + P.bin_off;
     int32_t* out = cells + P.ref_off;
+    const int32_t packed = pack_cell(cell, N);
     for (int z = b0[2]; z <= b1[2]; ++z)
         for (int y = b0[1]; y <= b1[1]; ++y)
             for (int x = b0[0]; x <= b1[0]; ++x) {
                 int b = x + P.nb[0] * (y + P.nb[1] * z);
-                out[st[b] + atomicAdd(&cur[b], 1)] = cell;
+                out[st[b] + atomicAdd(&cur[b], 1)] = packed;
             }
 }
 
-// Sort each bin's list by voxel id (insertion sort; lists are short) so the build is
+// Sort each bin's list by packed voxel, that is by voxel id (insertion sort; lists are short) so the build is
 // deterministic.
 __global__ void k_bin_sort(const PoseDev* __restrict__ poses, const int32_t* __restrict__ start,
                            int32_t* __restrict__ cells) {

@@ -15,7 +15,7 @@ struct nif_grid {
     nif::PoseDev* poses = nullptr;          // device [n_poses]
     float4* verts = nullptr;                // device [n_poses][(N+1)^3]
     int32_t* bin_start = nullptr;           // device, per pose nbins + 1 (exclusive scan)
-    int32_t* bin_cells = nullptr;           // device, occupied voxel ids per bin
+    int32_t* bin_cells = nullptr;           // device, occupied voxels per bin (pack_cell)
     int32_t* list = nullptr;                // device, occupied voxel ids (shared by all poses)
     int32_t* counts = nullptr;              // device, per-bin counters (build scratch)
     int32_t* scratch = nullptr;             // device, boxes / totals / flags

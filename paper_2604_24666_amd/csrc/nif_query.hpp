@@ -207,7 +207,8 @@ __device__ __forceinline__ void unpark_trav(const Parked& pk, Trav& T) {
 #endif
 
 // RPW rays per wave (64, or 16 for launches too small to hide the latency of a network round:
-// then a round is one pass of 16 segments instead of four, and four times as many waves run).
+// then a round is one pass of 16 segments instead of four, four lanes search each ray's voxels, and
+// four times as many waves run).
 template <int HW, int PREC, int RPW, bool GAMMA = false, int FD = 2>
 __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np, GridArgs G, RayArgs R, nif_hits out,
                                               int64_t* __restrict__ counters, int64_t* __restrict__ stats,
@@ -218,7 +219,12 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
     __shared__ int32_t s_park[QW_WORDS * 64];
     __shared__ float s_seg[64 * kSegStride];
     __shared__ float s_z[64 * kZStride];
+    // With 16 rays a wave, four lanes share a ray: they hold the same state, search its voxels
+    // together (next_segment) and the first of them (lead) writes.  idx: the ray within the wave.
+    constexpr int SUB = 64 / RPW;
     const int lane = lane_id();
+    const int idx = lane / SUB;
+    const bool lead = SUB == 1 || lane % SUB == 0;
     const Parked pk{s_park, lane};
     const int n_mat = np.H - 8;
 
@@ -275,17 +281,17 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
         bool hitnow = false;
         if (has) {
             ++nq;
-            ++n_eval;
-            const float* z = s_z + lane * kZStride;
+            if (lead) ++n_eval;
+            const float* z = s_z + idx * kZStride;
             last_z0 = z[0];
             if (z[0] > 0.f) {
                 sg.cell = pk.get(QW_CELL); sg.a = pk.getf(QW_A); sg.b = pk.getf(QW_B);
-                const float* my = s_seg + lane * kSegStride;
-                write_hit(out, r, sg, make_float3(my[0], my[1], my[2]), make_float3(my[4], my[5], my[6]), z, nq, n_mat,
+                const float* my = s_seg + idx * kSegStride;
+                if (lead) write_hit(out, r, sg, make_float3(my[0], my[1], my[2]), make_float3(my[4], my[5], my[6]), z, nq, n_mat,
                           np.dist_head, R.tmax ? R.tmax[r] : INFINITY, P);
                 r = -1;
-                ++n_done;
-                hitnow = true;
+                if (lead) ++n_done;
+                hitnow = lead;
             }
             has = false;
         }
@@ -293,15 +299,16 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
 
         // ---- give every lane a segment, taking new rays as old ones finish or miss
         for (;;) {
-            const bool need = cur < 8 && r < 0 && lane < RPW;
-            const uint64_t m = ballot(need);
+            const bool need = cur < 8 && r < 0;
+            const uint64_t m = ballot(need && lead);
             if (m) {
                 const int leader = __ffsll((unsigned long long)m) - 1;
                 unsigned long long base = 0;
                 if (lane == leader) base = atomicAdd((unsigned long long*)&counters[rid], (unsigned long long)popc64(m));
                 base = __shfl(base, leader);
                 if (need) {
-                    r = lo + (int64_t)base + rank_below(m);
+                    // rank of the ray's first lane among those that take one
+                    r = lo + (int64_t)base + popc64(m & ((1ull << (lane / SUB * SUB)) - 1ull));
                     if (r >= hi) {
                         r = -1;
                     } else {
@@ -333,18 +340,20 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
             }
             const bool search = r >= 0 && !has;
             if (!ballot(search)) {
-                if (cur < 8 && ballot(r < 0 && lane < RPW)) continue;   // lanes still to fill
+                if (cur < 8 && ballot(r < 0)) continue;   // lanes still to fill
                 break;
             }
             bool missed = false;
             if (search) {
-                has = next_segment(P, G.V, G.bin_start, G.bin_cells, G.N, ray, tv, sg, &bad);
+                has = next_segment<SUB>(P, G.V, G.bin_start, G.bin_cells, G.N, ray, tv, sg, &bad);
                 if (has && R.tmax && sg.a >= R.tmax[r]) has = false;     // occlusion bound reached
                 if (!has) {
-                    write_miss(out, r, nq, last_z0);
+                    if (lead) {
+                        write_miss(out, r, nq, last_z0);
+                        ++n_done;
+                    }
                     r = -1;
-                    ++n_done;
-                    missed = true;
+                    missed = lead;
                 }
             }
             if (pose_times) note_finished(stats, R.off, R.n_poses, missed, pose);
@@ -357,7 +366,7 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
             x0 = deform_inv(P, ray_at(ray, sg.a));
             x1 = deform_inv(P, ray_at(ray, sg.b));
         }
-        float* my = s_seg + lane * kSegStride;
+        float* my = s_seg + idx * kSegStride;
         my[0] = x0.x; my[1] = x0.y; my[2] = x0.z;
         my[4] = x1.x; my[5] = x1.y; my[6] = x1.z;
         pk.put(QW_R_LO, (int32_t)(uint32_t)(uint64_t)r); pk.put(QW_R_HI, (int32_t)(uint32_t)((uint64_t)r >> 32));

@@ -20,6 +20,11 @@
 // Woo).  Within the current bin the next segment is the interval with the smallest
 // (entry t, voxel id) after the last one returned whose entry t falls in the bin's t-range;
 // a voxel listed in several bins is therefore taken in exactly one of them.
+// The walk is one flat loop in which each ray either tests its next voxels or moves to its next
+// bin: rays of a wave meet voxels at different bins, and nested loops make every ray wait for
+// the longest list at every step.  SUB lanes (a power of two) share a ray: they walk the bins together
+// and test SUB voxels of a list at a time, so a long ray's chain of dependent loads is that much
+// shorter; all control flow is the same for the lanes of a ray.
 #pragma once
 #include "nif_device.hpp"
 
@@ -63,13 +68,14 @@ struct CellHit {
     int bad;             // odd or > 4 crossings (degenerate; reported as one interval)
 };
 
+// `cell` as the bin lists hold it (pack_cell).
 __device__ __forceinline__ CellHit cell_intervals(const float4* __restrict__ V, int N, int cell, const Ray& R) {
-    const int i = cell % N, j = (cell / N) % N, k = cell / (N * N);
-    const int64_t n1 = N + 1;
+    const int n1 = N + 1;
+    const float4* Vc = V + ((cell & 0x3ff) + n1 * (((cell >> 10) & 0x3ff) + n1 * (cell >> 20)));
     float3 v[8];
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
-        float4 q = V[(int64_t)(i + (m & 1)) + n1 * ((j + ((m >> 1) & 1)) + n1 * (k + (m >> 2)))];
+        float4 q = Vc[(m & 1) + n1 * (((m >> 1) & 1) + n1 * (m >> 2))];
         v[m] = make_float3(q.x, q.y, q.z);
     }
     const float dd = f3dot(R.d, R.d);
@@ -174,56 +180,191 @@ struct Segment {
     int32_t face;
 };
 
-// Next occupied segment after T.last in front-to-back order.  Returns false when the ray
-// has left the grid.  *bad counts degenerate voxel tests.
+// The bin the walk is in: how it leaves it, and its voxel list.
+struct BinWalk {
+    int32_t ax;          // axis of the face the ray leaves through
+    bool last;           // the ray leaves the grid there
+    float t_hi;          // end of the bin's t-range (infinite for the last bin)
+    int32_t s0, s1;      // its list
+};
+
+__device__ __forceinline__ void open_bin(const PoseDev& P, const int32_t* __restrict__ bin_start, const Trav& T, BinWalk& B) {
+    B.ax = 0;
+    float th = T.tmx;
+    if (T.tmy < th) { B.ax = 1; th = T.tmy; }
+    if (T.tmz < th) { B.ax = 2; th = T.tmz; }
+    if (B.ax == 0) B.last = T.ix + T.sx == T.ex;
+    else if (B.ax == 1) B.last = T.iy + T.sy == T.ey;
+    else B.last = T.iz + T.sz == T.ez;
+    B.last = B.last || !(th < INFINITY);
+    B.t_hi = B.last ? INFINITY : th;
+    const int64_t bin = (int64_t)T.ix + (int64_t)P.nb[0] * (T.iy + (int64_t)P.nb[1] * T.iz);
+    B.s0 = bin_start[P.bin_off + bin];
+    B.s1 = bin_start[P.bin_off + bin + 1];
+}
+
+__device__ __forceinline__ void leave_bin(const BinWalk& B, Trav& T) {
+    T.t_lo = B.t_hi;
+    if (B.ax == 0) { T.ix += T.sx; T.tmx += T.tdx; }
+    else if (B.ax == 1) { T.iy += T.sy; T.tmy += T.tdy; }
+    else { T.iz += T.sz; T.tmz += T.tdz; }
+}
+
+// Empty bins a ray may pass in one step of the flat loop (a step over a bin costs a list lookup,
+// a voxel test eight vertices and about 300 operations).
+constexpr int kBinsPerStep = 3;
+
+// Next occupied segment after T.last in front-to-back order (the same result in the SUB lanes of
+// the ray).  Returns false when the ray has left the grid.  *bad counts degenerate voxel tests.
+template <int SUB>
 __device__ __forceinline__ bool next_segment(const PoseDev& P, const float4* __restrict__ V,
                                              const int32_t* __restrict__ bin_start,
                                              const int32_t* __restrict__ bin_cells, int N, const Ray& R,
                                              Trav& T, Segment& out, int* bad) {
-    while (T.active) {
-        // which face of the current bin the ray leaves through
-        int ax = 0;
-        float th = T.tmx;
-        if (T.tmy < th) { ax = 1; th = T.tmy; }
-        if (T.tmz < th) { ax = 2; th = T.tmz; }
-        bool last;
-        if (ax == 0) last = T.ix + T.sx == T.ex;
-        else if (ax == 1) last = T.iy + T.sy == T.ey;
-        else last = T.iz + T.sz == T.ez;
-        last = last || !(th < INFINITY);
-        const float t_hi = last ? INFINITY : th;
-        const int64_t bin = (int64_t)T.ix + (int64_t)P.nb[0] * (T.iy + (int64_t)P.nb[1] * T.iz);
-        const int32_t s0 = bin_start[P.bin_off + bin], s1 = bin_start[P.bin_off + bin + 1];
-        float best_a = INFINITY, best_b = 0.f;
-        int32_t best_c = 0x7fffffff, best_f = -1;
-        for (int32_t e = s0; e < s1; ++e) {
-            const int32_t c = bin_cells[P.ref_off + e];
-            CellHit h = cell_intervals(V + P.vert_off, N, c, R);
-            *bad += h.bad;
+    if (!T.active) return false;
+    const int sub = SUB > 1 ? lane_id() & (SUB - 1) : 0;
+    float best_a = INFINITY, best_b = 0.f;
+    int32_t best_c = 0x7fffffff, best_f = -1;
+    BinWalk B;
+    open_bin(P, bin_start, T, B);
+    int32_t e = B.s0;
+    for (;;) {
+        if (e < B.s1) {
+            if (SUB == 1 || e + sub < B.s1) {
+                const int32_t c = bin_cells[P.ref_off + e + sub];
+                CellHit h = cell_intervals(V + P.vert_off, N, c, R);
+                *bad += h.bad;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                if (q >= h.n) break;
-                const float a = fmaxf(q == 0 ? h.a0 : h.a1, 0.f);
-                const float b = q == 0 ? h.b0 : h.b1;
-                if (!(b > a) || a < T.t_lo || !(a < t_hi)) continue;
-                const bool after = a > T.last_a || (a == T.last_a && c > T.last_cell);
-                const bool better = a < best_a || (a == best_a && c < best_c);
-                if (after && better) { best_a = a; best_b = b; best_c = c; best_f = q == 0 ? h.entry_face : -1; }
+                for (int q = 0; q < 2; ++q) {
+                    if (q >= h.n) break;
+                    const float a = fmaxf(q == 0 ? h.a0 : h.a1, 0.f);
+                    const float b = q == 0 ? h.b0 : h.b1;
+                    if (!(b > a) || a < T.t_lo || !(a < B.t_hi)) continue;
+                    const bool after = a > T.last_a || (a == T.last_a && c > T.last_cell);
+                    const bool better = a < best_a || (a == best_a && c < best_c);
+                    if (after && better) { best_a = a; best_b = b; best_c = c; best_f = q == 0 ? h.entry_face : -1; }
+                }
+            }
+            e += SUB;
+            if (e < B.s1) continue;
+            if constexpr (SUB > 1) {                    // the bin's best over the ray's lanes
+#pragma unroll
+                for (int o = 1; o < SUB; o <<= 1) {
+                    const float a = __shfl_xor(best_a, o), b = __shfl_xor(best_b, o);
+                    const int32_t c = __shfl_xor(best_c, o), f = __shfl_xor(best_f, o);
+                    if (a < best_a || (a == best_a && c < best_c)) { best_a = a; best_b = b; best_c = c; best_f = f; }
+                }
+            }
+            if (best_a < INFINITY) {
+                T.last_a = best_a;
+                T.last_cell = best_c;
+                out.cell = cell_id(best_c, N); out.a = best_a; out.b = best_b; out.face = best_f;
+                return true;
             }
         }
-        if (best_a < INFINITY) {
-            T.last_a = best_a;
-            T.last_cell = best_c;
-            out.cell = best_c; out.a = best_a; out.b = best_b; out.face = best_f;
-            return true;
+        for (int k = 0; k < kBinsPerStep; ++k) {
+            if (B.last) { T.active = 0; return false; }
+            leave_bin(B, T);
+            open_bin(P, bin_start, T, B);
+            e = B.s0;
+            if (e < B.s1) break;
         }
-        if (last) { T.active = 0; return false; }
-        T.t_lo = t_hi;
-        if (ax == 0) { T.ix += T.sx; T.tmx += T.tdx; }
-        else if (ax == 1) { T.iy += T.sy; T.tmy += T.tdy; }
-        else { T.iz += T.sz; T.tmz += T.tdz; }
     }
-    return false;
+}
+
+// Every occupied segment of the ray in order: emit(cell, a, b) for each, by one of its SUB lanes.
+// The walk of repeated next_segment calls, but a bin's segments are found in one pass over its
+// list (each lane keeps its first kTraceSlots; a bin with more is gone over again from the last
+// one emitted).
+constexpr int kTraceSlots = 4;
+template <int SUB, class Emit>
+__device__ __forceinline__ void all_segments(const PoseDev& P, const float4* __restrict__ V,
+                                             const int32_t* __restrict__ bin_start,
+                                             const int32_t* __restrict__ bin_cells, int N, const Ray& R, Trav& T, Emit emit) {
+    if (!T.active) return;
+    const int sub = SUB > 1 ? lane_id() & (SUB - 1) : 0;
+    float ca[kTraceSlots], cb[kTraceSlots];
+    int32_t cc[kTraceSlots];
+    int found = 0;
+#pragma unroll
+    for (int k = 0; k < kTraceSlots; ++k) { ca[k] = INFINITY; cb[k] = 0.f; cc[k] = 0x7fffffff; }
+    BinWalk B;
+    open_bin(P, bin_start, T, B);
+    int32_t e = B.s0;
+    for (;;) {
+        if (e < B.s1) {
+            if (SUB == 1 || e + sub < B.s1) {
+                const int32_t c = bin_cells[P.ref_off + e + sub];
+                CellHit h = cell_intervals(V + P.vert_off, N, c, R);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (q >= h.n) break;
+                    float a = fmaxf(q == 0 ? h.a0 : h.a1, 0.f), b = q == 0 ? h.b0 : h.b1;
+                    if (!(b > a) || a < T.t_lo || !(a < B.t_hi)) continue;
+                    if (!(a > T.last_a || (a == T.last_a && c > T.last_cell))) continue;
+                    ++found;
+                    int32_t ci = c;
+#pragma unroll
+                    for (int k = 0; k < kTraceSlots; ++k) {         // insertion into the sorted slots
+                        const bool first = a < ca[k] || (a == ca[k] && ci < cc[k]);
+                        const float ta = first ? ca[k] : a, tb = first ? cb[k] : b;
+                        const int32_t tc = first ? cc[k] : ci;
+                        if (first) { ca[k] = a; cb[k] = b; cc[k] = ci; }
+                        a = ta; b = tb; ci = tc;
+                    }
+                }
+            }
+            e += SUB;
+            if (e < B.s1) continue;
+            // Emit in order while no lane has dropped a segment that could come first: a lane that
+            // found more than its slots may be followed only up to its last slot.
+            const bool spilled = found > kTraceSlots;
+            bool any = spilled;
+            float lim_a = spilled ? ca[kTraceSlots - 1] : INFINITY;
+            int32_t lim_c = spilled ? cc[kTraceSlots - 1] : 0x7fffffff;
+#pragma unroll
+            for (int o = 1; o < SUB; o <<= 1) {
+                const float a = __shfl_xor(lim_a, o);
+                const int32_t c = __shfl_xor(lim_c, o);
+                any = any || __shfl_xor((int)any, o);
+                if (a < lim_a || (a == lim_a && c < lim_c)) { lim_a = a; lim_c = c; }
+            }
+            for (;;) {
+                float a = ca[0], b = cb[0];
+                int32_t c = cc[0];
+#pragma unroll
+                for (int o = 1; o < SUB; o <<= 1) {
+                    const float a2 = __shfl_xor(a, o), b2 = __shfl_xor(b, o);
+                    const int32_t c2 = __shfl_xor(c, o);
+                    if (a2 < a || (a2 == a && c2 < c)) { a = a2; b = b2; c = c2; }
+                }
+                if (!(a < INFINITY) || a > lim_a || (a == lim_a && c > lim_c)) break;
+                T.last_a = a;
+                T.last_cell = c;
+                emit(cell_id(c, N), a, b);
+                if (cc[0] == c && ca[0] == a) {                      // its owner moves on
+#pragma unroll
+                    for (int k = 0; k + 1 < kTraceSlots; ++k) { ca[k] = ca[k + 1]; cb[k] = cb[k + 1]; cc[k] = cc[k + 1]; }
+                    ca[kTraceSlots - 1] = INFINITY;
+                    cc[kTraceSlots - 1] = 0x7fffffff;
+                }
+            }
+            found = 0;
+            if (any) {                                               // over the list again, from the last one emitted
+#pragma unroll
+                for (int k = 0; k < kTraceSlots; ++k) { ca[k] = INFINITY; cc[k] = 0x7fffffff; }
+                e = B.s0;
+                continue;
+            }
+        }
+        for (int k = 0; k < kBinsPerStep; ++k) {
+            if (B.last) { T.active = 0; return; }
+            leave_bin(B, T);
+            open_bin(P, bin_start, T, B);
+            e = B.s0;
+            if (e < B.s1) break;
+        }
+    }
 }
 
 // Pose of ray r (rays are grouped by pose; offsets[0] = 0, offsets[n_poses] = n_rays).
