@@ -99,7 +99,10 @@ __device__ inline void cell_box(const float4* __restrict__ V, int32_t N, int32_t
     for (int a = 0; a < 3; ++a) { lo[a] -= kBinPad; hi[a] += kBinPad; }
 }
 
-// bbox[p][6] as ordered ints: min x,y,z then max x,y,z
+// bbox[p][6] as ordered ints: min x,y,z then max x,y,z.  Few blocks per pose, one set of atomics
+// each: the six addresses of a pose take one atomic at a time (one set per wave over 8 poses of the
+// 128^3 scene: 214 us).
+constexpr int kBoxBlocks = 48;
 __global__ void k_pose_bbox(const PoseDev* __restrict__ poses, const float4* __restrict__ V, int32_t N,
                             const int32_t* __restrict__ list, int32_t n_occ, int32_t* __restrict__ bbox) {
     const int p = blockIdx.y;
@@ -116,11 +119,17 @@ __global__ void k_pose_bbox(const PoseDev* __restrict__ poses, const float4* __r
             hi[c] = fmaxf(hi[c], __shfl_xor(hi[c], off));
         }
     }
-    if (lane_id() == 0) {
-        for (int c = 0; c < 3; ++c) {
-            atomicMin(&bbox[6 * p + c], f2ord(lo[c]));
-            atomicMax(&bbox[6 * p + 3 + c], f2ord(hi[c]));
-        }
+    __shared__ float red[4][6];
+    const int w = threadIdx.x >> 6;
+    if (lane_id() == 0)
+        for (int c = 0; c < 3; ++c) { red[w][c] = lo[c]; red[w][3 + c] = hi[c]; }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        const int c = (int)threadIdx.x;
+        float v = red[0][c];
+        for (int k = 1; k < 4; ++k) v = c < 3 ? fminf(v, red[k][c]) : fmaxf(v, red[k][c]);
+        if (c < 3) atomicMin(&bbox[6 * p + c], f2ord(v));
+        else atomicMax(&bbox[6 * p + c], f2ord(v));
     }
 }
 
@@ -150,31 +159,66 @@ __global__ void k_bin_count(const PoseDev* __restrict__ poses, const float4* __r
                 atomicAdd(&cnt[x + P.nb[0] * (y + P.nb[1] * z)], 1);
 }
 
-// Exclusive scan of counts[0..n) into start[0..n] by one workgroup of 1024 threads.
-__global__ void __launch_bounds__(1024) k_scan(const PoseDev* __restrict__ poses, const int32_t* __restrict__ counts,
-                                               int32_t* __restrict__ start, int32_t* __restrict__ totals) {
-    const int p = blockIdx.x;
+// Exclusive scan of a pose's counts[0..n) into start[0..n] in chunks of kScanChunk bins: sums of the
+// chunks, then every chunk's own scan from the sums before it (one workgroup per pose walked all
+// bins alone: 505 us at 64^3 bins).
+constexpr int kScanChunk = 4096;
+
+__device__ inline int64_t pose_bins(const PoseDev& P) { return (int64_t)P.nb[0] * P.nb[1] * P.nb[2]; }
+
+// Block (x, p): sum of chunk x of pose p.
+__global__ void __launch_bounds__(256) k_chunk_sums(const PoseDev* __restrict__ poses, const int32_t* __restrict__ counts,
+                                                    int32_t* __restrict__ sums, int max_chunks) {
+    const PoseDev P = poses[blockIdx.y];
+    const int64_t n = pose_bins(P), a = (int64_t)blockIdx.x * kScanChunk, b = min(n, a + kScanChunk);
+    if (a >= n) return;
+    const int32_t* c = counts + P.bin_off;
+    int32_t sum = 0;
+    for (int64_t i = a + threadIdx.x; i < b; i += 256) sum += c[i];
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    __shared__ int32_t red[4];
+    if (lane_id() == 0) red[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) sums[(int64_t)blockIdx.y * max_chunks + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+
+__global__ void __launch_bounds__(256) k_scan(const PoseDev* __restrict__ poses, const int32_t* __restrict__ counts,
+                                              const int32_t* __restrict__ sums, int max_chunks, int32_t* __restrict__ start,
+                                              int32_t* __restrict__ totals) {
+    const int p = blockIdx.y, T = threadIdx.x;
     const PoseDev P = poses[p];
-    const int64_t n = (int64_t)P.nb[0] * P.nb[1] * P.nb[2];
+    const int64_t n = pose_bins(P), a = (int64_t)blockIdx.x * kScanChunk;
+    if (a >= n) return;
     const int32_t* c = counts + P.bin_off;
     int32_t* s = start + P.bin_off;
-    __shared__ int32_t part[1024];
-    const int T = blockDim.x;
-    const int64_t per = (n + T - 1) / T;
-    const int64_t a = min(n, (int64_t)threadIdx.x * per), b = min(n, a + per);
-    int32_t sum = 0;
-    for (int64_t i = a; i < b; ++i) sum += c[i];
-    part[threadIdx.x] = sum;
+    __shared__ int32_t part[256], before[256];
+    int32_t pre = 0;                                   // the chunks before this one
+    for (int k = T; k < (int)blockIdx.x; k += 256) pre += sums[(int64_t)p * max_chunks + k];
+    constexpr int PER = kScanChunk / 256;
+    const int64_t i0 = a + (int64_t)T * PER;
+    int32_t v[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        v[k] = i0 + k < n ? c[i0 + k] : 0;
+        sum += v[k];
+    }
+    part[T] = sum;
+    before[T] = pre;
     __syncthreads();
-    for (int off = 1; off < T; off <<= 1) {
-        int32_t v = threadIdx.x >= off ? part[threadIdx.x - off] : 0;
+    for (int off = 1; off < 256; off <<= 1) {
+        const int32_t x = T >= off ? part[T - off] : 0, y = T >= off ? before[T - off] : 0;
         __syncthreads();
-        part[threadIdx.x] += v;
+        part[T] += x;
+        before[T] += y;
         __syncthreads();
     }
-    int32_t run = part[threadIdx.x] - sum;   // exclusive prefix of this thread's range
-    for (int64_t i = a; i < b; ++i) { s[i] = run; run += c[i]; }
-    if (threadIdx.x == T - 1) { s[n] = part[T - 1]; totals[p] = part[T - 1]; }
+    int32_t run = before[255] + part[T] - sum;         // exclusive prefix of this thread's bins
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (i0 + k < n) s[i0 + k] = run;
+        run += v[k];
+    }
+    if (a + kScanChunk >= n && T == 255) { s[n] = run; totals[p] = run; }
 }
 
 // Per-pose offsets into the shared reference list (one thread).  A pose whose references do
@@ -243,32 +287,59 @@ __global__ void k_bin_fill(const PoseDev* __restrict__ poses, const float4* __re
             }
 }
 
-// Sort each bin's list by packed voxel, that is by voxel id (insertion sort; lists are short) so the build is
-// deterministic.
-__global__ void k_bin_sort(const PoseDev* __restrict__ poses, const int32_t* __restrict__ start,
-                           int32_t* __restrict__ cells) {
+__device__ inline void sort_list(int32_t* __restrict__ l, int32_t n) {
+    for (int32_t i = 1; i < n; ++i) {
+        const int32_t v = l[i];
+        int32_t j = i;
+        for (; j > 0 && l[j - 1] > v; --j) l[j] = l[j - 1];
+        l[j] = v;
+    }
+}
+
+// Sort each bin's list by packed voxel, that is by voxel id, so that the build is deterministic
+// (insertion sort; lists are short).  A block takes 128 neighbouring bins, whose lists are one range
+// of the references: it is sorted in LDS where it fits, so that the chains of a sort are LDS reads.
+constexpr int kSortBins = 128, kSortRefs = 6144;
+__global__ void __launch_bounds__(kSortBins) k_bin_sort(const PoseDev* __restrict__ poses, const int32_t* __restrict__ start,
+                                                        int32_t* __restrict__ cells) {
+    __shared__ int32_t s_ref[kSortRefs];
     const int p = blockIdx.y;
     const PoseDev P = poses[p];
-    int64_t nb = (int64_t)P.nb[0] * P.nb[1] * P.nb[2];
-    int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb || P.empty) return;
+    const int64_t nb = pose_bins(P);
+    const int64_t b0 = (int64_t)blockIdx.x * kSortBins, b = b0 + threadIdx.x;
+    if (b0 >= nb || P.empty) return;
     const int32_t* st = start + P.bin_off;
     int32_t* c = cells + P.ref_off;
-    for (int32_t i = st[b] + 1; i < st[b + 1]; ++i) {
-        int32_t v = c[i], j = i - 1;
-        while (j >= st[b] && c[j] > v) { c[j + 1] = c[j]; --j; }
-        c[j + 1] = v;
+    const int32_t r0 = st[b0], r1 = st[min(nb, b0 + kSortBins)];
+    const bool staged = r1 - r0 <= kSortRefs;
+    if (!staged) {
+        if (b < nb) sort_list(c + st[b], st[b + 1] - st[b]);
+        return;
     }
+    const int32_t m = r1 - r0;
+    for (int32_t i = (int32_t)threadIdx.x; i < m; i += kSortBins) s_ref[i] = c[r0 + i];
+    __syncthreads();
+    if (b < nb) {
+        const int32_t s0 = st[b] - r0, s1 = st[b + 1] - r0;
+        for (int32_t i = s0 + 1; i < s1; ++i) {
+            const int32_t v = s_ref[i];
+            int32_t j = i;
+            for (; j > s0 && s_ref[j - 1] > v; --j) s_ref[j] = s_ref[j - 1];
+            s_ref[j] = v;
+        }
+    }
+    __syncthreads();
+    for (int32_t i = (int32_t)threadIdx.x; i < m; i += kSortBins) c[r0 + i] = s_ref[i];
 }
 
 // ------------------------------------------------------------------ host orchestration
 
 void grid_free(nif_grid* g) {
-    void* ps[] = {g->poses, g->verts, g->bin_start, g->bin_cells, g->list, g->counts, g->scratch, g->order_pre};
+    void* ps[] = {g->poses, g->verts, g->bin_start, g->bin_cells, g->list, g->counts, g->scratch, g->order_pre, g->scan_sums};
     for (void* p : ps)
         if (p) (void)hipFree(p);
     g->poses = nullptr; g->verts = nullptr; g->bin_start = nullptr; g->bin_cells = nullptr;
-    g->list = nullptr; g->counts = nullptr; g->scratch = nullptr; g->order_pre = nullptr;
+    g->list = nullptr; g->counts = nullptr; g->scratch = nullptr; g->order_pre = nullptr; g->scan_sums = nullptr;
 }
 
 // scratch layout: bbox [6 P] | totals [P] | overflow [1] | n_occ [1]
@@ -276,6 +347,8 @@ static int32_t* sc_bbox(nif_grid* g) { return g->scratch; }
 static int32_t* sc_totals(nif_grid* g) { return g->scratch + 6 * g->n_poses; }
 static int32_t* sc_overflow(nif_grid* g) { return g->scratch + 7 * g->n_poses; }
 static int32_t* sc_nocc(nif_grid* g) { return g->scratch + 7 * g->n_poses + 1; }
+
+static int scan_chunks(int64_t max_bins) { return (int)((max_bins + kScanChunk - 1) / kScanChunk); }
 
 // Vertices, boxes, bin sizes, counts, scan and per-pose offsets; fills the reference lists
 // when `fill`.  Device work only: no allocation, no synchronisation.
@@ -286,7 +359,7 @@ static int grid_rebin(nif_grid* g, bool fill, hipStream_t st) {
     hipLaunchKernelGGL(k_vertices, dim3((unsigned)((nv + 255) / 256), P), dim3(256), 0, st, g->poses, N, g->verts);
     hipLaunchKernelGGL(k_bbox_init, dim3((6 * P + 255) / 256), dim3(256), 0, st, sc_bbox(g), P);
     if (n_occ > 0) {
-        unsigned nblk = (unsigned)std::min<int64_t>((n_occ + 255) / 256, 1024);
+        unsigned nblk = (unsigned)std::min<int64_t>((n_occ + 255) / 256, kBoxBlocks);
         hipLaunchKernelGGL(k_pose_bbox, dim3(nblk, P), dim3(256), 0, st, g->poses, g->verts, N, g->list, n_occ, sc_bbox(g));
     }
     hipLaunchKernelGGL(k_pose_bins, dim3((P + 63) / 64), dim3(64), 0, st, g->poses, P, sc_bbox(g), n_occ);
@@ -294,14 +367,17 @@ static int grid_rebin(nif_grid* g, bool fill, hipStream_t st) {
     const unsigned occ_blk = (unsigned)std::max<int64_t>(1, (n_occ + 255) / 256);
     if (n_occ > 0)
         hipLaunchKernelGGL(k_bin_count, dim3(occ_blk, P), dim3(256), 0, st, g->poses, g->verts, N, g->list, n_occ, g->counts);
-    hipLaunchKernelGGL(k_scan, dim3(P), dim3(1024), 0, st, g->poses, g->counts, g->bin_start, sc_totals(g));
+    const int chunks = scan_chunks(g->max_bins);
+    hipLaunchKernelGGL(k_chunk_sums, dim3(chunks, P), dim3(256), 0, st, g->poses, g->counts, g->scan_sums, chunks);
+    hipLaunchKernelGGL(k_scan, dim3(chunks, P), dim3(256), 0, st, g->poses, g->counts, g->scan_sums, chunks, g->bin_start,
+                       sc_totals(g));
     hipLaunchKernelGGL(k_ref_offsets, dim3(1), dim3(64), 0, st, g->poses, P, sc_totals(g), fill ? g->ref_capacity : (int64_t)0,
                        sc_overflow(g));
     if (fill && n_occ > 0) {
         hipLaunchKernelGGL(k_fill_i32, dim3(1024), dim3(256), 0, st, g->counts, g->bin_total, 0);
         hipLaunchKernelGGL(k_bin_fill, dim3(occ_blk, P), dim3(256), 0, st, g->poses, g->verts, N, g->list, n_occ,
                            g->bin_start, g->counts, g->bin_cells);
-        hipLaunchKernelGGL(k_bin_sort, dim3((unsigned)((g->max_bins + 255) / 256), P), dim3(256), 0, st, g->poses,
+        hipLaunchKernelGGL(k_bin_sort, dim3((unsigned)((g->max_bins + kSortBins - 1) / kSortBins), P), dim3(kSortBins), 0, st, g->poses,
                            g->bin_start, g->bin_cells);
     }
     return check_hip(hipGetLastError(), "grid rebin launch");
@@ -352,7 +428,7 @@ int grid_build(nif_grid* g, const uint8_t* occ, int32_t N, const nif_pose* poses
     hipLaunchKernelGGL(k_vertices, dim3((unsigned)((nv + 255) / 256), n_poses), dim3(256), 0, st, g->poses, N, g->verts);
     hipLaunchKernelGGL(k_bbox_init, dim3((6 * n_poses + 255) / 256), dim3(256), 0, st, sc_bbox(g), n_poses);
     if (n_occ > 0) {
-        unsigned nblk = (unsigned)std::min<int64_t>((n_occ + 255) / 256, 1024);
+        unsigned nblk = (unsigned)std::min<int64_t>((n_occ + 255) / 256, kBoxBlocks);
         hipLaunchKernelGGL(k_pose_bbox, dim3(nblk, n_poses), dim3(256), 0, st, g->poses, g->verts, N, g->list, n_occ, sc_bbox(g));
     }
     NIF_TRY(hipGetLastError(), "bbox");
@@ -376,6 +452,7 @@ int grid_build(nif_grid* g, const uint8_t* occ, int32_t N, const nif_pose* poses
     g->max_bins = max_bins;
     NIF_TRY(hipMalloc(&g->bin_start, sizeof(int32_t) * bin_total), "hipMalloc bin_start");
     NIF_TRY(hipMalloc(&g->counts, sizeof(int32_t) * bin_total), "hipMalloc bin counts");
+    NIF_TRY(hipMalloc(&g->scan_sums, sizeof(int32_t) * (size_t)scan_chunks(max_bins) * n_poses), "hipMalloc scan sums");
     NIF_TRY(hipMemcpyAsync(g->poses, P.data(), sizeof(PoseDev) * n_poses, hipMemcpyHostToDevice, st), "copy poses");
     // count pass, then size the reference lists with headroom for later re-poses
     g->ref_capacity = 0;
