@@ -1455,13 +1455,16 @@ __global__ void __launch_bounds__(kTgBlock) k_tg_fill(EncBwdParams P, const int3
 
 // Levels whose table (or dense grid) is small enough to be summed in LDS as it is: no records.  A
 // level of up to kDirectWindows windows of kDirectWindow entries (64-bit fixed-point sums of both
-// features) is taken.  A block goes through its share of the chunk's samples for one window of one
+// features) can be; a model is summed this way if all its levels can be (a few levels of a model with
+// records leave the chip idle: 866 us against 440 for two such levels of the 128^3 scene).  Backward
+// of 2^17 points with 2^14, 2^15 and 2^16 entries a table, records against this: 2.29 and 1.57,
+// 2.17 and 1.97, 2.21 and 2.97 ms.  A block goes through its share of the chunk's samples for one window of one
 // level, skipping cells outside, and adds its sums to the level's in memory (64-bit integers: exact,
 // in any order).  The levels get equal numbers of blocks, whatever their windows (the atomics are
 // the same, a further window costs another walk over the positions), and the lanes of a wave take
 // samples far apart: neighbours in a spatially ordered batch share cells, and LDS atomics on one
 // address go one after the other.
-constexpr int kDirectWindow = 9600, kDirectWindows = 8;
+constexpr int kDirectWindow = 9600, kDirectWindows = 4;
 struct DirectPlan {
     int32_t n;                        // levels
     uint8_t lev[16], win[16];         // level, its windows
