@@ -7,10 +7,11 @@
 // inside; torus, union of spheres, Gaussian blobs, parameters as for nif_voxelize).
 //
 // The first point of the chord with f <= 0: t = 0 if f(x0) <= 0; for spheres the entering
-// root of each sphere's quadratic (the smallest in [0, len]); otherwise 256 uniform sign steps
-// over [0, len] and bisection of the first bracket down to 1e-13.  Normal = grad f / |grad f|
+// root of each sphere's quadratic (the smallest in [0, len]); otherwise the first of 256 uniform
+// sign steps over [0, len] that is inside, and the root of its bracket to 1e-13.  Normal = grad f / |grad f|
 // at that point.  Everything in FP64, so the sign decisions are taken in the same precision as
 // the reference implementation.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <vector>
@@ -116,10 +117,89 @@ __device__ void scene_attributes(int kind, const double* __restrict__ sp, const 
     *mat = (int)sp[1 + kSceneStride * arg + 7];
 }
 
+// Gradient and attributes of the blob scene at p, from one set of exponentials.
+__device__ void blob_surface(const double* __restrict__ sp, const double p[3], double g[3], double a[3], int* mat) {
+    const int n = (int)sp[0];
+    double wsum = 0.0, wbest = -1.0;
+    int arg = 0;
+    for (int c = 0; c < 3; ++c) { g[c] = 0.0; a[c] = 0.0; }
+    for (int i = 0; i < n; ++i) {
+        const double* b = sp + 1 + kSceneStride * i;
+        const double dx = p[0] - b[0], dy = p[1] - b[1], dz = p[2] - b[2];
+        const double s2 = b[3] * b[3];
+        const double e = exp(-(dx * dx + dy * dy + dz * dz) / (2.0 * s2));
+        g[0] += e * dx / s2; g[1] += e * dy / s2; g[2] += e * dz / s2;
+        wsum += e;
+        a[0] += e * b[4]; a[1] += e * b[5]; a[2] += e * b[6];
+        if (e > wbest) { wbest = e; arg = i; }
+    }
+    if (wsum > 0.0) { a[0] /= wsum; a[1] /= wsum; a[2] /= wsum; }
+    *mat = (int)sp[1 + kSceneStride * arg + 7];
+}
+
+// scene_value of the blobs, and the slope along u of their sum G = 0.5 - f.
+__device__ double blob_value(const double* __restrict__ sp, const double p[3], const double u[3], double* slope) {
+    const int n = (int)sp[0];
+    double g = 0.0, d = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const double* b = sp + 1 + kSceneStride * i;
+        const double dx = p[0] - b[0], dy = p[1] - b[1], dz = p[2] - b[2];
+        const double e = exp(-(dx * dx + dy * dy + dz * dz) / (2.0 * b[3] * b[3]));
+        g += e;
+        d -= e / (b[3] * b[3]) * (dx * u[0] + dy * u[1] + dz * u[2]);
+    }
+    *slope = d;
+    return 0.5 - g;
+}
+
+// Bounds over the chord for the blob sum G along it.  A blob's term exp(-q / 2 s^2), at distance r
+// along the chord from its nearest point to the centre, has the second derivative
+// term (r^2 / s^2 - 1) / s^2, which lies in [-1 / s^2, 2 exp(-3/2) / s^2].
+struct BlobBounds {
+    double up;       // G'' <= up
+    double curve;    // |G''| <= curve
+    double margin;   // on G: rounding of the points and of the sum
+};
+
+__device__ BlobBounds blob_bounds(const double* __restrict__ sp, const double x0[3], const double u[3], double len) {
+    const int n = (int)sp[0];
+    BlobBounds B = {0.0, 0.0, 0.0};
+    double steep = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const double* b = sp + 1 + kSceneStride * i;
+        const double w[3] = {x0[0] - b[0], x0[1] - b[1], x0[2] - b[2]};
+        const double at = w[0] * u[0] + w[1] * u[1] + w[2] * u[2];
+        const double t = fmin(fmax(-at, 0.0), len);
+        const double d[3] = {w[0] + t * u[0], w[1] + t * u[1], w[2] + t * u[2]};
+        const double is2 = 1.0 / (b[3] * b[3]);
+        const double e = exp(-0.5 * (d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) * is2);   // its largest on the chord
+        const double far = fmax(fabs(at), fabs(at + len));
+        const double k = far * far * is2 - 1.0;
+        B.up += fmin(e * fmax(k, 0.0), 0.4463) * is2;
+        B.curve += fmin(e * fmax(k, 1.0), 1.0) * is2;
+        steep += 0.61 * sqrt(is2);
+    }
+    B.up *= 1.0 + 1e-6;
+    B.curve *= 1.0 + 1e-6;
+    B.margin = 1e-9 + 1e-15 * steep * (fabs(x0[0]) + fabs(x0[1]) + fabs(x0[2]) + 2.0 * len);
+    return B;
+}
+
 // First parameter tau in [0, len] of x0 + tau u with f <= 0.
+//
+// The first of the 256 steps that is inside is found without evaluating every one: from a point
+// outside, f keeps its sign over a distance that the point itself gives.  Torus and marched spheres:
+// the distance to the surface, which changes by at most the way gone.  Blobs: where the sum's tangent
+// plus its largest curvature reaches 1/2 (a Newton step that cannot overshoot).  Steps within that
+// distance, less a margin for rounding, are passed over; wherever the bound says nothing (also NaN)
+// the next step is evaluated.  In the bracket, if the slope cannot change sign the blobs' root is
+// taken by Newton's method, else by bisection.  FP64 exponentials bound the blobs (32 per
+// evaluation): 2^18 segments of the 128^3 scene took 6.6 ms with every step and bisection.
 __device__ bool chord_first_inside(int kind, const double* __restrict__ sp, int force_march, const double x0[3],
                                    const double u[3], double len, double* tau) {
-    if (scene_value(kind, sp, x0) <= 0.0) { *tau = 0.0; return true; }
+    double slope = 0.0;
+    double f = kind == 2 ? blob_value(sp, x0, u, &slope) : scene_value(kind, sp, x0);
+    if (f <= 0.0) { *tau = 0.0; return true; }
     if (len <= 0.0) return false;
     if (kind == 1 && !force_march) {
         const int n = (int)sp[0];
@@ -137,26 +217,54 @@ __device__ bool chord_first_inside(int kind, const double* __restrict__ sp, int 
         return false;
     }
     constexpr int kSteps = 256;
-    double prev = 0.0;
-    for (int s = 1; s <= kSteps; ++s) {
+    BlobBounds B = {0.0, 0.0, 0.0};
+    if (kind == 2) B = blob_bounds(sp, x0, u, len);
+    const double round = 1e-9 + 1e-14 * (fabs(x0[0]) + fabs(x0[1]) + fabs(x0[2]) + 2.0 * len);
+    int s = 0;                                          // f > 0 (or not a number) at step s
+    for (;;) {
+        double clear;                                   // f > 0 up to this distance
+        if (kind == 2) {
+            const double gap = f - B.margin;
+            const double root = sqrt(slope * slope + 2.0 * B.up * gap);
+            clear = slope > 0.0 ? 2.0 * gap / (slope + root) : B.up > 0.0 ? (root - slope) / B.up : INFINITY;
+            clear = gap > 0.0 ? clear * (1.0 - 1e-6) : 0.0;
+        } else if (kind == 1) {
+            clear = f - round;
+        } else {
+            clear = sqrt(f + sp[4] * sp[4]) - fabs(sp[4]) - round;
+        }
+        const double skip = clear * (kSteps * (1.0 - 1e-9)) / len;
+        if (skip >= kSteps - s) return false;
+        s += skip >= 1.0 ? (int)skip + 1 : 1;
+        if (s > kSteps) return false;
         const double t = len * s / kSteps;
         const double p[3] = {x0[0] + t * u[0], x0[1] + t * u[1], x0[2] + t * u[2]};
-        if (scene_value(kind, sp, p) <= 0.0) {
-            double a = prev, b = t;                     // f(a) > 0 >= f(b)
-            while (b - a > 1e-13) {
-                const double m = 0.5 * (a + b);
-                const double q[3] = {x0[0] + m * u[0], x0[1] + m * u[1], x0[2] + m * u[2]};
-                if (scene_value(kind, sp, q) <= 0.0) b = m; else a = m;
-            }
-            *tau = b;
-            return true;
-        }
-        prev = t;
+        f = kind == 2 ? blob_value(sp, p, u, &slope) : scene_value(kind, sp, p);
+        if (f <= 0.0) break;
     }
-    return false;
+    double a = s > 1 ? len * (s - 1) / kSteps : 0.0, b = len * s / kSteps;   // f(a) > 0 >= f(b)
+    if (kind == 2 && slope > B.curve * (b - a)) {
+        double x = b;
+        for (int it = 0; it < 6; ++it) {
+            const double y = fmin(fmax(x + f / slope, a), b);
+            if (fabs(y - x) <= 2e-14) { *tau = y; return true; }
+            x = y;
+            const double q[3] = {x0[0] + x * u[0], x0[1] + x * u[1], x0[2] + x * u[2]};
+            f = blob_value(sp, q, u, &slope);
+            if (f <= 0.0) b = x; else a = x;
+        }
+    }
+    while (b - a > 1e-13) {
+        const double m = 0.5 * (a + b);
+        if (m <= a || m >= b) break;                    // neighbouring numbers
+        const double q[3] = {x0[0] + m * u[0], x0[1] + m * u[1], x0[2] + m * u[2]};
+        if (scene_value(kind, sp, q) <= 0.0) b = m; else a = m;
+    }
+    *tau = b;
+    return true;
 }
 
-__global__ void __launch_bounds__(256) k_label(int kind, const double* __restrict__ sp, int force_march,
+__device__ __forceinline__ void label_segments(int kind, const double* __restrict__ sp, int force_march,
                                                const float* __restrict__ x0, const float* __restrict__ x1, int64_t n,
                                                uint8_t* __restrict__ hit, float* __restrict__ t, float* __restrict__ nrm,
                                                float* __restrict__ alb, int32_t* __restrict__ mat) {
@@ -172,11 +280,15 @@ __global__ void __launch_bounds__(256) k_label(int kind, const double* __restric
         int m = 0;
         if (h) {
             const double p[3] = {p0[0] + tau * u[0], p0[1] + tau * u[1], p0[2] + tau * u[2]};
-            scene_gradient(kind, sp, p, g);
+            if (kind == 2) {
+                blob_surface(sp, p, g, a, &m);
+            } else {
+                scene_gradient(kind, sp, p, g);
+                scene_attributes(kind, sp, p, a, &m);
+            }
             const double gl = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
             if (gl > 0.0) { g[0] /= gl; g[1] /= gl; g[2] /= gl; }
             else { g[0] = g[1] = g[2] = 0.0; }
-            scene_attributes(kind, sp, p, a, &m);
         } else {
             tau = 0.0;
         }
@@ -188,13 +300,36 @@ __global__ void __launch_bounds__(256) k_label(int kind, const double* __restric
     }
 }
 
-static void launch_label(int kind, const double* sp_dev, int force_march, const float* x0, const float* x1, int64_t n,
-                         uint8_t* hit, float* t, float* nrm, float* alb, int32_t* mat, hipStream_t st) {
+// The scene's parameters as a kernel argument (small scenes: no buffer, no copy) or in memory.
+constexpr int kSceneArgs = 416;
+struct SceneArgs {
+    double v[kSceneArgs];
+};
+
+__global__ void __launch_bounds__(256) k_label_args(SceneArgs scene, int kind, int force_march, const float* __restrict__ x0,
+                                                    const float* __restrict__ x1, int64_t n, uint8_t* __restrict__ hit,
+                                                    float* __restrict__ t, float* __restrict__ nrm, float* __restrict__ alb,
+                                                    int32_t* __restrict__ mat) {
+    label_segments(kind, scene.v, force_march, x0, x1, n, hit, t, nrm, alb, mat);
+}
+
+__global__ void __launch_bounds__(256) k_label(int kind, const double* __restrict__ sp, int force_march,
+                                               const float* __restrict__ x0, const float* __restrict__ x1, int64_t n,
+                                               uint8_t* __restrict__ hit, float* __restrict__ t, float* __restrict__ nrm,
+                                               float* __restrict__ alb, int32_t* __restrict__ mat) {
+    label_segments(kind, sp, force_march, x0, x1, n, hit, t, nrm, alb, mat);
+}
+
+static unsigned label_blocks(int64_t n) {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
-    const int64_t blocks = std::min<int64_t>((n + 255) / 256, (int64_t)cus * 16);
-    hipLaunchKernelGGL(k_label, dim3((unsigned)blocks), dim3(256), 0, st, kind, sp_dev, force_march, x0, x1, n, hit, t,
+    return (unsigned)std::min<int64_t>((n + 255) / 256, (int64_t)cus * 16);
+}
+
+static void launch_label(int kind, const double* sp_dev, int force_march, const float* x0, const float* x1, int64_t n,
+                         uint8_t* hit, float* t, float* nrm, float* alb, int32_t* mat, hipStream_t st) {
+    hipLaunchKernelGGL(k_label, dim3(label_blocks(n)), dim3(256), 0, st, kind, sp_dev, force_march, x0, x1, n, hit, t,
                        nrm, alb, mat);
 }
 
@@ -202,8 +337,17 @@ int label_launch(int kind, const double* params_host, int32_t n_params, int forc
                  const float* x1, int64_t n, uint8_t* hit, float* t, float* nrm, float* alb, int32_t* mat,
                  hipStream_t st) {
     if (n == 0) return NIF_OK;
+    int rc;
+    if (n_params <= kSceneArgs) {
+        SceneArgs scene = {};
+        std::copy(params_host, params_host + n_params, scene.v);
+        hipLaunchKernelGGL(k_label_args, dim3(label_blocks(n)), dim3(256), 0, st, scene, kind, force_march, x0, x1, n, hit, t,
+                           nrm, alb, mat);
+        if ((rc = check_hip(hipGetLastError(), "k_label launch"))) return rc;
+        return check_hip(hipStreamSynchronize(st), "label sync");
+    }
     double* dp = nullptr;
-    int rc = check_hip(hipMalloc(&dp, sizeof(double) * n_params), "hipMalloc scene");
+    rc = check_hip(hipMalloc(&dp, sizeof(double) * n_params), "hipMalloc scene");
     if (rc) return rc;
     rc = check_hip(hipMemcpyAsync(dp, params_host, sizeof(double) * n_params, hipMemcpyHostToDevice, st), "copy scene");
     if (!rc) {
