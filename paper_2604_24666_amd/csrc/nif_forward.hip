@@ -10,23 +10,61 @@ namespace nif {
 
 // ------------------------------------------------------------------ network on given points
 
-// Full encoding of n points (lane per point): out[i][(s L + l) Fd + f].
+// Full encoding of n points: out[i][(s L + l) Fd + f], one thread per (point, level).  For three
+// features and the concatenated form, which have no panels.
 __global__ void __launch_bounds__(256) k_encode(EncParams ep, const float* __restrict__ x, int64_t n,
                                                 float* __restrict__ out) {
     const int S = 1 + 2 * ep.F;
     const int W = S * ep.L * ep.Fd;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * ep.L; e += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t i = e / ep.L;
+        const int l = (int)(e - i * ep.L);
         PEState pe;
         pe_begin(pe, x[i], x[n + i], x[2 * n + i]);
         for (int s = 0; s < S; ++s) {
             double smp[3];
             pe_sample(pe, s, smp);
-            for (int l = 0; l < ep.L; ++l) {
-                float* o = out + i * W + (s * ep.L + l) * ep.Fd;
-                if (ep.f16) grid_lookup_any<true>(ep, l, smp[0], smp[1], smp[2], set_offset(ep, s), o);
-                else grid_lookup_any<false>(ep, l, smp[0], smp[1], smp[2], set_offset(ep, s), o);
-            }
+            float* o = out + i * W + (s * ep.L + l) * ep.Fd;
+            if (ep.f16) grid_lookup_any<true>(ep, l, smp[0], smp[1], smp[2], set_offset(ep, s), o);
+            else grid_lookup_any<false>(ep, l, smp[0], smp[1], smp[2], set_offset(ep, s), o);
         }
+    }
+}
+
+// FP64 PE samples of n points (SoA, stride ld): pos[s][axis][i].
+__global__ void __launch_bounds__(64) k_samples(int F, const float* __restrict__ x, int64_t n, int64_t ld,
+                                                double* __restrict__ pos) {
+    const int S = 1 + 2 * F;
+    const int64_t pn = panel_stride(n), i = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (i >= n) return;
+    PEState pe;
+    pe_begin(pe, x[i], x[ld + i], x[2 * ld + i]);
+    for (int s = 0; s < S; ++s) {
+        double smp[3];
+        pe_sample(pe, s, smp);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) pos[((int64_t)s * 3 + a) * pn + i] = smp[a];
+    }
+}
+
+// Panels of single points to rows: out[i][s L + l] from enc[l S + s][i], two floats each, by tiles of
+// 64 x 64 through LDS, so that both sides move full lines.  Bound: memory (60,001 points at 16 levels
+// and 13 samples: 100 MB each way).
+__global__ void __launch_bounds__(256) k_panel_rows(int S, int L, const float2* __restrict__ enc, int64_t n,
+                                                    float* __restrict__ out) {
+    __shared__ float2 s_t[64][65];
+    const int64_t pn = panel_stride(n), i0 = (int64_t)blockIdx.x * 64;
+    const int G = S * L, g0 = (int)blockIdx.y * 64;
+    const int a = threadIdx.x & 63, b = threadIdx.x >> 6;
+    for (int k = b; k < 64 && g0 + k < G; k += 4) {
+        const int s = (g0 + k) / L, l = (g0 + k) - s * L;
+        if (i0 + a < n) s_t[k][a] = enc[((int64_t)l * S + s) * pn + i0 + a];
+    }
+    __syncthreads();
+    if (g0 + a >= G) return;
+    for (int p = b; p < 64 && i0 + p < n; p += 4) {
+        const float2 v = s_t[a][p];
+        __builtin_memcpy(out + ((i0 + p) * G + g0 + a) * 2, &v, sizeof(v));     // any float's alignment
     }
 }
 
@@ -285,12 +323,24 @@ NetParams make_net_params(const nif_model* m, int32_t precision) {
     return np;
 }
 
-int encode_launch(const nif_model* m, const float* x, int64_t n, float* out, hipStream_t st) {
-    if (n == 0) return NIF_OK;
-    const NetParams np = make_net_params(m, NIF_PREC_FP32);
-    const int64_t blocks = std::min<int64_t>((n + 255) / 256, (int64_t)device_cus() * 16);
-    hipLaunchKernelGGL(k_encode, dim3((unsigned)blocks), dim3(256), 0, st, np.enc, x, n, out);
-    return check_hip(hipGetLastError(), "k_encode launch");
+// Panels of n point pairs or points from their positions.
+template <class Pos>
+static void launch_lookups(const EncParams& ep, const Pos* pos, int64_t n, float* enc, hipStream_t st) {
+    const int C = combinations<Pos>(1 + 2 * ep.F);
+    // Small tables are looked up in LDS once the copies pay: 8 levels of 2^14 FP32 entries, 16,212
+    // pairs 58 -> 30 us, 60,000 203 -> 60; 500 pairs 9 -> 19 us, hence the least of 2^17 lookups a
+    // level.  Only where every level fits: the three coarsest of a 16-level 2^19 grid cost as much
+    // from LDS as they save.
+    const LdsPlan S = lds_plan(ep, C * n, device_cus());
+    if (S.n == ep.L && C * n >= (1 << 17)) {
+        if (ep.f16) hipLaunchKernelGGL((k_encode_lds<true, Pos>), dim3(S.total), dim3(1024), S.bytes, st, ep, S, pos, (uint32_t)n, (float2*)enc);
+        else hipLaunchKernelGGL((k_encode_lds<false, Pos>), dim3(S.total), dim3(1024), S.bytes, st, ep, S, pos, (uint32_t)n, (float2*)enc);
+        return;
+    }
+    const EncPlan P = level_plan(ep, (n + 255) / 256, (C + kEncKC - 1) / kEncKC);
+    const dim3 g(plan_blocks(P));
+    if (ep.f16) hipLaunchKernelGGL((k_encode_levels<kEncKC, true, Pos>), g, dim3(256), 0, st, ep, P, pos, n, (float2*)enc);
+    else hipLaunchKernelGGL((k_encode_levels<kEncKC, false, Pos>), g, dim3(256), 0, st, ep, P, pos, n, (float2*)enc);
 }
 
 // Positions and panels of n pairs (SoA with stride ld).
@@ -298,21 +348,30 @@ static void launch_panels(const NetParams& np, const float* x0, const float* x1,
                           float* enc, hipStream_t st) {
     const unsigned pb = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
     hipLaunchKernelGGL(k_positions, dim3(pb, 4), dim3(256), 0, st, np.enc.F, x0, x1, n, ld, pos);
-    const int C = 2 * (1 + 2 * np.enc.F);
-    // Small tables are looked up in LDS once the copies pay: 8 levels of 2^14 FP32 entries, 16,212
-    // pairs 58 -> 30 us, 60,000 203 -> 60; 500 pairs 9 -> 19 us, hence the least of 2^17 lookups a
-    // level.  Only where every level fits: the three coarsest of a 16-level 2^19 grid cost as much
-    // from LDS as they save.
-    const LdsPlan S = lds_plan(np.enc, n, device_cus());
-    if (S.n == np.enc.L && C * n >= (1 << 17)) {
-        if (np.enc.f16) hipLaunchKernelGGL(k_encode_lds<true>, dim3(S.total), dim3(1024), S.bytes, st, np.enc, S, pos, (uint32_t)n, (float2*)enc);
-        else hipLaunchKernelGGL(k_encode_lds<false>, dim3(S.total), dim3(1024), S.bytes, st, np.enc, S, pos, (uint32_t)n, (float2*)enc);
-        return;
+    launch_lookups<uint32_t>(np.enc, pos, n, enc, st);
+}
+
+// Points go through the forward's panels, by chunks of its size: one lane per point walked its S L
+// lookups one after the other (60,001 points at 16 levels of 2^19 FP16 entries: 2.4 ms).
+int encode_launch(const nif_model* m, const float* x, int64_t n, float* out, hipStream_t st) {
+    if (n == 0) return NIF_OK;
+    const EncParams ep = make_net_params(m, NIF_PREC_FP32).enc;
+    if (!uses_panels(m)) {
+        const int64_t blocks = std::min<int64_t>((n * ep.L + 255) / 256, (int64_t)device_cus() * 32);
+        hipLaunchKernelGGL(k_encode, dim3((unsigned)blocks), dim3(256), 0, st, ep, x, n, out);
+        return check_hip(hipGetLastError(), "k_encode launch");
     }
-    const EncPlan P = level_plan(np.enc, (n + 255) / 256, (C + kEncKC - 1) / kEncKC);
-    const dim3 g(plan_blocks(P));
-    if (np.enc.f16) hipLaunchKernelGGL((k_encode_levels<kEncKC, true>), g, dim3(256), 0, st, np.enc, P, pos, n, (float2*)enc);
-    else hipLaunchKernelGGL((k_encode_levels<kEncKC, false>), g, dim3(256), 0, st, np.enc, P, pos, n, (float2*)enc);
+    const int G = m->S * ep.L;
+    const int64_t most = forward_chunk(m);
+    double* pos = reinterpret_cast<double*>(m->fwd_pos);        // S FP64 samples: the bytes of 2 S fixed-point ones
+    for (int64_t c0 = 0; c0 < n; c0 += most) {
+        const int64_t c = std::min<int64_t>(most, n - c0);
+        hipLaunchKernelGGL(k_samples, dim3((unsigned)((c + 63) / 64)), dim3(64), 0, st, ep.F, x + c0, c, n, pos);
+        launch_lookups<double>(ep, pos, c, m->fwd_enc, st);
+        hipLaunchKernelGGL(k_panel_rows, dim3((unsigned)((c + 63) / 64), (unsigned)((G + 63) / 64)), dim3(256), 0, st, m->S, ep.L,
+                           (const float2*)m->fwd_enc, c, out + c0 * G * 2);
+    }
+    return check_hip(hipGetLastError(), "encode launch");
 }
 
 template <int HW, int CB, int PREC>

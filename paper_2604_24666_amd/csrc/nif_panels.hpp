@@ -10,7 +10,8 @@
 // Panels: enc[g][i][2], g = l C + c: the two features of level l, PE combination c (point-major,
 // C = 2 S of them) of segment i; rows of panel_stride(n) segments, so that pairs of segments are
 // 16-byte aligned.  Positions: pos[c][axis][i], 32-bit fixed point, the same row length.
-// Both hold exactly the values the fused kernels form in registers.
+// Both hold exactly the values the fused kernels form in registers.  nif_encode uses the same form
+// for single points: C = S combinations, FP64 positions.
 #pragma once
 #include <algorithm>
 #include <cstring>
@@ -22,11 +23,15 @@ namespace nif {
 
 __host__ __device__ inline int64_t panel_stride(int64_t n) { return (n + 15) & ~(int64_t)15; }
 
-// Interpolated features of KC fixed-point positions at one (wave-uniform) level: the lookup of
+// Cell and weight of a position on one axis: 32-bit fixed point, or FP64.
+__device__ __forceinline__ void axis_at(uint32_t f, uint32_t N, uint32_t& i0, float& w) { fix_axis(f, N, i0, w); }
+__device__ __forceinline__ void axis_at(double s, uint32_t N, uint32_t& i0, float& w) { grid_axis(s, (int)N, i0, w); }
+
+// Interpolated features of KC positions at one (wave-uniform) level: the lookup of
 // lookup_levels with the roles of levels and positions exchanged, the same arithmetic in the
 // same order.
-template <int KC, bool F16>
-__device__ __forceinline__ void lookup_points(const EncParams& ep, int l, const uint32_t (&f)[KC][3],
+template <int KC, bool F16, class Pos>
+__device__ __forceinline__ void lookup_points(const EncParams& ep, int l, const Pos (&f)[KC][3],
                                               const uint32_t (&set_off)[KC], float2 (&out)[KC]) {
     using E = typename TabTypes<F16>::E;
     using Pr = typename TabTypes<F16>::Pr;
@@ -41,9 +46,9 @@ __device__ __forceinline__ void lookup_points(const EncParams& ep, int l, const 
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
         uint32_t ix, iy, iz;
-        fix_axis(f[k][0], N, ix, wx[k]);
-        fix_axis(f[k][1], N, iy, wy[k]);
-        fix_axis(f[k][2], N, iz, wz[k]);
+        axis_at(f[k][0], N, ix, wx[k]);
+        axis_at(f[k][1], N, iy, wy[k]);
+        axis_at(f[k][2], N, iz, wz[k]);
         swp[k] = odd[k] = 0u;
         const E* tl = tab + (set_off[k] + ((uint32_t)l << ep.log2T));
         if (dense) {
@@ -94,6 +99,10 @@ __device__ __forceinline__ void lookup_points(const EncParams& ep, int l, const 
         out[k] = acc;
     }
 }
+
+// Point pairs have fixed-point positions and two points of S samples, single points S FP64 samples.
+template <class Pos>
+__host__ __device__ constexpr int combinations(int S) { return std::is_same<Pos, double>::value ? S : 2 * S; }
 
 // Work of a level-by-level pass: which (level, part) items each XCD goes through, in order.  A part is
 // a share of the level's (combination group, segment tile) workgroups.  Workgroup b runs on XCD
@@ -161,16 +170,17 @@ __device__ __forceinline__ bool plan_item(const EncPlan& P, int& l, int& grp, in
 // 0.72 ms (75 G lookups/s); the fused forward of the same pairs took 1.44 ms, 4,096 pairs 41
 // against 277 us.  Two combinations per thread keep 8 to 16 loads in flight; one takes 0.75 ms,
 // four (fewer waves) 0.84.
-template <int KC, bool F16>
-__global__ void __launch_bounds__(256) k_encode_levels(EncParams ep, EncPlan plan, const uint32_t* __restrict__ pos,
+template <int KC, bool F16, class Pos>
+__global__ void __launch_bounds__(256) k_encode_levels(EncParams ep, EncPlan plan, const Pos* __restrict__ pos,
                                                        int64_t n, float2* __restrict__ enc) {
-    const int S = 1 + 2 * ep.F, C = 2 * S;
+    const int S = 1 + 2 * ep.F, C = combinations<Pos>(S);
     int l, grp, tile;
     if (!plan_item(plan, l, grp, tile)) return;
     const int64_t i = (int64_t)tile * 256 + threadIdx.x;
     if (i >= n) return;
     const int64_t pn = panel_stride(n);
-    uint32_t f[KC][3], so[KC];
+    Pos f[KC][3];
+    uint32_t so[KC];
     float2 o[KC];
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
@@ -179,7 +189,7 @@ __global__ void __launch_bounds__(256) k_encode_levels(EncParams ep, EncPlan pla
 #pragma unroll
         for (int a = 0; a < 3; ++a) f[k][a] = pos[((int64_t)c * 3 + a) * pn + i];
     }
-    lookup_points<KC, F16>(ep, l, f, so, o);
+    lookup_points<KC, F16, Pos>(ep, l, f, so, o);
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
         const int c = grp * KC + k;
@@ -195,11 +205,11 @@ constexpr int kLdsTableBytes = 152 * 1024;
 struct LdsPlan {
     int32_t n;                  // levels
     uint8_t lev[16];
-    uint16_t blocks[16];        // blocks of each
+    uint16_t blocks[16];        // blocks of each, by its lookups
     int32_t entries[16];        // entries in use
     int32_t total, bytes;       // blocks in all, largest table
 };
-inline LdsPlan lds_plan(const EncParams& ep, int64_t n, int cus) {
+inline LdsPlan lds_plan(const EncParams& ep, int64_t lookups, int cus) {
     LdsPlan P;
     memset(&P, 0, sizeof(P));
     if (ep.set_stride) return P;                        // one table set per sample: too many tables
@@ -213,7 +223,6 @@ inline LdsPlan lds_plan(const EncParams& ep, int64_t n, int cus) {
         P.bytes = std::max<int32_t>(P.bytes, (int32_t)((e * size + 15) / 16 * 16));
         ++P.n;
     }
-    const int64_t lookups = 2 * (1 + 2 * (int64_t)ep.F) * n;
     for (int k = 0; k < P.n; ++k) {
         // one block per compute unit over all levels, each with enough lookups to pay for the copy
         const int64_t least = std::max<int64_t>(4096, P.entries[k] / 2);
@@ -223,8 +232,8 @@ inline LdsPlan lds_plan(const EncParams& ep, int64_t n, int cus) {
     return P;
 }
 
-template <bool F16>
-__global__ void __launch_bounds__(1024) k_encode_lds(EncParams ep, LdsPlan plan, const uint32_t* __restrict__ pos, uint32_t n,
+template <bool F16, class Pos>
+__global__ void __launch_bounds__(1024) k_encode_lds(EncParams ep, LdsPlan plan, const Pos* __restrict__ pos, uint32_t n,
                                                      float2* __restrict__ enc) {
     using E = typename TabTypes<F16>::E;
     extern __shared__ uint4 s_raw[];
@@ -235,19 +244,19 @@ __global__ void __launch_bounds__(1024) k_encode_lds(EncParams ep, LdsPlan plan,
     const E* tab = reinterpret_cast<const E*>(ep.tab) + ((size_t)l << ep.log2T);
     for (int e = threadIdx.x; e < plan.entries[k]; e += 1024) s_tab[e] = tab[e];
     __syncthreads();
-    const uint32_t C = 2 * (1 + 2 * ep.F), all = C * n;
+    const uint32_t C = combinations<Pos>(1 + 2 * ep.F), all = C * n;
     const int64_t pn = panel_stride(n);
     const uint32_t f0 = (uint32_t)((uint64_t)all * b / G), f1 = (uint32_t)((uint64_t)all * (b + 1) / G);
     const uint32_t N = (uint32_t)ep.res[l], n1 = N + 1u, mask = (1u << ep.log2T) - 1u;
     const bool dense = (ep.dense_mask >> l) & 1u;
     for (uint32_t f = f0 + threadIdx.x; f < f1; f += 1024) {
         const uint32_t c = f / n, i = f - c * n;
-        const uint32_t* p = pos + (int64_t)c * 3 * pn + i;
+        const Pos* p = pos + (int64_t)c * 3 * pn + i;
         uint32_t ix, iy, iz;
         float wx, wy, wz;
-        fix_axis(p[0], N, ix, wx);
-        fix_axis(p[pn], N, iy, wy);
-        fix_axis(p[2 * pn], N, iz, wz);
+        axis_at(p[0], N, ix, wx);
+        axis_at(p[pn], N, iy, wy);
+        axis_at(p[2 * pn], N, iz, wz);
         E v[4][2];
         if (dense) {
             const uint32_t e = ix + n1 * (iy + n1 * iz);

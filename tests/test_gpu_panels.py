@@ -41,3 +41,27 @@ def test_forward_does_not_depend_on_the_launch_form(name, prec):
         assert torch.equal(part, whole[at:at + size]), size
         at += size
     assert bool(torch.isfinite(whole).all()) and float(whole.std()) > 0
+
+
+@pytest.mark.parametrize("name", list(MODELS))
+def test_encode_does_not_depend_on_the_launch_form(name):
+    """Rows of nif_encode: chunks, level-by-level and LDS lookups, an output that is aligned to 4 bytes only."""
+    import torch
+    import paper_2604_24666_amd as P
+    m = MODELS[name]
+    n = 140003
+    say(f"encode launch forms: {name}")
+    tab, prm, _ = model_params(m, 13, 1e3)
+    model = P.Model(m)
+    model.set_params(tab, prm)
+    x, _ = (dev_f32(v) for v in S.random_points(n, 14))
+    whole = model.encode(x)
+    at = 0
+    for size in (1, 63, 64, 65, 300, 5003, 20011, 70001):
+        part = x[:, at:at + size].contiguous()
+        out = torch.full((size * whole.shape[1] + 1,), float("nan"), device="cuda")
+        P.nif_encode(model.h, part, size, out[1:])
+        torch.cuda.synchronize()
+        assert torch.equal(out[1:].view(size, -1), whole[at:at + size]), size
+        at += size
+    assert bool(torch.isfinite(whole).all()) and float(whole.std()) > 0
