@@ -263,6 +263,9 @@ int nif_set_query_blocks_per_cu(int32_t blocks_per_cu);
 /* Rays each wave of the fused query walks at a time: 64, or 16 (one network pass of 16
  * segments per round instead of four: shorter serial chains for launches too small to fill
  * the GPU), or 0 = chosen from the launch size (16 below 8192 rays per compute unit).
+ * With 0 or 16, launches of few rays (64 per compute unit) run in blocks of four waves per 16
+ * rays.  Launches of 2^14 to 2^21 rays without flags evaluate the rays' first segments in
+ * stages (two features, composed encoding); these settings shape what is left.
  * Process-wide; results do not depend on it. */
 int nif_set_query_rays_per_wave(int32_t rays_per_wave);
 /* Measurement support (not part of the method): device ceilings that the rooflines are read

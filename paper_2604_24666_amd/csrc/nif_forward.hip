@@ -110,8 +110,12 @@ __global__ void __launch_bounds__(256, 2) k_forward(NetParams np, const float* _
 // (pair, quarter of the combinations), the runs of layer1_levels, so that the double-angle
 // recurrence starts where it does there.
 __global__ void __launch_bounds__(256) k_positions(int F, const float* __restrict__ x0, const float* __restrict__ x1,
-                                                   int64_t n, int64_t ld, uint32_t* __restrict__ pos) {
+                                                   int64_t n, int64_t ld, uint32_t* __restrict__ pos, Live lv) {
     const int S = 1 + 2 * F, C = 2 * S, U = (C + 3) >> 2;
+    int64_t first;
+    live_range(lv, first, n);
+    x0 += first;
+    x1 += first;
     const int q = blockIdx.y;
     const int64_t pn = panel_stride(n);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
@@ -136,7 +140,10 @@ __global__ void __launch_bounds__(256) k_positions(int F, const float* __restric
 // Bound: at width 128 the FP32 MFMA rate (41 GFLOP per 2^17 pairs), in 16 bits the panels' bytes.
 template <int HW, int CB, int PREC>
 __global__ void __launch_bounds__(256, 2) k_mlp_panels(NetParams np, const float2* __restrict__ enc, int64_t n,
-                                                       float* __restrict__ heads, float* __restrict__ acts) {
+                                                       float* __restrict__ heads, float* __restrict__ acts, Live lv) {
+    int64_t first;
+    live_range(lv, first, n);
+    heads += first * np.H;
     __shared__ float s_z_all[4][16 * CB * kZStride];
     const int w = threadIdx.x >> 6, lane = lane_id();
     float* s_z = s_z_all[w];
@@ -156,129 +163,31 @@ __global__ void __launch_bounds__(256, 2) k_mlp_panels(NetParams np, const float
 }
 
 // The same for launches too small to fill the chip with waves of 16 pairs: a block of four waves
-// shares 16 pairs, each wave computing a quarter of every layer's output blocks (the layers'
-// activations meet in LDS), with four batches of its first-layer operands in flight.  The MFMA
-// steps of every output are those of k_mlp_panels.  Bound: the latency of the panels and weights,
-// a chain of C L / 16 batches that a single wave walks with one batch in flight: 2,000 pairs at
-// width 128 in BF16 took 45 us.
+// shares 16 pairs (block_mlp).  Bound: the latency of the panels and weights, a chain of C L / 16
+// batches that a single wave walks with one batch in flight: 2,000 pairs at width 128 in BF16 took
+// 45 us.
 template <int HW, int PREC>
 __global__ void __launch_bounds__(256) k_mlp_panels_block(NetParams np, const float2* __restrict__ enc, int64_t n,
                                                           float* __restrict__ heads, float* __restrict__ acts) {
-    constexpr int OB = HW / 16, WB = OB >= 4 ? OB / 4 : 1;         // output blocks, of one wave
-    constexpr int LDA = HW + 4;
-    constexpr int DEPTH = 4;
-    using W = typename std::conditional<PREC == P_FP32, float4, shortx4>::type;
-    __shared__ float s_h[2][16 * LDA];
+    __shared__ float s_h[2][16 * (HW + 4)];
     __shared__ float s_z[16 * kZStride];
-    const int w = threadIdx.x >> 6, lane = lane_id(), q = lane >> 4, j = lane & 15;
-    const bool live_w = w * WB < OB;
-    const int L = np.enc.L, C = 2 * (1 + 2 * np.enc.F), U = (C + 3) >> 2, NLB = L >> 2, T = U * NLB;
+    const int lane = lane_id(), q = lane >> 4, j = lane & 15;
+    const int L = np.enc.L, C = 2 * (1 + 2 * np.enc.F), U = (C + 3) >> 2, NLB = L >> 2;
     const int64_t pn = panel_stride(n);
-    const W* wl = reinterpret_cast<const W*>(np.W0L) + (size_t)(live_w ? w * WB : 0) * T * 128 + lane;
     for (int64_t tile = blockIdx.x; tile * 16 < n; tile += gridDim.x) {
-        const int64_t i0 = tile * 16, row = min(i0 + j, n - 1), seg = i0 + j;
-        floatx4 acc[WB];
-        if (live_w) {
+        const int64_t i0 = tile * 16, row = min(i0 + j, n - 1);
+        block_mlp<HW, PREC, FeatRaw>(np, U * NLB, s_h, s_z, acts, n, i0 + j, [&](int t) {
+            const int u = t / NLB, lb = t - u * NLB, c = q * U + u;
+            const bool live = c < C;
+            const float2* p = enc + ((int64_t)(4 * lb) * C + (live ? c : 0)) * pn + row;
+            FeatRaw r;
 #pragma unroll
-            for (int b = 0; b < WB; ++b) {
-                const float4 bb = *reinterpret_cast<const float4*>(np.b[0] + (w * WB + b) * 16 + 4 * q);
-                acc[b] = floatx4{bb.x, bb.y, bb.z, bb.w};
+            for (int k = 0; k < 4; ++k) {
+                r.f[k] = p[(int64_t)k * C * pn];
+                if (!live) r.f[k] = make_float2(0.f, 0.f);
             }
-            float2 f[DEPTH][4];
-            W wt[DEPTH][WB][2];
-            auto load = [&](int t, float2 (&ff)[4], W (&ww)[WB][2]) {
-                const int u = t / NLB, lb = t - u * NLB, c = q * U + u;
-                const bool live = c < C;
-                const float2* p = enc + ((int64_t)(4 * lb) * C + (live ? c : 0)) * pn + row;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    ff[k] = p[(int64_t)k * C * pn];
-                    if (!live) ff[k] = make_float2(0.f, 0.f);
-                }
-#pragma unroll
-                for (int b = 0; b < WB; ++b) {
-                    ww[b][0] = wl[((size_t)b * T + t) * 128];
-                    ww[b][1] = wl[((size_t)b * T + t) * 128 + 64];
-                }
-            };
-#pragma unroll
-            for (int d = 0; d < DEPTH; ++d)
-                if (d < T) load(d, f[d], wt[d]);
-            for (int t0 = 0; t0 < T; t0 += DEPTH)
-#pragma unroll
-                for (int d = 0; d < DEPTH; ++d) {
-                    if (t0 + d >= T) break;
-                    if constexpr (PREC == P_FP32) {
-#pragma unroll
-                        for (int b = 0; b < WB; ++b) {
-                            const float wf[8] = {wt[d][b][0].x, wt[d][b][0].y, wt[d][b][0].z, wt[d][b][0].w,
-                                                 wt[d][b][1].x, wt[d][b][1].y, wt[d][b][1].z, wt[d][b][1].w};
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) {
-                                acc[b] = mfma32(wf[2 * k], f[d][k].x, acc[b]);
-                                acc[b] = mfma32(wf[2 * k + 1], f[d][k].y, acc[b]);
-                            }
-                        }
-                    } else {
-                        shortx4 pk[2];
-#pragma unroll
-                        for (int h = 0; h < 2; ++h)
-                            pk[h] = pack4<PREC>(f[d][2 * h].x, f[d][2 * h].y, f[d][2 * h + 1].x, f[d][2 * h + 1].y);
-#pragma unroll
-                        for (int b = 0; b < WB; ++b)
-#pragma unroll
-                            for (int h = 0; h < 2; ++h) acc[b] = mfma16<PREC>(wt[d][b][h], pk[h], acc[b]);
-                    }
-                    if (t0 + d + DEPTH < T) load(t0 + d + DEPTH, f[d], wt[d]);
-                }
-        }
-        for (int layer = 1; layer <= np.n_hidden; ++layer) {
-            float* h = s_h[layer & 1];
-            if (live_w) {
-#pragma unroll
-                for (int b = 0; b < WB; ++b) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[b][r] = fmaxf(acc[b][r], 0.f);
-                    const float4 v = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
-                    const int o = (w * WB + b) * 16 + 4 * q;
-                    *reinterpret_cast<float4*>(h + j * LDA + o) = v;
-                    if (acts && seg < n)
-                        *reinterpret_cast<float4*>(acts + (int64_t)(layer - 1) * n * HW + seg * HW + o) = v;
-                }
-            }
-            __syncthreads();
-            const bool is_out = layer == np.n_hidden;
-            if (is_out ? w == 0 : live_w) {
-                const float* bl = np.b[layer];
-#pragma unroll
-                for (int b = 0; b < WB; ++b) {
-                    if (is_out && b > 0) break;
-                    const int oo = is_out ? 0 : w * WB + b;
-                    const float4 bb = *reinterpret_cast<const float4*>(bl + oo * 16 + 4 * q);
-                    floatx4 o = {bb.x, bb.y, bb.z, bb.w};
-#pragma unroll
-                    for (int ib = 0; ib < OB; ++ib) {
-                        const float4 x = *reinterpret_cast<const float4*>(h + j * LDA + ib * 16 + 4 * q);
-                        const size_t at = (size_t)(oo * 16 + j) * HW + ib * 16 + 4 * q;
-                        if constexpr (PREC == P_FP32) {
-                            const float4 wv = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(np.W[layer]) + at);
-                            o = mfma32(wv.x, x.x, o);
-                            o = mfma32(wv.y, x.y, o);
-                            o = mfma32(wv.z, x.z, o);
-                            o = mfma32(wv.w, x.w, o);
-                        } else {
-                            const shortx4 wa = *reinterpret_cast<const shortx4*>(reinterpret_cast<const uint16_t*>(np.W[layer]) + at);
-                            o = mfma16<PREC>(wa, pack4<PREC>(x.x, x.y, x.z, x.w), o);
-                        }
-                    }
-                    acc[b] = o;
-                }
-                if (is_out)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) s_z[j * kZStride + 4 * q + r] = acc[0][r];
-            }
-        }
-        __syncthreads();
+            return r;
+        });
         for (int t = threadIdx.x; t < 16 * np.H; t += 256) {
             const int i = t / np.H, hh = t - i * np.H;
             if (i0 + i < n) heads[(i0 + i) * np.H + hh] = s_z[i * kZStride + hh];
@@ -324,8 +233,9 @@ NetParams make_net_params(const nif_model* m, int32_t precision) {
 }
 
 // Panels of n point pairs or points from their positions.
+// (n: the most there can be, with lv).
 template <class Pos>
-static void launch_lookups(const EncParams& ep, const Pos* pos, int64_t n, float* enc, hipStream_t st) {
+static void launch_lookups(const EncParams& ep, const Pos* pos, int64_t n, float* enc, hipStream_t st, const Live& lv = Live{}) {
     const int C = combinations<Pos>(1 + 2 * ep.F);
     // Small tables are looked up in LDS once the copies pay: 8 levels of 2^14 FP32 entries, 16,212
     // pairs 58 -> 30 us, 60,000 203 -> 60; 500 pairs 9 -> 19 us, hence the least of 2^17 lookups a
@@ -333,22 +243,22 @@ static void launch_lookups(const EncParams& ep, const Pos* pos, int64_t n, float
     // from LDS as they save.
     const LdsPlan S = lds_plan(ep, C * n, device_cus());
     if (S.n == ep.L && C * n >= (1 << 17)) {
-        if (ep.f16) hipLaunchKernelGGL((k_encode_lds<true, Pos>), dim3(S.total), dim3(1024), S.bytes, st, ep, S, pos, (uint32_t)n, (float2*)enc);
-        else hipLaunchKernelGGL((k_encode_lds<false, Pos>), dim3(S.total), dim3(1024), S.bytes, st, ep, S, pos, (uint32_t)n, (float2*)enc);
+        if (ep.f16) hipLaunchKernelGGL((k_encode_lds<true, Pos>), dim3(S.total), dim3(1024), S.bytes, st, ep, S, pos, n, (float2*)enc, lv);
+        else hipLaunchKernelGGL((k_encode_lds<false, Pos>), dim3(S.total), dim3(1024), S.bytes, st, ep, S, pos, n, (float2*)enc, lv);
         return;
     }
     const EncPlan P = level_plan(ep, (n + 255) / 256, (C + kEncKC - 1) / kEncKC);
     const dim3 g(plan_blocks(P));
-    if (ep.f16) hipLaunchKernelGGL((k_encode_levels<kEncKC, true, Pos>), g, dim3(256), 0, st, ep, P, pos, n, (float2*)enc);
-    else hipLaunchKernelGGL((k_encode_levels<kEncKC, false, Pos>), g, dim3(256), 0, st, ep, P, pos, n, (float2*)enc);
+    if (ep.f16) hipLaunchKernelGGL((k_encode_levels<kEncKC, true, Pos>), g, dim3(256), 0, st, ep, P, pos, n, (float2*)enc, lv);
+    else hipLaunchKernelGGL((k_encode_levels<kEncKC, false, Pos>), g, dim3(256), 0, st, ep, P, pos, n, (float2*)enc, lv);
 }
 
 // Positions and panels of n pairs (SoA with stride ld).
 static void launch_panels(const NetParams& np, const float* x0, const float* x1, int64_t n, int64_t ld, uint32_t* pos,
-                          float* enc, hipStream_t st) {
+                          float* enc, hipStream_t st, const Live& lv) {
     const unsigned pb = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_positions, dim3(pb, 4), dim3(256), 0, st, np.enc.F, x0, x1, n, ld, pos);
-    launch_lookups<uint32_t>(np.enc, pos, n, enc, st);
+    hipLaunchKernelGGL(k_positions, dim3(pb, 4), dim3(256), 0, st, np.enc.F, x0, x1, n, ld, pos, lv);
+    launch_lookups<uint32_t>(np.enc, pos, n, enc, st, lv);
 }
 
 // Points go through the forward's panels, by chunks of its size: one lane per point walked its S L
@@ -375,10 +285,10 @@ int encode_launch(const nif_model* m, const float* x, int64_t n, float* out, hip
 }
 
 template <int HW, int CB, int PREC>
-static void launch_mlp(const NetParams& np, const float* enc, int64_t n, float* heads, float* acts, hipStream_t st) {
+static void launch_mlp(const NetParams& np, const float* enc, int64_t n, float* heads, float* acts, hipStream_t st, const Live& lv) {
     const int64_t tiles = (n + 16 * CB - 1) / (16 * CB);
     const unsigned blocks = (unsigned)std::min<int64_t>((tiles + 3) / 4, (int64_t)device_cus() * 8);
-    hipLaunchKernelGGL((k_mlp_panels<HW, CB, PREC>), dim3(blocks), dim3(256), 0, st, np, (const float2*)enc, n, heads, acts);
+    hipLaunchKernelGGL((k_mlp_panels<HW, CB, PREC>), dim3(blocks), dim3(256), 0, st, np, (const float2*)enc, n, heads, acts, lv);
 }
 
 // 8,001 pairs FP32 / BF16 at width 128: 126 / 116 us with blocks, 171 / 128 with waves; 16,212
@@ -388,17 +298,17 @@ constexpr int64_t kBlockMlpPairsPerCU = 40;
 // enc: panels of n pairs (panel_stride(n) E floats), or rows [n][E] (nullable) for the variants.
 template <int HW, int PREC>
 static void launch_forward(const NetParams& np, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
-                           float* acts, float* enc, uint32_t* pos, hipStream_t st) {
+                           float* acts, float* enc, uint32_t* pos, hipStream_t st, const Live& lv) {
     if (np.gamma_F < 0 && np.enc.Fd == 2) {
-        launch_panels(np, x0, x1, n, ld, pos, enc, st);
+        launch_panels(np, x0, x1, n, ld, pos, enc, st, lv);
         // a block per 16 pairs while that is what it takes to fill the chip, 16 pairs per wave until two
         // waves per SIMD are busy, then as many as the registers hold
         constexpr int CB = HW >= 128 ? 2 : 4;
-        if (n <= (int64_t)device_cus() * kBlockMlpPairsPerCU) {
+        if (!lv.count && n <= (int64_t)device_cus() * kBlockMlpPairsPerCU) {
             const unsigned blocks = (unsigned)((n + 15) / 16);
             hipLaunchKernelGGL((k_mlp_panels_block<HW, PREC>), dim3(blocks), dim3(256), 0, st, np, (const float2*)enc, n, heads, acts);
-        } else if (n < (int64_t)device_cus() * 8 * 16 * CB) launch_mlp<HW, 1, PREC>(np, enc, n, heads, acts, st);
-        else launch_mlp<HW, CB, PREC>(np, enc, n, heads, acts, st);
+        } else if (n < (int64_t)device_cus() * 8 * 16 * CB) launch_mlp<HW, 1, PREC>(np, enc, n, heads, acts, st, lv);
+        else launch_mlp<HW, CB, PREC>(np, enc, n, heads, acts, st, lv);
         return;
     }
     // small launches (up to 2^17 pairs) take 16 pairs per wave so that they still fill the chip
@@ -414,12 +324,12 @@ static void launch_forward(const NetParams& np, const float* x0, const float* x1
 
 template <int PREC>
 static int dispatch_forward(int hw, const NetParams& np, const float* x0, const float* x1, int64_t n, int64_t ld,
-                            float* heads, float* acts, float* enc, uint32_t* pos, hipStream_t st) {
+                            float* heads, float* acts, float* enc, uint32_t* pos, hipStream_t st, const Live& lv) {
     switch (hw) {
-        case 16: launch_forward<16, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st); break;
-        case 32: launch_forward<32, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st); break;
-        case 64: launch_forward<64, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st); break;
-        case 128: launch_forward<128, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st); break;
+        case 16: launch_forward<16, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st, lv); break;
+        case 32: launch_forward<32, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st, lv); break;
+        case 64: launch_forward<64, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st, lv); break;
+        case 128: launch_forward<128, PREC>(np, x0, x1, n, ld, heads, acts, enc, pos, st, lv); break;
         default: return fail(NIF_E_UNSUPPORTED, "hidden_width must be 16, 32, 64 or 128");
     }
     return NIF_OK;
@@ -427,26 +337,48 @@ static int dispatch_forward(int hw, const NetParams& np, const float* x0, const 
 
 bool uses_panels(const nif_model* m) { return m->desc.feat_dim == 2 && !m->desc.concat_encoding; }
 
-int forward_rows_launch(const nif_model* m, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
-                        int32_t precision, float* acts, float* enc, uint32_t* pos, hipStream_t st) {
+static int forward_any(const nif_model* m, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
+                       int32_t precision, float* acts, float* enc, uint32_t* pos, hipStream_t st, const Live& lv) {
     if (n == 0) return NIF_OK;
     if (heads == nullptr || ld < n || (uses_panels(m) && (!enc || !pos)))
         return fail(NIF_E_INVALID_ARG, "forward needs a heads buffer, ld >= n and its encoding scratch");
     const NetParams np = make_net_params(m, precision);
     const int hw = m->desc.hidden_width;
     int rc;
-    if (precision == NIF_PREC_FP32) rc = dispatch_forward<P_FP32>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st);
-    else if (precision == NIF_PREC_BF16) rc = dispatch_forward<P_BF16>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st);
-    else rc = dispatch_forward<P_FP16>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st);
+    if (precision == NIF_PREC_FP32) rc = dispatch_forward<P_FP32>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st, lv);
+    else if (precision == NIF_PREC_BF16) rc = dispatch_forward<P_BF16>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st, lv);
+    else rc = dispatch_forward<P_FP16>(hw, np, x0, x1, n, ld, heads, acts, enc, pos, st, lv);
     if (rc) return rc;
     return check_hip(hipGetLastError(), "forward launch");
 }
 
+int forward_rows_launch(const nif_model* m, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
+                        int32_t precision, float* acts, float* enc, uint32_t* pos, hipStream_t st) {
+    return forward_any(m, x0, x1, n, ld, heads, precision, acts, enc, pos, st, Live{});
+}
+
+// Pairs of the panel scratch: 2^16, if that is at most 256 MB.  One part of a staged query takes as
+// many (40,192, as nif_forward: its MLP and launches take 5 to 8% longer; 2^17: the same).
+int64_t stage_chunk(const nif_model* m) {
+    return std::max<int64_t>(4096, std::min<int64_t>(1 << 16, ((int64_t)1 << 28) / ((int64_t)m->E * 4) / 256 * 256));
+}
+
+int forward_live_launch(const nif_model* m, const float* x, int64_t ld, const int32_t* count, int32_t cap, float* heads,
+                        int32_t precision, hipStream_t st) {
+    const int32_t chunk = (int32_t)stage_chunk(m);
+    for (int s = 0; s * chunk < cap; ++s) {
+        const int rc = forward_any(m, x, x + 3 * ld, std::min(cap, chunk), ld, heads, precision, nullptr, m->fwd_enc, m->fwd_pos, st,
+                                   Live{count, cap, chunk, s});
+        if (rc) return rc;
+    }
+    return NIF_OK;
+}
+
 // Chunk of nif_forward: its panels stay within 128 MB, half of the Infinity Cache, so the MLP
-// reads them from there; 40,192 pairs at E = 832, at most 2^17.
+// reads them from there; 40,192 pairs at E = 832, at most 2^16 (stage_chunk).
 int64_t forward_chunk(const nif_model* m) {
     const int64_t per = (int64_t)m->E * 4;
-    return std::max<int64_t>(4096, std::min<int64_t>(1 << 17, ((int64_t)1 << 27) / per / 256 * 256));
+    return std::max<int64_t>(4096, std::min<int64_t>(1 << 16, ((int64_t)1 << 27) / per / 256 * 256));
 }
 
 int forward_launch(const nif_model* m, const float* x0, const float* x1, int64_t B, float* heads, int32_t precision,

@@ -88,9 +88,14 @@ struct nif_model {
     int64_t* tcount = nullptr;          // [16] positives, step, clean steps, flags
     int32_t step = 0;
     bool params_set = false;
-    int64_t* counters = nullptr;        // [8] query work counters
-    float* fwd_enc = nullptr;           // panels of one chunk of nif_forward (forward_chunk pairs)
+    int64_t* counters = nullptr;        // [16] query work counters: 8 ranges, staged segments, rays left over
+    float* fwd_enc = nullptr;           // panels of one part (at most stage_chunk pairs) of nif_forward, nif_encode or a staged query
     uint32_t* fwd_pos = nullptr;        //   and their positions
+    // staged query (panel models): first segments of a part of the rays, their heads, rays left over
+    int32_t* q_list = nullptr;          // [4][stage_cap] ray, voxel, entry t, exit t
+    float* q_x = nullptr;               // [6][stage_cap] rest points
+    float* q_heads = nullptr;           // [stage_cap][H]
+    int32_t* q_rest = nullptr;          // [4][kStageRays] ray, packed voxel, entry t, hit logit
 };
 
 namespace nif {
@@ -111,6 +116,9 @@ int voxelize_launch(int32_t scene_kind, const float* params_dev, int32_t N, uint
 
 // nif_query.hip
 int device_cus();
+// Most rays of a staged query; its list has room for the segments of a quarter of them.
+constexpr int64_t kStageRays = 1 << 21;
+int64_t stage_cap(const nif_model* m);
 int trace_launch(const nif_grid* g, const nif_rays* r, int64_t n, int32_t max_seg,
                  const nif_segments* out, hipStream_t st);
 int query_launch(const nif_model* m, const nif_grid* g, const nif_rays* r, int64_t n,
@@ -135,6 +143,10 @@ int encode_launch(const nif_model* m, const float* x, int64_t n, float* out, hip
 // Whether the model's encodings go through level panels (nif_panels.hpp); else rows [n][E].
 bool uses_panels(const nif_model* m);
 int64_t forward_chunk(const nif_model* m);
+// Heads of the first min(*count, cap) of the pairs x [6][ld].
+int forward_live_launch(const nif_model* m, const float* x, int64_t ld, const int32_t* count, int32_t cap, float* heads,
+                        int32_t precision, hipStream_t st);
+int64_t stage_chunk(const nif_model* m);
 int forward_launch(const nif_model* m, const float* x0, const float* x1, int64_t B, float* heads,
                    int32_t precision, hipStream_t st);
 // Forward of n pairs whose SoA rows have stride ld (heads [n][H], acts [layers][n][HW] local to

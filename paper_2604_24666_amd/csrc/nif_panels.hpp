@@ -104,6 +104,23 @@ __device__ __forceinline__ void lookup_points(const EncParams& ep, int l, const 
 template <class Pos>
 __host__ __device__ constexpr int combinations(int S) { return std::is_same<Pos, double>::value ? S : 2 * S; }
 
+// Pairs of a launch whose number only the device knows (nif_query's segments): slot `slot` of the
+// fewest equal parts of at most `chunk` pairs that min(*count, cap) pairs make.  Without a count the
+// launch's own n pairs from 0.
+struct Live {
+    const int32_t* count;
+    int32_t cap, chunk, slot;
+};
+__device__ __forceinline__ void live_range(const Live& L, int64_t& first, int64_t& n) {
+    first = 0;
+    if (!L.count) return;
+    const int32_t total = min(*L.count, L.cap), k = (total + L.chunk - 1) / L.chunk;
+    if (L.slot >= k) { n = 0; return; }
+    const int32_t size = ((total + k - 1) / k + 255) & ~255;
+    first = (int64_t)L.slot * size;
+    n = max((int64_t)0, min((int64_t)size, total - first));
+}
+
 // Work of a level-by-level pass: which (level, part) items each XCD goes through, in order.  A part is
 // a share of the level's (combination group, segment tile) workgroups.  Workgroup b runs on XCD
 // b mod 8 (round-robin dispatch; only the speed depends on it).
@@ -152,17 +169,19 @@ inline EncPlan level_plan(const EncParams& ep, int64_t tiles, int groups) {
 }
 inline unsigned plan_blocks(const EncPlan& P) { return (unsigned)(kEncXcds * P.most * (int64_t)P.per_item); }
 
-// The (level, combination group, tile) of this workgroup; false if it has none.
+// The (level, combination group, tile) of item v of an XCD's workgroups; false if there is none.
+__device__ __forceinline__ bool plan_item(const EncPlan& P, int x, int v, int tiles, int per_item, int& l, int& grp, int& tile) {
+    const int item = P.item[x][v / per_item];
+    l = item / P.parts;
+    const int b = (item % P.parts) * per_item + v % per_item;           // workgroup within the level
+    grp = b / tiles;
+    tile = b % tiles;
+    return grp < P.groups;
+}
+// The item of this workgroup in a launch of plan_blocks workgroups.
 __device__ __forceinline__ bool plan_item(const EncPlan& P, int& l, int& grp, int& tile) {
     const int x = (int)(blockIdx.x % kEncXcds), v = (int)(blockIdx.x / kEncXcds);
-    const int it = v / P.per_item;
-    if (it >= P.n_items[x]) return false;
-    const int item = P.item[x][it];
-    l = item / P.parts;
-    const int b = (item % P.parts) * P.per_item + v % P.per_item;       // workgroup within the level
-    grp = b / P.tiles;
-    tile = b % P.tiles;
-    return grp < P.groups;
+    return v < P.n_items[x] * P.per_item && plan_item(P, x, v, P.tiles, P.per_item, l, grp, tile);
 }
 
 // Bound: the rate at which L1 and L2 take the lanes' corner requests (about 5 distinct lines per
@@ -172,28 +191,35 @@ __device__ __forceinline__ bool plan_item(const EncPlan& P, int& l, int& grp, in
 // four (fewer waves) 0.84.
 template <int KC, bool F16, class Pos>
 __global__ void __launch_bounds__(256) k_encode_levels(EncParams ep, EncPlan plan, const Pos* __restrict__ pos,
-                                                       int64_t n, float2* __restrict__ enc) {
+                                                       int64_t n, float2* __restrict__ enc, Live lv) {
     const int S = 1 + 2 * ep.F, C = combinations<Pos>(S);
-    int l, grp, tile;
-    if (!plan_item(plan, l, grp, tile)) return;
-    const int64_t i = (int64_t)tile * 256 + threadIdx.x;
-    if (i >= n) return;
+    int64_t first;
+    live_range(lv, first, n);
+    const int tiles = (int)((n + 255) / 256);
+    const int per_item = (int)(((int64_t)tiles * plan.groups + plan.parts - 1) / plan.parts);
     const int64_t pn = panel_stride(n);
-    Pos f[KC][3];
-    uint32_t so[KC];
-    float2 o[KC];
+    const int x = (int)(blockIdx.x % kEncXcds);
+    for (int v = (int)(blockIdx.x / kEncXcds); v < plan.n_items[x] * per_item; v += (int)(gridDim.x / kEncXcds)) {
+        int l, grp, tile;
+        if (!plan_item(plan, x, v, tiles, per_item, l, grp, tile)) continue;
+        const int64_t i = (int64_t)tile * 256 + threadIdx.x;
+        if (i >= n) continue;
+        Pos f[KC][3];
+        uint32_t so[KC];
+        float2 o[KC];
 #pragma unroll
-    for (int k = 0; k < KC; ++k) {
-        const int c = min(grp * KC + k, C - 1);
-        so[k] = combo_set_offset(ep, c, S);
+        for (int k = 0; k < KC; ++k) {
+            const int c = min(grp * KC + k, C - 1);
+            so[k] = combo_set_offset(ep, c, S);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) f[k][a] = pos[((int64_t)c * 3 + a) * pn + i];
-    }
-    lookup_points<KC, F16, Pos>(ep, l, f, so, o);
+            for (int a = 0; a < 3; ++a) f[k][a] = pos[((int64_t)c * 3 + a) * pn + i];
+        }
+        lookup_points<KC, F16, Pos>(ep, l, f, so, o);
 #pragma unroll
-    for (int k = 0; k < KC; ++k) {
-        const int c = grp * KC + k;
-        if (c < C) enc[((int64_t)l * C + c) * pn + i] = o[k];
+        for (int k = 0; k < KC; ++k) {
+            const int c = grp * KC + k;
+            if (c < C) enc[((int64_t)l * C + c) * pn + i] = o[k];
+        }
     }
 }
 
@@ -233,10 +259,14 @@ inline LdsPlan lds_plan(const EncParams& ep, int64_t lookups, int cus) {
 }
 
 template <bool F16, class Pos>
-__global__ void __launch_bounds__(1024) k_encode_lds(EncParams ep, LdsPlan plan, const Pos* __restrict__ pos, uint32_t n,
-                                                     float2* __restrict__ enc) {
+__global__ void __launch_bounds__(1024) k_encode_lds(EncParams ep, LdsPlan plan, const Pos* __restrict__ pos, int64_t n_pairs,
+                                                     float2* __restrict__ enc, Live lv) {
     using E = typename TabTypes<F16>::E;
     extern __shared__ uint4 s_raw[];
+    int64_t first;
+    live_range(lv, first, n_pairs);
+    const uint32_t n = (uint32_t)n_pairs;
+    if (n == 0) return;
     E* s_tab = reinterpret_cast<E*>(s_raw);
     int k = 0, b = (int)blockIdx.x;
     while (b >= plan.blocks[k]) b -= plan.blocks[k++];
@@ -379,6 +409,143 @@ __device__ __forceinline__ void layer1_panels(const NetParams& np, const float2*
                     for (int cb = 0; cb < CB; ++cb) acc[ob][cb] = mfma16<PREC>(w[ob][h], pk[cb][h], acc[ob][cb]);
         }
     }
+}
+
+// First-layer operands of one batch (four levels of one combination) as a lane holds them: features,
+// and packed for the 16-bit MFMAs.
+struct FeatRaw {
+    float2 f[4];
+};
+template <int PREC>
+struct FeatOp {
+    shortx4 v[2];
+};
+template <>
+struct FeatOp<P_FP32> {
+    float2 f[4];
+};
+template <int PREC>
+__device__ __forceinline__ FeatOp<PREC> feat_op(const FeatRaw& r) {
+    FeatOp<PREC> o;
+    if constexpr (PREC == P_FP32) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o.f[k] = r.f[k];
+    } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) o.v[h] = pack4<PREC>(r.f[2 * h].x, r.f[2 * h].y, r.f[2 * h + 1].x, r.f[2 * h + 1].y);
+    }
+    return o;
+}
+template <int PREC>
+__device__ __forceinline__ const FeatOp<PREC>& feat_op(const FeatOp<PREC>& o) { return o; }
+
+// MLP of 16 pairs by a block of four waves, each computing a quarter of every layer's output blocks:
+// the layers' activations meet in LDS (s_h), DEPTH batches of first-layer operands are in flight.  The
+// MFMA steps of every output are those of the one-wave forms.  load(t): operands of batch t.
+// acts (nullable): activations [layer][act_rows][HW], row seg, if seg < act_rows.  Ends with the heads in
+// s_z after a barrier.
+template <int HW, int PREC, class Raw, class Load>
+__device__ __forceinline__ void block_mlp(const NetParams& np, int T, float (*s_h)[16 * (HW + 4)], float* s_z, float* acts,
+                                          int64_t act_rows, int64_t seg, Load load) {
+    constexpr int OB = HW / 16, WB = OB >= 4 ? OB / 4 : 1;         // output blocks, of one wave
+    constexpr int LDA = HW + 4;
+    constexpr int DEPTH = 4;
+    using W = typename std::conditional<PREC == P_FP32, float4, shortx4>::type;
+    const int w = threadIdx.x >> 6, lane = lane_id(), q = lane >> 4, j = lane & 15;
+    const bool live_w = w * WB < OB;
+    const W* wl = reinterpret_cast<const W*>(np.W0L) + (size_t)(live_w ? w * WB : 0) * T * 128 + lane;
+    floatx4 acc[WB];
+    if (live_w) {
+#pragma unroll
+        for (int b = 0; b < WB; ++b) {
+            const float4 bb = *reinterpret_cast<const float4*>(np.b[0] + (w * WB + b) * 16 + 4 * q);
+            acc[b] = floatx4{bb.x, bb.y, bb.z, bb.w};
+        }
+        Raw f[DEPTH];
+        W wt[DEPTH][WB][2];
+        auto fetch = [&](int t, Raw& ff, W (&ww)[WB][2]) {
+            ff = load(t);
+#pragma unroll
+            for (int b = 0; b < WB; ++b) {
+                ww[b][0] = wl[((size_t)b * T + t) * 128];
+                ww[b][1] = wl[((size_t)b * T + t) * 128 + 64];
+            }
+        };
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d)
+            if (d < T) fetch(d, f[d], wt[d]);
+        for (int t0 = 0; t0 < T; t0 += DEPTH)
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                if (t0 + d >= T) break;
+                const FeatOp<PREC> op = feat_op<PREC>(f[d]);
+                if constexpr (PREC == P_FP32) {
+#pragma unroll
+                    for (int b = 0; b < WB; ++b) {
+                        const float wf[8] = {wt[d][b][0].x, wt[d][b][0].y, wt[d][b][0].z, wt[d][b][0].w,
+                                             wt[d][b][1].x, wt[d][b][1].y, wt[d][b][1].z, wt[d][b][1].w};
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            acc[b] = mfma32(wf[2 * k], op.f[k].x, acc[b]);
+                            acc[b] = mfma32(wf[2 * k + 1], op.f[k].y, acc[b]);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int b = 0; b < WB; ++b)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) acc[b] = mfma16<PREC>(wt[d][b][h], op.v[h], acc[b]);
+                }
+                if (t0 + d + DEPTH < T) fetch(t0 + d + DEPTH, f[d], wt[d]);
+            }
+    }
+    for (int layer = 1; layer <= np.n_hidden; ++layer) {
+        float* h = s_h[layer & 1];
+        if (live_w) {
+#pragma unroll
+            for (int b = 0; b < WB; ++b) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[b][r] = fmaxf(acc[b][r], 0.f);
+                const float4 v = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
+                const int o = (w * WB + b) * 16 + 4 * q;
+                *reinterpret_cast<float4*>(h + j * LDA + o) = v;
+                if (acts && seg < act_rows)
+                    *reinterpret_cast<float4*>(acts + (int64_t)(layer - 1) * act_rows * HW + seg * HW + o) = v;
+            }
+        }
+        __syncthreads();
+        const bool is_out = layer == np.n_hidden;
+        if (is_out ? w == 0 : live_w) {
+            const float* bl = np.b[layer];
+#pragma unroll
+            for (int b = 0; b < WB; ++b) {
+                if (is_out && b > 0) break;
+                const int oo = is_out ? 0 : w * WB + b;
+                const float4 bb = *reinterpret_cast<const float4*>(bl + oo * 16 + 4 * q);
+                floatx4 o = {bb.x, bb.y, bb.z, bb.w};
+#pragma unroll
+                for (int ib = 0; ib < OB; ++ib) {
+                    const float4 x = *reinterpret_cast<const float4*>(h + j * LDA + ib * 16 + 4 * q);
+                    const size_t at = (size_t)(oo * 16 + j) * HW + ib * 16 + 4 * q;
+                    if constexpr (PREC == P_FP32) {
+                        const float4 wv = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(np.W[layer]) + at);
+                        o = mfma32(wv.x, x.x, o);
+                        o = mfma32(wv.y, x.y, o);
+                        o = mfma32(wv.z, x.z, o);
+                        o = mfma32(wv.w, x.w, o);
+                    } else {
+                        const shortx4 wa = *reinterpret_cast<const shortx4*>(reinterpret_cast<const uint16_t*>(np.W[layer]) + at);
+                        o = mfma16<PREC>(wa, pack4<PREC>(x.x, x.y, x.z, x.w), o);
+                    }
+                }
+                acc[b] = o;
+            }
+            if (is_out)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s_z[j * kZStride + 4 * q + r] = acc[0][r];
+        }
+    }
+    __syncthreads();
 }
 
 }  // namespace nif

@@ -111,6 +111,123 @@ __global__ void __launch_bounds__(256) k_proxy(GridArgs G, RayArgs R, nif_hits o
     }
 }
 
+// ------------------------------------------------------------------ staged query
+//
+// Launches of many rays evaluate the rays' first segments in stages, each a kernel over all of them: search, encoding level by level, MLP, results.  Table lookups then run
+// at the rate of one level's table in L2 (nif_panels.hpp) and the matrix cores on full tiles, and the
+// search on all lanes.  The fused kernel takes the rays whose first segment is no hit, from there on,
+// and those beyond the list's room (a quarter of the rays; it would otherwise be mostly empty
+// launches).  A ray's result depends on neither.
+
+// First segment of every ray, SUB lanes each: rays without one are misses, the others go
+// to the list, in order of the blocks.
+template <int SUB>
+__global__ void __launch_bounds__(256) k_first(GridArgs G, RayArgs R, nif_hits out, int32_t cap, int32_t* __restrict__ list,
+                                               int64_t ld, float* __restrict__ x, int32_t* __restrict__ n_list,
+                                               int32_t* __restrict__ rest, int32_t* __restrict__ n_rest, int64_t* __restrict__ stats) {
+    __shared__ int32_t s_n[4], s_base;
+    const int64_t r = (int64_t)blockIdx.x * (256 / SUB) + threadIdx.x / SUB;
+    const bool lead = threadIdx.x % SUB == 0;
+    const int w = threadIdx.x >> 6, lane = lane_id();
+    bool has = false;
+    int bad = 0;
+    Segment sg;
+    float3 x0, x1;
+    if (r < R.n) {
+        const Ray ray = load_ray(R, r);
+        const PoseDev P = G.poses[find_pose(R.off, R.n_poses, r)];
+        Trav tv;
+        trav_init(P, ray, tv);
+        has = next_segment<SUB>(P, G.V, G.bin_start, G.bin_cells, G.N, ray, tv, sg, &bad);
+        if (has && R.tmax && sg.a >= R.tmax[r]) has = false;         // occlusion bound reached
+        if (has) {
+            x0 = deform_inv(P, ray_at(ray, sg.a));
+            x1 = deform_inv(P, ray_at(ray, sg.b));
+        } else if (lead) {
+            write_miss(out, r, 0, -INFINITY);
+        }
+    }
+    const bool done = lead && r < R.n && !has;
+    has = has && lead;
+    const uint64_t mask = ballot(has), below = (1ull << lane) - 1ull;
+    if (lane == 0) s_n[w] = popc64(mask);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int32_t c = s_n[0] + s_n[1] + s_n[2] + s_n[3];
+        s_base = c ? atomicAdd(n_list, c) : 0;
+    }
+    __syncthreads();
+    int32_t k = s_base + popc64(mask & below);
+    for (int v = 0; v < w; ++v) k += s_n[v];
+    const bool over = has && k >= cap;
+    if (has && !over) {
+        list[k] = (int32_t)r;
+        list[ld + k] = sg.cell;
+        list[2 * ld + k] = __float_as_int(sg.a);
+        list[3 * ld + k] = __float_as_int(sg.b);
+        x[k] = x0.x; x[ld + k] = x0.y; x[2 * ld + k] = x0.z;
+        x[3 * ld + k] = x1.x; x[4 * ld + k] = x1.y; x[5 * ld + k] = x1.z;
+    }
+    const uint64_t om = ballot(over);
+    if (om) {
+        int32_t base = 0;
+        if (lane == 0) base = atomicAdd(n_rest, popc64(om));
+        base = __shfl(base, 0);
+        if (over) {
+            const int32_t at = base + popc64(om & below);
+            rest[at] = (int32_t)r;
+            rest[kStageRays + at] = -1;
+        }
+    }
+    // every lane counts its own tests; those of a ray beyond the list are counted when it is searched again
+    const uint64_t ray_lanes = SUB == 64 ? ~0ull : ((1ull << SUB) - 1ull) << (lane / SUB * SUB);
+    if (om & ray_lanes) bad = 0;
+    if (stats) wave_add_stats(stats, done ? 1 : 0, 0, bad);
+}
+
+// Results of the staged segments: hits are written, the other rays are left for the fused kernel.
+__global__ void __launch_bounds__(256) k_first_hits(GridArgs G, RayArgs R, nif_hits out, int H, int dist_head, int32_t cap,
+                                                    const int32_t* __restrict__ list, int64_t ld, const float* __restrict__ x,
+                                                    const float* __restrict__ heads, const int32_t* __restrict__ n_list,
+                                                    int32_t* __restrict__ rest, int32_t* __restrict__ n_rest,
+                                                    int64_t* __restrict__ stats) {
+    const int32_t n = min(*n_list, cap);
+    int64_t n_done = 0, n_eval = 0;
+    for (int32_t k0 = (int32_t)blockIdx.x * 256; k0 < n; k0 += (int32_t)gridDim.x * 256) {
+        const int32_t k = k0 + (int32_t)threadIdx.x;
+        bool left = false;
+        if (k < n) {
+            const float* z = heads + (int64_t)k * H;
+            const int64_t r = list[k];
+            ++n_eval;
+            if (z[0] > 0.f) {
+                Segment sg;
+                sg.cell = list[ld + k]; sg.a = __int_as_float(list[2 * ld + k]); sg.b = __int_as_float(list[3 * ld + k]); sg.face = -1;
+                write_hit(out, r, sg, make_float3(x[k], x[ld + k], x[2 * ld + k]),
+                          make_float3(x[3 * ld + k], x[4 * ld + k], x[5 * ld + k]), z, 1, H - 8, dist_head,
+                          R.tmax ? R.tmax[r] : INFINITY, G.poses[find_pose(R.off, R.n_poses, r)]);
+                ++n_done;
+            } else {
+                left = true;
+            }
+        }
+        const uint64_t m = ballot(left);
+        if (m) {
+            int32_t base = 0;
+            if (lane_id() == 0) base = atomicAdd(n_rest, popc64(m));
+            base = __shfl(base, 0);
+            if (left) {
+                const int32_t at = base + popc64(m & ((1ull << lane_id()) - 1ull));
+                rest[at] = list[k];
+                rest[kStageRays + at] = pack_cell(list[ld + k], G.N);
+                rest[2 * kStageRays + at] = list[2 * ld + k];
+                rest[3 * kStageRays + at] = __float_as_int(heads[(int64_t)k * H]);
+            }
+        }
+    }
+    if (stats) wave_add_stats(stats, n_done, n_eval, 0);
+}
+
 // ------------------------------------------------------------------ host launchers
 
 int device_cus() {
@@ -148,6 +265,10 @@ static RayArgs ray_args(const nif_grid* g, const nif_rays* r, int64_t n) {
     R.ox = r->ox; R.oy = r->oy; R.oz = r->oz; R.dx = r->dx; R.dy = r->dy; R.dz = r->dz;
     R.off = r->pose_offsets; R.tmax = r->tmax; R.n_poses = g->n_poses; R.n = n;
     R.order_pre = nullptr;
+    R.rest_n = nullptr;
+    R.rest = nullptr;
+    R.least = 0;
+    R.most = INT64_MAX;
     return R;
 }
 
@@ -177,6 +298,47 @@ static int g_query_blocks_per_cu = 12;
 // Rays per wave: 0 = by launch size, else 16 or 64.
 static int g_query_rays_per_wave = 0;
 
+static int launch_fused(const nif_model* m, const GridArgs& G, const RayArgs& R, const nif_hits* out, int32_t precision,
+                        int64_t* stats, int pt, hipStream_t st) {
+    const NetParams np = make_net_params(m, precision);
+    const int hw = m->desc.hidden_width;
+    const QueryShape sh{device_cus(), g_query_blocks_per_cu, g_query_rays_per_wave};
+    int rc;
+    if (precision == NIF_PREC_FP32) rc = query_fp32(sh, hw, np, G, R, *out, m->counters, stats, pt, st);
+    else if (precision == NIF_PREC_BF16) rc = query_bf16(sh, hw, np, G, R, *out, m->counters, stats, pt, st);
+    else rc = query_fp16(sh, hw, np, G, R, *out, m->counters, stats, pt, st);
+    if (rc) return rc;
+    return check_hip(hipGetLastError(), "k_query launch");
+}
+
+int64_t stage_cap(const nif_model* m) {
+    const int64_t c = stage_chunk(m);
+    return (kStageRays / 4 + c - 1) / c * c;
+}
+
+static int query_staged(const nif_model* m, const GridArgs& G, RayArgs R, int64_t n, const nif_hits* out, int32_t precision,
+                        int64_t* stats, hipStream_t st) {
+    int32_t* n_list = reinterpret_cast<int32_t*>(m->counters + 8);
+    int32_t* n_rest = reinterpret_cast<int32_t*>(m->counters + 9);
+    const int64_t ld = stage_cap(m), chunk = stage_chunk(m);
+    const int32_t cap = (int32_t)std::min(std::max<int64_t>(1, (n / 4 + chunk - 1) / chunk) * chunk, n);
+    hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, st, m->counters, 16);
+    constexpr int SUB = 2;
+    hipLaunchKernelGGL(k_first<SUB>, dim3((unsigned)((n * SUB + 255) / 256)), dim3(256), 0, st, G, R, *out, cap, m->q_list, ld, m->q_x,
+                       n_list, m->q_rest, n_rest, stats);
+    int rc;
+    if ((rc = forward_live_launch(m, m->q_x, ld, n_list, cap, m->q_heads, precision, st))) return rc;
+    const unsigned blocks = (unsigned)std::min<int64_t>((cap + 255) / 256, (int64_t)device_cus() * 8);
+    hipLaunchKernelGGL(k_first_hits, dim3(blocks), dim3(256), 0, st, G, R, *out, m->H, m->desc.dist_head, cap, m->q_list, ld, m->q_x,
+                       m->q_heads, n_list, m->q_rest, n_rest, stats);
+    R.rest_n = n_rest;
+    R.rest = m->q_rest;
+    return launch_fused(m, G, R, out, precision, stats, 0, st);
+}
+
+// Launches of so many rays are staged.
+constexpr int64_t kStageLeastRays = 1 << 14;
+
 int query_launch(const nif_model* m, const nif_grid* g, const nif_rays* r, int64_t n, const nif_hits* out,
                  uint32_t flags, int32_t precision, int64_t* stats, hipStream_t st) {
     if (n == 0) return NIF_OK;
@@ -187,6 +349,8 @@ int query_launch(const nif_model* m, const nif_grid* g, const nif_rays* r, int64
         hipLaunchKernelGGL(k_proxy, dim3((unsigned)blocks), dim3(256), 0, st, G, R, *out, stats);
         return check_hip(hipGetLastError(), "k_proxy launch");
     }
+    if (uses_panels(m) && n >= kStageLeastRays && n <= kStageRays && !(flags & (NIF_Q_POSE_ORDER | NIF_Q_POSE_TIMES)))
+        return query_staged(m, G, R, n, out, precision, stats, st);
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, st, m->counters, 8);
     if (flags & NIF_Q_POSE_ORDER) {
         hipLaunchKernelGGL(k_order_prefix, dim3(1), dim3(64), 0, st, R.off, R.n_poses, g->order_pre);
@@ -194,15 +358,7 @@ int query_launch(const nif_model* m, const nif_grid* g, const nif_rays* r, int64
     }
     const int pt = (flags & NIF_Q_POSE_TIMES) && stats ? 1 : 0;
     if (pt) hipLaunchKernelGGL(k_reset_pose_times, dim3(1), dim3(256), 0, st, stats, g->n_poses);
-    int rc;
-    const NetParams np = make_net_params(m, precision);
-    const int hw = m->desc.hidden_width;
-    const QueryShape sh{device_cus(), g_query_blocks_per_cu, g_query_rays_per_wave};
-    if (precision == NIF_PREC_FP32) rc = query_fp32(sh, hw, np, G, R, *out, m->counters, stats, pt, st);
-    else if (precision == NIF_PREC_BF16) rc = query_bf16(sh, hw, np, G, R, *out, m->counters, stats, pt, st);
-    else rc = query_fp16(sh, hw, np, G, R, *out, m->counters, stats, pt, st);
-    if (rc) return rc;
-    return check_hip(hipGetLastError(), "k_query launch");
+    return launch_fused(m, G, R, out, precision, stats, pt, st);
 }
 
 int set_query_blocks_per_cu(int v) {

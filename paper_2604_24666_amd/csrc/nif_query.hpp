@@ -16,6 +16,7 @@
 
 #include "nif_internal.hpp"
 #include "nif_net.hpp"
+#include "nif_panels.hpp"
 #include "nif_trace.hpp"
 
 namespace nif {
@@ -35,6 +36,10 @@ struct RayArgs {
     int32_t n_poses;
     int64_t n;
     const int64_t* order_pre;   // nullable: pose-ordered dealing, [8][n_poses + 1] (k_order_prefix)
+    // nullable: the rays are rest_n[0] entries of a staged query's list [4][kStageRays] instead: ray,
+    // packed voxel and entry t of its last segment (-1: none yet), its hit logit
+    const int32_t *rest_n, *rest;
+    int64_t least, most;        // of a list: the launch does nothing if it is shorter or longer
 };
 
 __device__ __forceinline__ Ray load_ray(const RayArgs& R, int64_t r) {
@@ -216,6 +221,7 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
     static_assert(RPW == 16 || RPW == 64, "rays per wave");
     constexpr int CB = kQueryCB;
     constexpr int PASSES = RPW / 16 / CB;
+    constexpr bool REST = RPW == 16 && !GAMMA && FD == 2;      // takes a staged query's list
     __shared__ int32_t s_park[QW_WORDS * 64];
     __shared__ float s_seg[64 * kSegStride];
     __shared__ float s_z[64 * kZStride];
@@ -236,15 +242,17 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
     // each pose's rays (positions counted in R.order_pre), so every XCD finishes pose p
     // before it starts pose p + 1.
     const int home = (int)(blockIdx.x & 7);
-    const int64_t span = (R.n + 7) / 8;
+    const int64_t n_rays = REST && R.rest_n ? *R.rest_n : R.n;
+    if (REST && n_rays < R.least) return;
+    const int64_t span = (n_rays + 7) / 8;
     const int64_t* opre = R.order_pre;
     auto range_of = [&](int id, int64_t& l, int64_t& h) {
         if (opre) {
             l = 0;
             h = opre[(int64_t)id * (R.n_poses + 1) + R.n_poses];
         } else {
-            l = std::min<int64_t>((int64_t)id * span, R.n);
-            h = std::min<int64_t>(l + span, R.n);
+            l = std::min<int64_t>((int64_t)id * span, n_rays);
+            h = std::min<int64_t>(l + span, n_rays);
         }
     };
     int cur = 0;                                   // ranges tried (wave-uniform); 8 = none left
@@ -304,14 +312,23 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
             if (m) {
                 const int leader = __ffsll((unsigned long long)m) - 1;
                 unsigned long long base = 0;
-                if (lane == leader) base = atomicAdd((unsigned long long*)&counters[rid], (unsigned long long)popc64(m));
-                base = __shfl(base, leader);
+                // a range that is not the wave's own, or few rays: look first, the atomics of a
+                // launch's waves on one counter go one after the other (3,072 waves past 8 ranges
+                // without a ray: 300 us)
+                bool dry = false;
+                if (REST && (cur > 0 || R.rest_n))
+                    dry = (int64_t)__hip_atomic_load((unsigned long long*)&counters[rid], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT) >= hi - lo;
+                if (lane == leader && !dry) base = atomicAdd((unsigned long long*)&counters[rid], (unsigned long long)popc64(m));
+                base = dry ? (unsigned long long)(hi - lo) : __shfl(base, leader);
                 if (need) {
                     // rank of the ray's first lane among those that take one
                     r = lo + (int64_t)base + popc64(m & ((1ull << (lane / SUB * SUB)) - 1ull));
                     if (r >= hi) {
                         r = -1;
                     } else {
+                        const int64_t at = r;        // in the staged query's list
+                        if (REST && R.rest_n) r = R.rest[at];
                         if (opre) {                  // position r of range rid -> (pose, ray)
                             const int64_t* pre = opre + (int64_t)rid * (R.n_poses + 1);
                             int a = 0, b = R.n_poses - 1;
@@ -330,6 +347,12 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
                         trav_init(P, ray, tv);
                         nq = 0;
                         last_z0 = -INFINITY;
+                        if (REST && R.rest_n && R.rest[kStageRays + at] >= 0) {
+                            tv.last_cell = R.rest[kStageRays + at];
+                            tv.last_a = __int_as_float(R.rest[2 * kStageRays + at]);
+                            last_z0 = __int_as_float(R.rest[3 * kStageRays + at]);
+                            nq = 1;
+                        }
                     }
                 }
                 if (lo + (int64_t)base + popc64(m) >= hi) {       // this range is used up: next one
@@ -384,11 +407,192 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
     if (stats) wave_add_stats(stats, n_done, n_eval, bad);
 }
 
+// The fused query for few rays: a block of four waves evaluates 16 rays' segments together.  A launch
+// of few rays takes its longest ray's chain of rounds, and a round the latency of its lookups and
+// layers: here each wave searches four of the rays with 16 lanes each, looks up every fourth batch of
+// levels, and computes a quarter of every layer (block_mlp); a wave of 16 rays does all of it in turn.
+// The features meet in LDS, in the operands' form; traversal state stays in registers.  Values and
+// results are those of k_query.
+template <int PREC>
+__host__ __device__ constexpr int feat_bytes() { return (int)sizeof(FeatOp<PREC>) * 64; }   // of one batch
+
+template <int HW, int PREC>
+__global__ void __launch_bounds__(256) k_query_block(NetParams np, GridArgs G, RayArgs R, nif_hits out, int64_t* __restrict__ counters,
+                                                     int64_t* __restrict__ stats) {
+    constexpr int SUB = 16;
+    extern __shared__ uint4 s_dyn[];                // features [batch][part][lane], 16 bytes each
+    __shared__ float s_h[2][16 * (HW + 4)];
+    __shared__ float s_seg[16 * kSegStride];
+    __shared__ float s_z[16 * kZStride];
+    constexpr int PARTS = feat_bytes<PREC>() / 1024;
+    const int w = threadIdx.x >> 6, lane = lane_id(), q = lane >> 4, j = lane & 15;
+    const int idx = w * 4 + lane / SUB;
+    const bool lead = lane % SUB == 0;
+    const int64_t n_rays = R.rest_n ? *R.rest_n : R.n;
+    if (n_rays > R.most) return;
+    const int home = (int)(blockIdx.x & 7);
+    const int64_t span = (n_rays + 7) / 8;
+    int cur = 0, rid = home;
+    int64_t lo = std::min<int64_t>((int64_t)rid * span, n_rays), hi = std::min<int64_t>(lo + span, n_rays);
+    const int L = np.enc.L, S = 1 + 2 * np.enc.F, C = 2 * S, U = (C + 3) >> 2, NLB = L >> 2, T = U * NLB;
+
+    int64_t r = -1, n_done = 0, n_eval = 0;
+    int pose = 0, nq = 0, bad = 0;
+    float last_z0 = -INFINITY;
+    bool has = false;
+    Ray ray;
+    ray.o = ray.d = make_float3(0.f, 0.f, 0.f);
+    PoseDev P;
+    P.kind = 0;
+    Trav tv;
+    tv.active = 0;
+    Segment sg;
+    sg.cell = -1; sg.a = sg.b = 0.f; sg.face = -1;
+    for (;;) {
+        // ---- give every ray a segment (as k_query)
+        for (;;) {
+            const bool need = cur < 8 && r < 0;
+            const uint64_t m = ballot(need && lead);
+            if (m) {
+                const int leader = __ffsll((unsigned long long)m) - 1;
+                unsigned long long base = 0;
+                bool dry = hi <= lo;
+                if (!dry && (cur > 0 || R.rest_n))
+                    dry = (int64_t)__hip_atomic_load((unsigned long long*)&counters[rid], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT) >= hi - lo;
+                if (lane == leader && !dry) base = atomicAdd((unsigned long long*)&counters[rid], (unsigned long long)popc64(m));
+                base = dry ? (unsigned long long)(hi - lo) : __shfl(base, leader);
+                if (need) {
+                    const int64_t at = lo + (int64_t)base + popc64(m & ((1ull << (lane / SUB * SUB)) - 1ull));
+                    if (at < hi) {
+                        r = R.rest_n ? R.rest[at] : at;
+                        pose = find_pose(R.off, R.n_poses, r);
+                        ray = load_ray(R, r);
+                        P = G.poses[pose];
+                        trav_init(P, ray, tv);
+                        nq = 0;
+                        last_z0 = -INFINITY;
+                        if (R.rest_n && R.rest[kStageRays + at] >= 0) {
+                            tv.last_cell = R.rest[kStageRays + at];
+                            tv.last_a = __int_as_float(R.rest[2 * kStageRays + at]);
+                            last_z0 = __int_as_float(R.rest[3 * kStageRays + at]);
+                            nq = 1;
+                        }
+                    }
+                }
+                if (lo + (int64_t)base + popc64(m) >= hi) {       // this range is used up: next one
+                    ++cur;
+                    rid = (home + cur) & 7;
+                    lo = std::min<int64_t>((int64_t)rid * span, n_rays);
+                    hi = std::min<int64_t>(lo + span, n_rays);
+                }
+            }
+            const bool search = r >= 0 && !has;
+            if (!ballot(search)) {
+                if (cur < 8 && ballot(r < 0)) continue;
+                break;
+            }
+            if (search) {
+                has = next_segment<SUB>(P, G.V, G.bin_start, G.bin_cells, G.N, ray, tv, sg, &bad);
+                if (has && R.tmax && sg.a >= R.tmax[r]) has = false;     // occlusion bound reached
+                if (!has) {
+                    if (lead) {
+                        write_miss(out, r, nq, last_z0);
+                        ++n_done;
+                    }
+                    r = -1;
+                }
+            }
+        }
+        if (!__syncthreads_or(has)) break;
+
+        // ---- rest-space segments, features, MLP
+        if (lead) {
+            float3 x0 = make_float3(0.5f, 0.5f, 0.5f), x1 = x0;
+            if (has) {
+                x0 = deform_inv(P, ray_at(ray, sg.a));
+                x1 = deform_inv(P, ray_at(ray, sg.b));
+            }
+            float* my = s_seg + idx * kSegStride;
+            my[0] = x0.x; my[1] = x0.y; my[2] = x0.z;
+            my[4] = x1.x; my[5] = x1.y; my[6] = x1.z;
+        }
+        __syncthreads();
+        PEWalk pw;
+        pw.p = -1;
+        pw.k = -1;
+        for (int u = 0; u < U; ++u) {
+            const int c_raw = q * U + u;
+            const bool live = c_raw < C;
+            const int c = live ? c_raw : 0;
+            uint32_t smp[3] = {0x80000000u, 0x80000000u, 0x80000000u};
+            if (live) {
+                double v[3];
+                pe_walk(s_seg + j * kSegStride, c, S, pw, v);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) smp[a] = to_fix32(v[a]);
+            }
+            for (int lb = 0; lb < NLB; ++lb) {
+                const int t = u * NLB + lb;
+                if ((t & 3) != w) continue;
+                FeatRaw fr;
+                float* feat = reinterpret_cast<float*>(fr.f);
+                const uint32_t soff = combo_set_offset(np.enc, c, S);
+                if (np.enc.f16) {
+                    lookup_levels<4, true>(np.enc, 4 * lb, smp, feat, soff);
+                } else {
+#pragma unroll
+                    for (int h = 0; h < 4; h += 2) lookup_levels<2, false>(np.enc, 4 * lb + h, smp, feat + 2 * h, soff);
+                }
+                if (!live)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) fr.f[k] = make_float2(0.f, 0.f);
+                const FeatOp<PREC> op = feat_op<PREC>(fr);
+                uint4 part[PARTS];
+                __builtin_memcpy(part, &op, sizeof(op));
+#pragma unroll
+                for (int k = 0; k < PARTS; ++k) s_dyn[(t * PARTS + k) * 64 + lane] = part[k];
+            }
+        }
+        __syncthreads();
+        block_mlp<HW, PREC, FeatOp<PREC>>(np, T, s_h, s_z, nullptr, 0, 0, [&](int t) {
+            uint4 part[PARTS];
+#pragma unroll
+            for (int k = 0; k < PARTS; ++k) part[k] = s_dyn[(t * PARTS + k) * 64 + lane];
+            FeatOp<PREC> op;
+            __builtin_memcpy(&op, part, sizeof(op));
+            return op;
+        });
+
+        // ---- results
+        if (has) {
+            ++nq;
+            if (lead) ++n_eval;
+            const float* z = s_z + idx * kZStride;
+            last_z0 = z[0];
+            if (z[0] > 0.f) {
+                const float* my = s_seg + idx * kSegStride;
+                if (lead) {
+                    write_hit(out, r, sg, make_float3(my[0], my[1], my[2]), make_float3(my[4], my[5], my[6]), z, nq, np.H - 8,
+                              np.dist_head, R.tmax ? R.tmax[r] : INFINITY, P);
+                    ++n_done;
+                }
+                r = -1;
+            }
+            has = false;
+        }
+    }
+    if (stats) wave_add_stats(stats, n_done, n_eval, bad);
+}
+
 // ------------------------------------------------------------------ launch
 
 // Below this many rays per compute unit a launch is latency-bound (the serial chain of
 // network rounds of its longest rays sets the time), and 16-ray waves finish it sooner.
 constexpr int64_t kSmallLaunchRaysPerCU = 8192;
+// Up to this many, blocks of four waves per 16 rays.
+constexpr int64_t kBlockRaysPerCU = 64;
+constexpr int kBlockFeatBytes = 112 * 1024;
 
 // Launch shape of the fused query: compute units, one-wave workgroups per unit, rays per wave
 // (0 = by launch size, else 16 or 64).
@@ -397,10 +601,22 @@ struct QueryShape {
 };
 
 template <int HW, int PREC>
-static void launch_query(const QueryShape& sh, const NetParams& np, const GridArgs& G, const RayArgs& R, const nif_hits& out, int64_t* ctr,
+static void launch_query(const QueryShape& sh, const NetParams& np, const GridArgs& G, RayArgs R, const nif_hits& out, int64_t* ctr,
                          int64_t* stats, int pt, hipStream_t st) {
     int rpw = sh.rays_per_wave;
-    if (rpw == 0) rpw = R.n < kSmallLaunchRaysPerCU * sh.cus ? 16 : 64;
+    if (rpw == 0 || R.rest_n) rpw = R.n < kSmallLaunchRaysPerCU * sh.cus || R.rest_n ? 16 : 64;
+    // Blocks of 16 rays: few rays, or the part of a staged query's rest that is few.
+    const bool plain = np.gamma_F < 0 && np.enc.Fd == 2 && !R.order_pre && !pt && rpw == 16;
+    const int feat = (((2 * (1 + 2 * np.enc.F)) + 3) >> 2) * (np.enc.L >> 2) * feat_bytes<PREC>();
+    const int64_t few = (int64_t)sh.cus * kBlockRaysPerCU;
+    if (plain && feat <= kBlockFeatBytes && (R.rest_n || R.n <= few)) {
+        RayArgs B = R;
+        if (R.rest_n) B.most = few;
+        const int64_t blocks = std::min<int64_t>((std::min(R.n, few) + 15) / 16, (int64_t)sh.cus * 3);
+        hipLaunchKernelGGL((k_query_block<HW, PREC>), dim3((unsigned)blocks), dim3(256), feat, st, np, G, B, out, ctr, stats);
+        if (!R.rest_n || R.n <= few) return;
+        R.least = few + 1;
+    }
     const int64_t waves = (R.n + rpw - 1) / rpw;
     const int64_t blocks = std::max<int64_t>(std::min<int64_t>(waves, (int64_t)sh.cus * sh.blocks_per_cu), 1);
     if (np.gamma_F >= 0 || np.enc.Fd == 3) {     // the method variants: one launch shape
