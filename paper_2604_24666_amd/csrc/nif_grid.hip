@@ -182,14 +182,15 @@ __global__ void __launch_bounds__(256) k_chunk_sums(const PoseDev* __restrict__ 
     if (threadIdx.x == 0) sums[(int64_t)blockIdx.y * max_chunks + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-__global__ void __launch_bounds__(256) k_scan(const PoseDev* __restrict__ poses, const int32_t* __restrict__ counts,
+// Leaves the counts cleared (the fill's cursors).
+__global__ void __launch_bounds__(256) k_scan(const PoseDev* __restrict__ poses, int32_t* __restrict__ counts,
                                               const int32_t* __restrict__ sums, int max_chunks, int32_t* __restrict__ start,
                                               int32_t* __restrict__ totals) {
     const int p = blockIdx.y, T = threadIdx.x;
     const PoseDev P = poses[p];
     const int64_t n = pose_bins(P), a = (int64_t)blockIdx.x * kScanChunk;
     if (a >= n) return;
-    const int32_t* c = counts + P.bin_off;
+    int32_t* c = counts + P.bin_off;
     int32_t* s = start + P.bin_off;
     __shared__ int32_t part[256], before[256];
     int32_t pre = 0;                                   // the chunks before this one
@@ -200,6 +201,7 @@ __global__ void __launch_bounds__(256) k_scan(const PoseDev* __restrict__ poses,
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         v[k] = i0 + k < n ? c[i0 + k] : 0;
+        if (i0 + k < n) c[i0 + k] = 0;
         sum += v[k];
     }
     part[T] = sum;
@@ -299,7 +301,7 @@ __device__ inline void sort_list(int32_t* __restrict__ l, int32_t n) {
 // Sort each bin's list by packed voxel, that is by voxel id, so that the build is deterministic
 // (insertion sort; lists are short).  A block takes 128 neighbouring bins, whose lists are one range
 // of the references: it is sorted in LDS where it fits, so that the chains of a sort are LDS reads.
-constexpr int kSortBins = 128, kSortRefs = 6144;
+constexpr int kSortBins = 128, kSortRefs = 3072;
 __global__ void __launch_bounds__(kSortBins) k_bin_sort(const PoseDev* __restrict__ poses, const int32_t* __restrict__ start,
                                                         int32_t* __restrict__ cells) {
     __shared__ int32_t s_ref[kSortRefs];
@@ -374,7 +376,6 @@ static int grid_rebin(nif_grid* g, bool fill, hipStream_t st) {
     hipLaunchKernelGGL(k_ref_offsets, dim3(1), dim3(64), 0, st, g->poses, P, sc_totals(g), fill ? g->ref_capacity : (int64_t)0,
                        sc_overflow(g));
     if (fill && n_occ > 0) {
-        hipLaunchKernelGGL(k_fill_i32, dim3(1024), dim3(256), 0, st, g->counts, g->bin_total, 0);
         hipLaunchKernelGGL(k_bin_fill, dim3(occ_blk, P), dim3(256), 0, st, g->poses, g->verts, N, g->list, n_occ,
                            g->bin_start, g->counts, g->bin_cells);
         hipLaunchKernelGGL(k_bin_sort, dim3((unsigned)((g->max_bins + kSortBins - 1) / kSortBins), P), dim3(kSortBins), 0, st, g->poses,

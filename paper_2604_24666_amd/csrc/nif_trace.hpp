@@ -215,8 +215,8 @@ __device__ __forceinline__ void leave_bin(const BinWalk& B, Trav& T) {
 constexpr int kBinsPerStep = 3;
 
 // Next occupied segment after T.last in front-to-back order (the same result in the SUB lanes of
-// the ray).  Bins that end before the last segment are passed over: a walk restarted with T.last goes
-// on where it was.  Returns false when the ray has left the grid.  *bad counts degenerate voxel tests.
+// the ray).  Bins that end before the last segment are passed over (SUB > 1): a walk restarted with
+// T.last goes on where it was.  Returns false when the ray has left the grid.  *bad counts degenerate voxel tests.
 template <int SUB>
 __device__ __forceinline__ bool next_segment(const PoseDev& P, const float4* __restrict__ V,
                                              const int32_t* __restrict__ bin_start,
@@ -228,7 +228,7 @@ __device__ __forceinline__ bool next_segment(const PoseDev& P, const float4* __r
     int32_t best_c = 0x7fffffff, best_f = -1;
     BinWalk B;
     open_bin(P, bin_start, T, B);
-    int32_t e = B.t_hi > T.last_a ? B.s0 : B.s1;
+    int32_t e = SUB == 1 || B.t_hi > T.last_a ? B.s0 : B.s1;
     for (;;) {
         if (e < B.s1) {
             if (SUB == 1 || e + sub < B.s1) {
@@ -267,7 +267,7 @@ __device__ __forceinline__ bool next_segment(const PoseDev& P, const float4* __r
             if (B.last) { T.active = 0; return false; }
             leave_bin(B, T);
             open_bin(P, bin_start, T, B);
-            e = B.t_hi > T.last_a ? B.s0 : B.s1;
+            e = SUB == 1 || B.t_hi > T.last_a ? B.s0 : B.s1;
             if (e < B.s1) break;
         }
     }
