@@ -38,13 +38,13 @@ HBM_PEAK_GBS = 8000.0
 # were taken on and the ray generator of the workload (SHA-256 of KQUERY_SOURCES); otherwise the
 # traffic is reported as null.
 KQUERY_SOURCES = ["paper_2604_24666_amd/csrc/nif_query.hip", "paper_2604_24666_amd/csrc/nif_query.hpp",
-                  "paper_2604_24666_amd/csrc/nif_query_fp32.hip", "paper_2604_24666_amd/csrc/nif_net.hpp",
+                  "paper_2604_24666_amd/csrc/nif_query_fp32.hip", "paper_2604_24666_amd/csrc/nif_net.hpp", "paper_2604_24666_amd/csrc/nif_panels.hpp",
                   "paper_2604_24666_amd/csrc/nif_trace.hpp", "paper_2604_24666_amd/csrc/nif_device.hpp",
                   "paper_2604_24666_amd/csrc/nif_internal.hpp", "paper_2604_24666_amd/build.py",
                   "nif_synth/__init__.py"]
 KQUERY_TRAFFIC = {
-    "sources_sha256": "7bb9c2a0530250ba2433426a0daaf766a3013fcd580931cd0dedcc63e86ea54a",
-    "fetch_kib": 1.04862e8, "write_kib": 1.93924e6,         # per k_query<64, FP32, 64> launch, default workload
+    "sources_sha256": "e9e0157825aad5b42b34d0d98341219e2045d5d652bce9163897f80638d9d142",
+    "fetch_kib": 1.05251e8, "write_kib": 2.62779e6,         # per k_query<64, FP32, 64> launch, default workload
     "fetch_scale": 1048576 / 524303, "write_scale": 1048576 / 1048577,   # 1 GiB copy reads 524,303 / writes 1,048,577 KiB
 }
 
