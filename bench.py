@@ -43,7 +43,7 @@ KQUERY_SOURCES = ["paper_2604_24666_amd/csrc/nif_query.hip", "paper_2604_24666_a
                   "paper_2604_24666_amd/csrc/nif_internal.hpp", "paper_2604_24666_amd/build.py",
                   "nif_synth/__init__.py"]
 KQUERY_TRAFFIC = {
-    "sources_sha256": "e9e0157825aad5b42b34d0d98341219e2045d5d652bce9163897f80638d9d142",
+    "sources_sha256": "bdf5d7f254312b64bdf9b4ca3160ae8f075bea281b05b1ab4800ffccb22c35e9",
     "fetch_kib": 1.05251e8, "write_kib": 2.62779e6,         # per k_query<64, FP32, 64> launch, default workload
     "fetch_scale": 1048576 / 524303, "write_scale": 1048576 / 1048577,   # 1 GiB copy reads 524,303 / writes 1,048,577 KiB
 }
