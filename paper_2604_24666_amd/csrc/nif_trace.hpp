@@ -327,7 +327,8 @@ __device__ __forceinline__ void all_segments(const PoseDev& P, const float4* __r
             for (int o = 1; o < SUB; o <<= 1) {
                 const float a = __shfl_xor(lim_a, o);
                 const int32_t c = __shfl_xor(lim_c, o);
-                any = any || __shfl_xor((int)any, o);
+                const int other = __shfl_xor((int)any, o);           // by every lane: not behind ||, which would leave
+                any = any || other != 0;                             // the lanes that spilled out of the exchange
                 if (a < lim_a || (a == lim_a && c < lim_c)) { lim_a = a; lim_c = c; }
             }
             for (;;) {
