@@ -1319,9 +1319,10 @@ template <int KB>
 __global__ void __launch_bounds__(kTgBlock) k_tg_fill(EncBwdParams P, const int32_t* __restrict__ total,
                                                  const float2* __restrict__ dE, int64_t pn) {
     constexpr int NR = 4 * kTgBlock * KB;
-    // [2][sets][NBL]: first free slot per bucket, end of the free slots; then the batch's buckets:
-    // [nh] records, [nh] (first sorted place, first slot)
-    extern __shared__ int32_t s_dyn[];
+    // the batch's buckets, [nh] (first sorted place, first slot) and [nh] records, and between them
+    // [2][sets][NBL]: first free slot per bucket, end of the free slots.  The pairs come first, where
+    // the array's type keeps them on 8 bytes.
+    extern __shared__ int2 s_at[];
     __shared__ float4 s_rec[NR];
     __shared__ uint16_t s_bkt[NR];
     __shared__ int32_t s_n;
@@ -1330,10 +1331,9 @@ __global__ void __launch_bounds__(kTgBlock) k_tg_fill(EncBwdParams P, const int3
     const bool sets = P.enc.set_stride != 0;
     const int nloc = P.NBL * n_table_sets(P), nh = sets ? KB * P.NBL : P.NBL;
     const uint32_t kmask = (1u << P.SB) - 1u, tmask = (1u << P.enc.log2T) - 1u;
-    int32_t* s_cur = s_dyn;
-    int32_t* s_end = s_dyn + nloc;
+    int32_t* s_cur = reinterpret_cast<int32_t*>(s_at + nh);
+    int32_t* s_end = s_cur + nloc;
     int32_t* s_hist = s_end + nloc;
-    int2* s_at = reinterpret_cast<int2*>(s_hist + nh);
     const int64_t n_cnt = (int64_t)P.n_buckets * P.n_blk;
     for (int i = tid; i < nloc; i += kTgBlock) {
         const int64_t k = level_bucket_global(P, y, i) * P.n_blk + bx;
