@@ -947,7 +947,12 @@ constexpr size_t kFillLdsMax = 60 * 1024;
 __device__ __forceinline__ int64_t level_bucket_global(const EncBwdParams& P, int y, int i) {
     return ((int64_t)(i / P.NBL) * P.n_lev + y) * P.NBL + i % P.NBL;
 }
-__device__ __forceinline__ int n_table_sets(const EncBwdParams& P) { return P.enc.set_stride ? P.S : 1; }
+__host__ __device__ __forceinline__ int n_table_sets(const EncBwdParams& P) { return P.enc.set_stride ? P.S : 1; }
+// Buckets that KB combinations of one level can meet in the fill: those of each combination's set, or
+// of the one set they share (also with a table set per sample where there is one sample).
+__host__ __device__ __forceinline__ int batch_buckets(const EncBwdParams& P, int KB) {
+    return n_table_sets(P) > 1 ? KB * P.NBL : P.NBL;
+}
 // Table set of PE combination c (point-major).
 __device__ __forceinline__ int combo_set(const EncBwdParams& P, int c) {
     return P.enc.set_stride ? (c >= P.S ? c - P.S : c) : 0;
@@ -1328,8 +1333,8 @@ __global__ void __launch_bounds__(kTgBlock) k_tg_fill(EncBwdParams P, const int3
     __shared__ int32_t s_n;
     const int tid = threadIdx.x, y = (int)blockIdx.y, l = P.lev[y];
     const int bx = (int)blockIdx.x + P.blk0;
-    const bool sets = P.enc.set_stride != 0;
-    const int nloc = P.NBL * n_table_sets(P), nh = sets ? KB * P.NBL : P.NBL;
+    const bool sets = n_table_sets(P) > 1;
+    const int nloc = P.NBL * n_table_sets(P), nh = batch_buckets(P, KB);
     const uint32_t kmask = (1u << P.SB) - 1u, tmask = (1u << P.enc.log2T) - 1u;
     int32_t* s_cur = reinterpret_cast<int32_t*>(s_at + nh);
     int32_t* s_end = s_cur + nloc;
@@ -2095,14 +2100,13 @@ static EncBwdParams table_grad_params(nif_model* m, const float* x0, const float
     const int log2T = m->desc.log2_table;
     ep.SB = log2T <= 12 ? log2T : std::max(12, log2T - 8);
     ep.NBL = 1 << (log2T - ep.SB);
-    const int n_sets = m->desc.per_sample_tables ? m->S : 1;
     const DirectPlan D = direct_plan(m, ep.enc);
     ep.n_lev = 0;
     for (int l = 0, k = 0; l < m->desc.levels; ++l) {
         if (k < D.n && D.lev[k] == l) { ++k; continue; }
         ep.lev[ep.n_lev++] = (uint8_t)l;
     }
-    ep.n_buckets = ep.n_lev * n_sets * ep.NBL;
+    ep.n_buckets = ep.n_lev * n_table_sets(ep) * ep.NBL;
     ep.cnt = m->bwd_cnt; ep.val = m->bwd_val;
     ep.cap = m->bwd_round * 2 * m->S * m->desc.levels * 8;
     ep.vmax = nullptr;
@@ -2147,12 +2151,11 @@ static TgRound tg_begin(nif_model* m, EncBwdParams ep, int64_t c0, int64_t n, hi
     R.total = m->bwd_scan + n_chunks;
     R.parts = R.total + 1;
     ep.vmax = reinterpret_cast<uint32_t*>(R.parts + ep.n_buckets + 1);
-    const int n_sets = m->desc.per_sample_tables ? m->S : 1;
     R.ep = ep;
     if (m->desc.feat_dim == 2) hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(64), 0, sd, reinterpret_cast<float*>(ep.vmax), (int64_t)1);
     if (ep.n_lev == 0) return R;
     const dim3 fg((unsigned)ep.n_blk, (unsigned)ep.n_lev);
-    const size_t lds_f = sizeof(int32_t) * (size_t)ep.NBL * n_sets;
+    const size_t lds_f = sizeof(int32_t) * (size_t)ep.NBL * n_table_sets(ep);
     if (m->desc.feat_dim == 2) hipLaunchKernelGGL(k_tg_count, fg, dim3(kTgBlock), lds_f, sd, ep);
     else hipLaunchKernelGGL(k_enc_bwd_count3, fg, dim3(256), lds_f, sd, ep);
     hipLaunchKernelGGL(k_scan_sums, dim3(n_chunks), dim3(256), 0, sd, ep.cnt, n_cnt, sums);
@@ -2182,9 +2185,8 @@ static void tg_fill(nif_model* m, const TgRound& R, const float* delta, int64_t 
     ep.blk0 = (int32_t)((c0 - ep.c0) / per_blk);
     const int64_t blk1 = std::min<int64_t>(ep.n_blk, (c0 + n - ep.c0 + per_blk - 1) / per_blk);
     const int hw = m->desc.hidden_width;
-    const int n_sets = m->desc.per_sample_tables ? m->S : 1;
     const dim3 fg((unsigned)(blk1 - ep.blk0), (unsigned)ep.n_lev);
-    const int nloc = ep.NBL * n_sets;
+    const int nloc = ep.NBL * n_table_sets(ep);
     const size_t lds_f = sizeof(int32_t) * (size_t)nloc;
     if (m->desc.feat_dim == 2) {
         switch (hw) {
@@ -2220,7 +2222,7 @@ static void tg_fill(nif_model* m, const TgRound& R, const float* delta, int64_t 
         }
         if (ep.n_lev > 0)
             hipLaunchKernelGGL(k_tg_fill<kTgBatch>, fg, dim3(kTgBlock),
-                               2 * lds_f + sizeof(int32_t) * 3 * (size_t)ep.NBL * (n_sets > 1 ? kTgBatch : 1), sd, ep, R.total, dE, panel_stride(n));
+                               2 * lds_f + sizeof(int32_t) * 3 * (size_t)batch_buckets(ep, kTgBatch), sd, ep, R.total, dE, panel_stride(n));
         return;
     }
     // three features: the staged first-layer rows, 4 per PE combination, hw + 4 floats each
