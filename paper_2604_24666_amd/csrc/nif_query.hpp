@@ -14,6 +14,7 @@
 #include <cmath>
 #include <cstring>
 
+#include "nif_deal.hpp"
 #include "nif_internal.hpp"
 #include "nif_net.hpp"
 #include "nif_panels.hpp"
@@ -310,20 +311,12 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
             const bool need = cur < 8 && r < 0;
             const uint64_t m = ballot(need && lead);
             if (m) {
-                const int leader = __ffsll((unsigned long long)m) - 1;
-                unsigned long long base = 0;
-                // a range that is not the wave's own, or few rays: look first, the atomics of a
-                // launch's waves on one counter go one after the other (3,072 waves past 8 ranges
-                // without a ray: 300 us)
-                bool dry = false;
-                if (REST && (cur > 0 || R.rest_n))
-                    dry = (int64_t)__hip_atomic_load((unsigned long long*)&counters[rid], __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT) >= hi - lo;
-                if (lane == leader && !dry) base = atomicAdd((unsigned long long*)&counters[rid], (unsigned long long)popc64(m));
-                base = dry ? (unsigned long long)(hi - lo) : __shfl(base, leader);
+                // a range that is not the wave's own, or few rays: look first
+                const int64_t base = take_tickets(&counters[rid], hi - lo, popc64(m), __ffsll((unsigned long long)m) - 1,
+                                                  REST && (cur > 0 || R.rest_n));
                 if (need) {
                     // rank of the ray's first lane among those that take one
-                    r = lo + (int64_t)base + popc64(m & ((1ull << (lane / SUB * SUB)) - 1ull));
+                    r = lo + base + popc64(m & ((1ull << (lane / SUB * SUB)) - 1ull));
                     if (r >= hi) {
                         r = -1;
                     } else {
@@ -355,7 +348,7 @@ __global__ void __launch_bounds__(64, NIF_QUERY_MIN_WAVES) k_query(NetParams np,
                         }
                     }
                 }
-                if (lo + (int64_t)base + popc64(m) >= hi) {       // this range is used up: next one
+                if (lo + base + popc64(m) >= hi) {       // this range is used up: next one
                     ++cur;
                     rid = (home + cur) & 7;
                     range_of(rid, lo, hi);
@@ -454,16 +447,10 @@ __global__ void __launch_bounds__(256) k_query_block(NetParams np, GridArgs G, R
             const bool need = cur < 8 && r < 0;
             const uint64_t m = ballot(need && lead);
             if (m) {
-                const int leader = __ffsll((unsigned long long)m) - 1;
-                unsigned long long base = 0;
-                bool dry = hi <= lo;
-                if (!dry && (cur > 0 || R.rest_n))
-                    dry = (int64_t)__hip_atomic_load((unsigned long long*)&counters[rid], __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT) >= hi - lo;
-                if (lane == leader && !dry) base = atomicAdd((unsigned long long*)&counters[rid], (unsigned long long)popc64(m));
-                base = dry ? (unsigned long long)(hi - lo) : __shfl(base, leader);
+                const int64_t base = take_tickets(&counters[rid], hi - lo, popc64(m), __ffsll((unsigned long long)m) - 1,
+                                                  cur > 0 || R.rest_n);
                 if (need) {
-                    const int64_t at = lo + (int64_t)base + popc64(m & ((1ull << (lane / SUB * SUB)) - 1ull));
+                    const int64_t at = lo + base + popc64(m & ((1ull << (lane / SUB * SUB)) - 1ull));
                     if (at < hi) {
                         r = R.rest_n ? R.rest[at] : at;
                         pose = find_pose(R.off, R.n_poses, r);
@@ -480,7 +467,7 @@ __global__ void __launch_bounds__(256) k_query_block(NetParams np, GridArgs G, R
                         }
                     }
                 }
-                if (lo + (int64_t)base + popc64(m) >= hi) {       // this range is used up: next one
+                if (lo + base + popc64(m) >= hi) {       // this range is used up: next one
                     ++cur;
                     rid = (home + cur) & 7;
                     lo = std::min<int64_t>((int64_t)rid * span, n_rays);

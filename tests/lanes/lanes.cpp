@@ -1,11 +1,13 @@
 // CPU emulation of the lanes that share a ray: the library's own traversal (nif_trace.hpp), compiled
 // for the host, on a bin grid built here.  Compares the segments of all_segments<SUB> and of repeated
-// next_segment<SUB> calls with repeated next_segment<1> calls, ray by ray.
+// next_segment<SUB> calls with repeated next_segment<1> calls, ray by ray.  And of the lanes of a wave
+// that takes rays from a counter which other waves move meanwhile (nif_deal.hpp).
 #include <ucontext.h>
 
 #include <memory>
 #include <vector>
 
+#include "nif_deal.hpp"
 #include "nif_trace.hpp"
 
 namespace lanes {
@@ -38,6 +40,20 @@ uint64_t exchange(int site, uint64_t v, int from) {
     return l.result;
 }
 
+static uint64_t g_others = 0, g_taken = 0;
+
+uint64_t counter_read(const unsigned long long* c) {
+    const uint64_t v = *c;
+    *const_cast<unsigned long long*>(c) += g_others;
+    return v;
+}
+uint64_t counter_add(unsigned long long* c, unsigned long long n) {
+    const uint64_t v = *c;
+    *c += n + g_others;
+    g_taken += n;
+    return v;
+}
+
 static void enter() {
     g_body(g_arg);
     g_lane[g_cur].done = true;
@@ -66,7 +82,9 @@ static bool run(int n, void (*body)(void*), void* arg) {
         for (int i = 1; i < n; ++i)
             if (g_lane[i].done != g_lane[0].done || (!g_lane[0].done && g_lane[i].site != g_lane[0].site)) return false;
         if (g_lane[0].done) return true;
-        for (int i = 0; i < n; ++i) g_lane[i].result = g_lane[g_lane[i].from].value;
+        uint64_t mask = 0;
+        for (int i = 0; i < n; ++i) mask |= (g_lane[i].value & 1) << i;
+        for (int i = 0; i < n; ++i) g_lane[i].result = g_lane[i].from < 0 ? mask : g_lane[g_lane[i].from].value;
     }
 }
 
@@ -236,4 +254,32 @@ extern "C" int lanes_check(int N, const uint8_t* occ, int kind, float s, int bin
         }
     }
     return 0;
+}
+
+namespace lanes {
+struct Take {
+    int64_t counter, size;
+    int n, leader;
+    bool look;
+    int64_t base[kMax];
+};
+static void take_body(void* p) {
+    Take& t = *static_cast<Take*>(p);
+    t.base[current()] = nif::take_tickets(&t.counter, t.size, t.n, t.leader, t.look);
+}
+}  // namespace lanes
+
+// A wave of 64 lanes takes n tickets of a counter at `at` of a range of `size` rays, while other waves
+// take `others` between any two accesses.  Returns the tickets' first one, -1 if the lanes came apart
+// or differ, -2 if the counter moved by other than n for this wave (or 0 where nothing was left).
+extern "C" int64_t lanes_take(int64_t at, int64_t size, int n, int leader, int look, int64_t others) {
+    using namespace lanes;
+    Take t{at, size, n, leader, look != 0, {}};
+    g_others = (uint64_t)others;
+    g_taken = 0;
+    if (!run(64, take_body, &t)) return -1;
+    for (int i = 1; i < 64; ++i)
+        if (t.base[i] != t.base[0]) return -1;
+    if (g_taken != (uint64_t)n && !(g_taken == 0 && t.base[0] >= size)) return -2;
+    return t.base[0];
 }

@@ -1,7 +1,7 @@
 """The lanes that share a ray in the traversal must keep together and find what one lane finds alone,
 also where a lane meets more segments in a bin than it has slots for (its ray then goes over the bin's
 list again): coarse bins and filled occupancies.  On the CPU the library's own traversal header runs
-lane by lane (tests/lanes) against repeated one-lane steps, bit for bit; on the GPU nif_trace on grids
+lane by lane (tests/lanes) against repeated one-lane steps, bit for bit, as do the lanes of a wave that takes rays; on the GPU nif_trace on grids
 whose rays spill, 8 and 16 lanes a ray, must give the segments of fine bins and of the oracle."""
 import ctypes as C
 import os
@@ -17,19 +17,22 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 @pytest.fixture(scope="module")
-def lanes(tmp_path_factory):
+def lib(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("lanes") / "liblanes.so")
     src = os.path.join(_HERE, "lanes")
     subprocess.run(["g++", "-O2", "-std=c++17", "-ffp-contract=off", "-fPIC", "-shared", "-Wno-unknown-pragmas", "-I" + src,
                     "-I" + os.path.join(_HERE, "..", "paper_2604_24666_amd", "csrc"), "-o", so, os.path.join(src, "lanes.cpp")],
                    check=True)
-    L = C.CDLL(so)
+    return C.CDLL(so)
 
+
+@pytest.fixture(scope="module")
+def lanes(lib):
     def check(N, occ, kind, s, bins, sub, o, d):
         o, d = (np.ascontiguousarray(v, dtype=np.float32) for v in (o, d))
         n = o.shape[1]
         res, spilled = np.zeros(6, np.int64), np.zeros(n, np.uint8)
-        rc = L.lanes_check(C.c_int(N), occ.ctypes.data_as(C.c_void_p), C.c_int(kind), C.c_float(s), C.c_int(bins), C.c_int(sub),
+        rc = lib.lanes_check(C.c_int(N), occ.ctypes.data_as(C.c_void_p), C.c_int(kind), C.c_float(s), C.c_int(bins), C.c_int(sub),
                            C.c_int64(n), o.ctypes.data_as(C.c_void_p), d.ctypes.data_as(C.c_void_p),
                            res.ctypes.data_as(C.c_void_p), spilled.ctypes.data_as(C.c_void_p))
         assert rc == 0
@@ -63,6 +66,20 @@ def test_lanes_of_a_ray_keep_together_on_a_surface(lanes, orc, bins, sub):
     say(f"lanes {sub}, torus surface bins={bins}: {got}")
     assert got["segments"] > 0
     assert not (got["apart"] or got["other"] or got["next_apart"] or got["next_other"])
+
+
+@pytest.mark.parametrize("look", [0, 1])
+def test_lanes_of_a_wave_take_the_same_tickets(lib, look):
+    """The counter moves past the end of the range while the wave takes its rays: all lanes must hold the
+    same tickets (some would else leave out or repeat rays), and none is taken twice."""
+    lib.lanes_take.restype = C.c_int64
+    for size in (0, 1, 40, 1000):
+        for at in sorted({0, max(0, size - 70), max(0, size - 1), size, size + 5}):
+            for n in (1, 4, 64):
+                for leader in (0, 4, 63):
+                    for others in (0, 1, 3, 64):
+                        base = lib.lanes_take(C.c_int64(at), C.c_int64(size), n, leader, look, C.c_int64(others))
+                        assert base >= min(at, size), (size, at, n, leader, others, base)
 
 
 @pytest.mark.gpu
