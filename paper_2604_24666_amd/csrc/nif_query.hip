@@ -19,9 +19,11 @@ __global__ void k_reset_pose_times(int64_t* stats, int n_poses) {
 // SUB lanes a ray: the time of a launch is that of the longest rays' chains of bins and voxel tests
 // (2^17 random rays through 8 poses of the 128^3 blob scene: 5.3 ms with one lane, 1.66 with four,
 // 1.60 with eight, 1.78 with sixteen; 3,000 rays: 0.52, 0.38 and 0.27 with four, eight, sixteen).
+// Four waves per SIMD: the form of 16 lanes takes 129 registers by itself, one above that line (16,300
+// rays 433 us, 395 with 128 registers and 12 bytes of scratch).
 // points: the rest-space end points are written here; else k_trace_points forms them from t_in, t_out.
 template <int SUB>
-__global__ void __launch_bounds__(64) k_trace(GridArgs G, RayArgs R, int64_t r0, int32_t max_seg, nif_segments out,
+__global__ void __launch_bounds__(64, 4) k_trace(GridArgs G, RayArgs R, int64_t r0, int32_t max_seg, nif_segments out,
                                                int points) {
     const int64_t r = r0 + (int64_t)blockIdx.x * (64 / SUB) + threadIdx.x / SUB;
     if (r >= R.n) return;

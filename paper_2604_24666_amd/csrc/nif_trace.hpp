@@ -205,9 +205,15 @@ __device__ __forceinline__ void open_bin(const PoseDev& P, const int32_t* __rest
 
 __device__ __forceinline__ void leave_bin(const BinWalk& B, Trav& T) {
     T.t_lo = B.t_hi;
-    if (B.ax == 0) { T.ix += T.sx; T.tmx += T.tdx; }
-    else if (B.ax == 1) { T.iy += T.sy; T.tmy += T.tdy; }
-    else { T.iz += T.sz; T.tmz += T.tdz; }
+    // by value: three conditional updates in place are merged through a selected address, which keeps
+    // the state in scratch
+    const bool x = B.ax == 0, y = B.ax == 1, z = B.ax == 2;
+    T.ix = x ? T.ix + T.sx : T.ix;
+    T.iy = y ? T.iy + T.sy : T.iy;
+    T.iz = z ? T.iz + T.sz : T.iz;
+    T.tmx = x ? T.tmx + T.tdx : T.tmx;
+    T.tmy = y ? T.tmy + T.tdy : T.tmy;
+    T.tmz = z ? T.tmz + T.tdz : T.tmz;
 }
 
 // Empty bins a ray may pass in one step of the flat loop (a step over a bin costs a list lookup,

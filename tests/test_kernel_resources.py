@@ -21,3 +21,16 @@ def test_pairs_in_dynamic_lds_are_aligned(kernels):
     ends."""
     for name, k in _named(kernels, "9k_tg_fill").items():
         assert k["lds"] % 8 == 0, (name, k)
+
+
+def test_traversal_state_stays_in_registers(kernels):
+    """Bin steps that update the walk in place through a selected address put it into scratch (16 bytes a
+    lane in every kernel below).  The 64-ray waves at width 64 and the tracing with 16 lanes a ray use all
+    the registers they are given and may spill 12 bytes, none of them the walk's."""
+    for part, limit in (("7k_traceILi8E", 0), ("7k_traceILi16E", 12), ("7k_first", 0), ("7k_proxy", 0), ("13k_query_block", 0)):
+        for name, k in _named(kernels, part).items():
+            assert k["scratch"] <= limit, (name, k)
+    for width, limit in ((16, 0), (32, 0), (64, 12)):
+        for rays in (16, 64):
+            for name, k in _named(kernels, f"7k_queryILi{width}ELi0ELi{rays}ELb0ELi2E").items():
+                assert k["scratch"] <= limit, (name, k)
