@@ -280,11 +280,13 @@ int nif_set_query_rays_per_wave(int32_t rays_per_wave);
  * stream.  n_bytes: a multiple of 16 in [4096, 2^33] (memory kinds); n_ops in [1, 2^40]. */
 enum { NIF_MB_HBM_READ = 0, NIF_MB_GATHER4 = 1, NIF_MB_GATHER8 = 2, NIF_MB_MFMA_F32 = 3, NIF_MB_MFMA_BF16 = 4 };
 int nif_microbench(int32_t kind, int64_t n_bytes, int64_t n_ops, int32_t reps, double* result, nif_stream stream);
-/* Autotuner of the fused query's launch shape: runs nif_query on the caller's rays (flags 0,
- * no stats) once to warm up and `reps` times timed with device events, for every pair of
- * workgroups per CU in {4, 6, 8, 10, 12, 14, 16, 20, 24} and rays per wave in {16, 64}; keeps
+/* Autotuner of the fused query's launch shape: runs the fused query on the caller's rays (flags 0,
+ * no stats; all rays, also where nif_query evaluates first segments in stages) once to warm up and
+ * `reps` times timed with device events, for every pair of
+ * workgroups per CU in {4, 6, 8, 10, 12, 14, 16, 20, 24} and rays per wave in {16, 64}, but no
+ * number of workgroups that makes the same launch as the present one; keeps
  * the fastest pair process-wide (as the two setters above would) and returns it in
- * best[0] (workgroups per CU), best[1] (rays per wave), with its time per launch in
+ * best[0] (workgroups per CU), best[1] (rays per wave), with nif_query's time per launch in
  * *best_ms (nullable).  Outputs are those of the last launch (they do not depend on the
  * shape).  Synchronises the stream; not for graph capture.  On an error the previous shape
  * is kept. */

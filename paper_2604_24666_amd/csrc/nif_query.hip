@@ -343,6 +343,10 @@ static int query_staged(const nif_model* m, const GridArgs& G, RayArgs R, int64_
 // in 64-ray waves: 25 M camera rays 26.2 ms fused, 27.0 in stages of 2^21.
 constexpr int64_t kStageLeastRays = 1 << 14;
 
+static bool staged(const nif_model* m, int64_t n, uint32_t flags) {
+    return uses_panels(m) && n >= kStageLeastRays && n <= kStageRays && !(flags & (NIF_Q_POSE_ORDER | NIF_Q_POSE_TIMES));
+}
+
 int query_launch(const nif_model* m, const nif_grid* g, const nif_rays* r, int64_t n, const nif_hits* out,
                  uint32_t flags, int32_t precision, int64_t* stats, hipStream_t st) {
     if (n == 0) return NIF_OK;
@@ -353,8 +357,7 @@ int query_launch(const nif_model* m, const nif_grid* g, const nif_rays* r, int64
         hipLaunchKernelGGL(k_proxy, dim3((unsigned)blocks), dim3(256), 0, st, G, R, *out, stats);
         return check_hip(hipGetLastError(), "k_proxy launch");
     }
-    if (uses_panels(m) && n >= kStageLeastRays && n <= kStageRays && !(flags & (NIF_Q_POSE_ORDER | NIF_Q_POSE_TIMES)))
-        return query_staged(m, G, R, n, out, precision, stats, st);
+    if (staged(m, n, flags)) return query_staged(m, G, R, n, out, precision, stats, st);
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, st, m->counters, 8);
     if (flags & NIF_Q_POSE_ORDER) {
         hipLaunchKernelGGL(k_order_prefix, dim3(1), dim3(64), 0, st, R.off, R.n_poses, g->order_pre);
@@ -376,40 +379,63 @@ int set_query_rays_per_wave(int v) {
 }
 
 // Times the fused query on the caller's rays for every launch shape of the search space
-// (workgroups per CU x rays per wave), keeps the fastest process-wide and reports it.
+// (workgroups per CU x rays per wave), keeps the fastest process-wide and reports it.  The fused kernel
+// itself, also where nif_query is staged: there it takes only the rays left over, in 16-ray waves whatever
+// the setting, and 16 and 64 would differ by noise alone.  For the same reason a number of workgroups
+// that makes the launch of the present one is passed over.
 int autotune_query(const nif_model* m, const nif_grid* g, const nif_rays* r, int64_t n, const nif_hits* out,
                    int32_t precision, int32_t reps, int32_t* best, float* best_ms, hipStream_t st) {
     static const int kBpc[] = {4, 6, 8, 10, 12, 14, 16, 20, 24};
     static const int kRpw[] = {16, 64};
     const int save_bpc = g_query_blocks_per_cu, save_rpw = g_query_rays_per_wave;
+    const bool listed = std::find(std::begin(kBpc), std::end(kBpc), save_bpc) != std::end(kBpc);
+    const GridArgs G = grid_args(g);
+    const RayArgs R = ray_args(g, r, n);
     hipEvent_t e0, e1;
     int rc = check_hip(hipEventCreate(&e0), "event");
     if (rc) return rc;
     if ((rc = check_hip(hipEventCreate(&e1), "event"))) { (void)hipEventDestroy(e0); return rc; }
+    auto fused = [&]() {
+        hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, st, m->counters, 8);
+        return launch_fused(m, G, R, out, precision, nullptr, 0, st);
+    };
+    auto query = [&]() { return query_launch(m, g, r, n, out, 0, precision, nullptr, st); };
+    auto timed = [&](auto launch, float* ms) {
+        int e = launch();                                              // warm-up
+        if (!e) e = check_hip(hipEventRecord(e0, st), "event record");
+        for (int i = 0; i < reps && !e; ++i) e = launch();
+        if (!e) e = check_hip(hipEventRecord(e1, st), "event record");
+        if (!e) e = check_hip(hipEventSynchronize(e1), "event sync");
+        if (!e) e = check_hip(hipEventElapsedTime(ms, e0, e1), "elapsed");
+        *ms /= (float)reps;
+        return e;
+    };
+    auto workgroups = [&](int bpc, int rpw) { return std::min<int64_t>((n + rpw - 1) / rpw, (int64_t)device_cus() * bpc); };
     float best_t = INFINITY;
     int bb = save_bpc, br = save_rpw;
     for (int rpw : kRpw) {
         for (int bpc : kBpc) {
+            if (listed && bpc != save_bpc && workgroups(bpc, rpw) == workgroups(save_bpc, rpw)) continue;
             g_query_blocks_per_cu = bpc;
             g_query_rays_per_wave = rpw;
-            if ((rc = query_launch(m, g, r, n, out, 0, precision, nullptr, st))) break;    // warm-up
-            if ((rc = check_hip(hipEventRecord(e0, st), "event record"))) break;
-            for (int i = 0; i < reps && !rc; ++i) rc = query_launch(m, g, r, n, out, 0, precision, nullptr, st);
-            if (rc) break;
-            if ((rc = check_hip(hipEventRecord(e1, st), "event record"))) break;
-            if ((rc = check_hip(hipEventSynchronize(e1), "event sync"))) break;
             float ms = 0.f;
-            if ((rc = check_hip(hipEventElapsedTime(&ms, e0, e1), "elapsed"))) break;
-            ms /= (float)reps;
+            if ((rc = timed(fused, &ms))) break;
             if (ms < best_t) { best_t = ms; bb = bpc; br = rpw; }
         }
         if (rc) break;
     }
+    if (!rc) {
+        g_query_blocks_per_cu = bb;
+        g_query_rays_per_wave = br;
+        if (staged(m, n, 0)) rc = timed(query, &best_t);               // what the caller's launches take
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    g_query_blocks_per_cu = rc ? save_bpc : bb;
-    g_query_rays_per_wave = rc ? save_rpw : br;
-    if (rc) return rc;
+    if (rc) {
+        g_query_blocks_per_cu = save_bpc;
+        g_query_rays_per_wave = save_rpw;
+        return rc;
+    }
     best[0] = bb;
     best[1] = br;
     if (best_ms) *best_ms = best_t;
