@@ -108,7 +108,11 @@ typedef struct {
                                 E = 2 (levels feat_dim + 3 (1 + 2 pe_freqs)); feat_dim 2 only */
 } nif_model_desc;
 
-/* Allocates parameters (FP32 masters and working copies), gradients and Adam state. */
+/* Allocates parameters (FP32 masters and working copies), gradients and Adam state.  Two features in
+   the composed form: also the scratch of nif_forward, nif_encode and nif_query, which allocate nothing
+   themselves: panels and positions of up to 2^16 point pairs (4 E + 24 (1 + 2 pe_freqs) bytes each, the
+   panels at most 2^28 bytes in all) and the lists of a query of 2^21 rays (about 80 MB); 200 MB at
+   E = 416, 320 MB at E = 832. */
 int nif_model_create(const nif_model_desc* desc, nif_model** out);
 int nif_model_destroy(nif_model* model);
 /* Element counts of the canonical tables and MLP parameter vectors. */
@@ -126,8 +130,9 @@ int nif_model_get_grads(const nif_model* model, float* g_tables_dev, float* g_ml
                         nif_stream stream);
 int nif_model_zero_grads(nif_model* model, nif_stream stream);
 /* Allocates the training scratch for batches of up to max_batch samples (activations,
-   deltas, one [min(max_batch, 2^17)][E] encoding scratch (two above 2^17 samples),
-   the table-gradient additions of a round of min(max_batch, 2^18) samples, weight-gradient
+   deltas, one [min(max_batch, 2^17)][E] encoding scratch (two above 2^17 samples), with two features
+   d encoding of the same size and the points' positions and gradients per level, the table-gradient
+   additions of a round of min(max_batch, 2^18) samples, weight-gradient
    partials and the spatially ordered copy of a batch); nif_backward and nif_train_step fail with NIF_E_STATE above it.  A later call
    with a larger max_batch frees and re-allocates everything, the stored encoding included. */
 int nif_model_reserve(nif_model* model, int64_t max_batch);

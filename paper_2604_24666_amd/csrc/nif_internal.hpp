@@ -89,6 +89,7 @@ struct nif_model {
     int32_t step = 0;
     bool params_set = false;
     int64_t* counters = nullptr;        // [16] query work counters: 8 ranges, staged segments, rays left over
+    float* call_scratch = nullptr;      // one allocation (panel models) that holds the six below
     float* fwd_enc = nullptr;           // panels of one part (at most stage_chunk pairs) of nif_forward, nif_encode or a staged query
     uint32_t* fwd_pos = nullptr;        //   and their positions
     // staged query (panel models): first segments of a part of the rays, their heads, rays left over

@@ -175,14 +175,20 @@ int model_alloc(nif_model* m) {
     if ((rc = dalloc(&m->m_s, 8, "adam m"))) return rc;
     if ((rc = dalloc(&m->v_s, 8, "adam v"))) return rc;
     if ((rc = dalloc(&m->counters, 16, "counters"))) return rc;
-    if (uses_panels(m)) {
+    if (uses_panels(m)) {                        // one allocation: each costs its share of the set-up
         const int64_t fc = stage_chunk(m), sc = stage_cap(m);       // forward_chunk is at most stage_chunk
-        if ((rc = dalloc(&m->fwd_enc, fc * m->E, "forward panels"))) return rc;
-        if ((rc = dalloc(&m->fwd_pos, fc * 6 * m->S, "forward positions"))) return rc;
-        if ((rc = dalloc(&m->q_list, 4 * sc, "query segments"))) return rc;
-        if ((rc = dalloc(&m->q_x, 6 * sc, "query segment points"))) return rc;
-        if ((rc = dalloc(&m->q_heads, m->H * sc, "query heads"))) return rc;
-        if ((rc = dalloc(&m->q_rest, 4 * kStageRays, "query rays left over"))) return rc;
+        const struct { void** p; int64_t words; } parts[] = {
+            {(void**)&m->fwd_enc, fc * m->E}, {(void**)&m->fwd_pos, fc * 6 * m->S}, {(void**)&m->q_list, 4 * sc},
+            {(void**)&m->q_x, 6 * sc}, {(void**)&m->q_heads, m->H * sc}, {(void**)&m->q_rest, 4 * kStageRays}};
+        auto room = [](int64_t words) { return (words + 63) & ~(int64_t)63; };      // 256-byte steps
+        int64_t words = 0;
+        for (const auto& b : parts) words += room(b.words);
+        if ((rc = dalloc(&m->call_scratch, words, "scratch of the forward, the encoding and the query"))) return rc;
+        float* at = m->call_scratch;
+        for (const auto& b : parts) {
+            *b.p = at;
+            at += room(b.words);
+        }
     }
     if ((rc = dalloc(&m->dacc, 16, "train accumulators"))) return rc;
     if ((rc = dalloc(&m->tcount, 16, "train counters"))) return rc;
@@ -202,7 +208,7 @@ void model_free(nif_model* m) {
                   m->g_tables, m->g_mlp, m->g_s, m->m_tables, m->v_tables, m->m_mlp, m->v_mlp,
                   m->m_s, m->v_s, m->counters, m->dacc, m->tcount, m->zbuf, m->dz, m->acts, m->delta,
                   m->enc, m->enc_all, m->bwd_cnt, m->bwd_scan, m->bwd_val, m->w0l_f32, m->w0l_bf16, m->w0l_f16,
-                  m->dw_part, m->fwd_enc, m->fwd_pos, m->q_list, m->q_x, m->q_heads, m->q_rest, m->pos, m->denc, m->dx_part, m->dir_acc, m->ord_u32, m->ord_f32, m->ord_temp};
+                  m->dw_part, m->call_scratch, m->pos, m->denc, m->dx_part, m->dir_acc, m->ord_u32, m->ord_f32, m->ord_temp};
     for (void* p : ps)
         if (p) (void)hipFree(p);
     if (m->ev_fork) (void)hipEventDestroy(m->ev_fork);
