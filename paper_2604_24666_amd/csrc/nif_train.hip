@@ -46,6 +46,7 @@ __global__ void __launch_bounds__(256) k_gamma_dx(const float* __restrict__ W0t,
         for (int p = 0; p < 2; ++p) {
             const float* xs = p ? x1 : x0;
             float* dx = p ? dx1 : dx0;
+            if (!dx) continue;
             float acc[3] = {0.f, 0.f, 0.f};
             for (int r = 0; r < GW; ++r) {
                 const int s = r / 3, a = r - 3 * s;
@@ -858,7 +859,7 @@ struct EncBwdParams {
     const float* x1;
     int32_t HW, E, S;
     float* g_tables;
-    float* dx0;          // nullable SoA [3][B]
+    float* dx0;          // SoA [3][B], each nullable
     float* dx1;
     int64_t B;           // stride of the SoA point arrays
     int64_t c0;          // first sample of this round
@@ -1007,6 +1008,7 @@ __global__ void __launch_bounds__(256) k_enc_bwd_fill3(EncBwdParams P) {
     const uint32_t kmask = (1u << P.SB) - 1u;
     const int nloc = P.NBL * n_table_sets(P);
     const int bx = (int)blockIdx.x + P.blk0;   // block within the round
+    const bool want_dx = P.dx0 || P.dx1;
     for (int i = tid; i < nloc; i += 256) s_cur[i] = P.cnt[level_bucket_global(P, lp, i) * P.n_blk + bx];
     // The W0 rows this block multiplies (combination c, (level, feature) r of its group: row
     // 4c + r, zero where r >= LG FD), staged once in LDS with rows padded by 4 floats, so the
@@ -1095,7 +1097,7 @@ __global__ void __launch_bounds__(256) k_enc_bwd_fill3(EncBwdParams P) {
                                 make_float4(v[0], v[1], v[2], __uint_as_float(idx[cc] & kmask));
                     }
                     vmx = fin ? fmaxf(vmx, amax) : INFINITY;
-                    if (P.dx0) {
+                    if (want_dx) {
 #pragma unroll
                         for (int cc = 0; cc < 8; ++cc) {
                             const size_t te = ((size_t)combo_set(P, c) * (size_t)P.enc.set_stride +
@@ -1115,24 +1117,24 @@ __global__ void __launch_bounds__(256) k_enc_bwd_fill3(EncBwdParams P) {
                             dl[2] += gd * (((cc >> 2) & 1) ? 1.f : -1.f) * fx * fy;
                         }
                     }
-                    if (P.dx0) {
+                    if (want_dx) {
                         const float N = (float)P.enc.res[l];
 #pragma unroll
                         for (int a = 0; a < 3; ++a) dpos[a] += dl[a] * N;
                     }
                 }
             }
-            if (P.dx0 && live) {
+            if (want_dx && live) {
                 const int p = c >= P.S ? 1 : 0;
 #pragma unroll
                 for (int a = 0; a < 3; ++a) dxa[p][a] += dpos[a] * dsdx[a] * inside[a];
             }
         }
-        if (P.dx0 && valid)
+        if (valid)
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                unsafeAtomicAdd(&P.dx0[a * P.B + seg], dxa[0][a]);
-                unsafeAtomicAdd(&P.dx1[a * P.B + seg], dxa[1][a]);
+                if (P.dx0) unsafeAtomicAdd(&P.dx0[a * P.B + seg], dxa[0][a]);
+                if (P.dx1) unsafeAtomicAdd(&P.dx1[a * P.B + seg], dxa[1][a]);
             }
         for (int off = 32; off > 0; off >>= 1) vmx = fmaxf(vmx, __shfl_xor(vmx, off));
         if (lane == 0 && vmx > 0.f) atomicMax(P.vmax, __float_as_uint(vmx));   // non-negative: bits order as values
@@ -2371,13 +2373,14 @@ int backward_launch(nif_model* m, const float* x0, const float* x1, int64_t B, c
         hipLaunchKernelGGL(k_pad_dz, dim3(grid_for(n * 16)), dim3(256), 0, st, dh + c0 * m->H, m->H, n, dz);
     }, st);
     if (rc) return rc;
-    if (dx0 && m->GW > 0) {                  // concatenated encoding: d x through the raw gamma values
+    if ((dx0 || dx1) && m->GW > 0) {                  // concatenated encoding: d x through the raw gamma values
         const int hw = m->desc.hidden_width, nh = m->desc.hidden_layers;
         const int E_phi = 2 * m->S * m->desc.levels * m->desc.feat_dim;
         for (int64_t c0 = 0; c0 < B; c0 += m->bwd_chunk) {
             const int64_t n = std::min<int64_t>(m->bwd_chunk, B - c0);
             hipLaunchKernelGGL(k_gamma_dx, dim3(grid_for(n)), dim3(256), 0, st, m->mlp_pad_f32 + m->wt_off[0],
-                               m->delta + (size_t)c0 * nh * hw, hw, E_phi, m->GW, x0 + c0, x1 + c0, n, B, dx0 + c0, dx1 + c0);
+                               m->delta + (size_t)c0 * nh * hw, hw, E_phi, m->GW, x0 + c0, x1 + c0, n, B,
+                               dx0 ? dx0 + c0 : nullptr, dx1 ? dx1 + c0 : nullptr);
         }
     }
     return check_hip(hipGetLastError(), "backward launch");
