@@ -17,7 +17,6 @@ enum { DEF_IDENTITY = 0, DEF_TWIST = 1, DEF_BEND = 2, DEF_TAPER = 3, DEF_TWIST_B
 constexpr float kCx = 0.5f, kCy = 0.5f, kCz = 0.5f;   // deformation pivot: cube centre
 constexpr float kBinPad = 1e-5f;                      // padding of voxel boxes when binned
 
-// One deformation pose and its deformed-space acceleration grid.
 // Voxel (i, j, k) as the bin lists hold it: 10 bits per axis (N <= 1024), ordered as the voxel id
 // i + N (j + N k), so that the lists need no division to find the voxel's corners.
 __host__ __device__ inline int32_t pack_cell(int32_t id, int32_t N) {
@@ -27,6 +26,7 @@ __host__ __device__ inline int32_t cell_id(int32_t packed, int32_t N) {
     return (packed & 0x3ff) + N * (((packed >> 10) & 0x3ff) + N * (packed >> 20));
 }
 
+// One deformation pose and its deformed-space acceleration grid.
 struct PoseDev {
     int32_t kind;
     float s;

@@ -115,9 +115,9 @@ __global__ void __launch_bounds__(256) k_proxy(GridArgs G, RayArgs R, nif_hits o
 
 // ------------------------------------------------------------------ staged query
 //
-// Launches of many rays evaluate the rays' first segments in stages, each a kernel over all of them: search, encoding level by level, MLP, results.  Table lookups then run
-// at the rate of one level's table in L2 (nif_panels.hpp) and the matrix cores on full tiles, and the
-// search on all lanes.  The fused kernel takes the rays whose first segment is no hit, from there on,
+// Launches of many rays evaluate the rays' first segments in stages, each a kernel over all of them:
+// search, encoding level by level, MLP, results.  Table lookups then run at the rate of one level's
+// table in L2 (nif_panels.hpp) and the matrix cores on full tiles, and the search on all lanes.  The fused kernel takes the rays whose first segment is no hit, from there on,
 // and those beyond the list's room (a quarter of the rays; it would otherwise be mostly empty
 // launches).  A ray's result depends on neither.
 
@@ -339,8 +339,11 @@ static int query_staged(const nif_model* m, const GridArgs& G, RayArgs R, int64_
 }
 
 // Launches of so many rays are staged, up to kStageRays.  16,001 rays: 262 us staged, 313 in blocks
-// (64^3 spheres), 566 and 627 (128^3 blobs, BF16); 8,001: 529 and 367.  Above, coherent rays run as fast
-// in 64-ray waves: 25 M camera rays 26.2 ms fused, 27.0 in stages of 2^21.
+// (64^3 spheres), 566 and 627 (128^3 blobs, BF16); 8,001: 529 and 367.  The upper line is the room of
+// the model's lists, not where staging stops to pay: at 2^21 rays the staged form is ahead for every
+// kind of rays (128^3 blobs, BF16, staged against 64 rays more fused: camera 3.39 and 5.23 ms, half
+// secondary 5.63 and 10.06, random 15.3 and 22.2).  Sweeps in stages of 2^21 were measured for coherent
+// rays only, and lose there: 25 M camera rays 27.0 ms, 26.2 fused.
 constexpr int64_t kStageLeastRays = 1 << 14;
 
 static bool staged(const nif_model* m, int64_t n, uint32_t flags) {
