@@ -68,8 +68,8 @@ __global__ void __launch_bounds__(256) k_panel_rows(int S, int L, const float2* 
     }
 }
 
-// Heads of point pairs for the method variants (concatenated encoding, three features), gathers
-// and MLP fused.  Each wave evaluates tiles of TILE pairs; acts (nullable) receives the hidden
+// Heads of point pairs for the method variants (concatenated encoding, three features) and for few
+// pairs of small networks, gathers and MLP fused.  Each wave evaluates tiles of TILE pairs; acts (nullable) receives the hidden
 // activations [layer][B][HW] and enc (nullable) the encoding [B][E], for the training backward.
 // x0 / x1 are SoA with row stride ld >= B.
 template <int HW, int PREC, bool GAMMA, int TILE, int FD>
@@ -295,11 +295,30 @@ static void launch_mlp(const NetParams& np, const float* enc, int64_t n, float* 
 // pairs: 234 / 214 against 244 / 199 (forward, all kernels).
 constexpr int64_t kBlockMlpPairsPerCU = 40;
 
+// Few pairs of a small network whose first layer is one to four batches of lookups: the fused kernel,
+// one launch in place of three.  Fused and in panels, 2^14-entry tables, FP32: 8 levels without PE at
+// width 64 13.9 and 18.8 us for one pair, 17 and 24 for 16,384; at width 16 8.3 and 18.4, 9.9 and 19.7;
+// four batches at width 16 10.8 and 20.6, 14.1 and 24.2.  Four batches at width 64 have no line
+// (16 levels of 2^19 without PE: 18.0 and 19.6 us for one pair, 27.1 and 20.3 for 2,048), and width 128
+// is faster in panels (8 levels: 32 and 20.6 us for 256 pairs).  At 40,000 pairs and width 16 two batches
+// take 18 and 27 us, three 31 and 33, four 37 and 32.  Heads are the same bits.
+static bool forward_fused(const NetParams& np, int hw, int64_t n) {
+    const int batches = ((2 * (1 + 2 * np.enc.F) + 3) >> 2) * (np.enc.L >> 2);
+    return hw <= 64 && batches <= 4 && batches * hw <= 128 && n <= (batches <= 3 ? 1 << 16 : 1 << 14);
+}
+
 // enc: panels of n pairs (panel_stride(n) E floats), or rows [n][E] (nullable) for the variants.
 template <int HW, int PREC>
 static void launch_forward(const NetParams& np, const float* x0, const float* x1, int64_t n, int64_t ld, float* heads,
                            float* acts, float* enc, uint32_t* pos, hipStream_t st, const Live& lv) {
     if (np.gamma_F < 0 && np.enc.Fd == 2) {
+        if constexpr (HW <= 64) {
+            if (!acts && !lv.count && forward_fused(np, HW, n)) {
+                hipLaunchKernelGGL((k_forward<HW, PREC, false, 16, 2>), dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, np, x0, x1, n, ld,
+                                   heads, nullptr, nullptr);
+                return;
+            }
+        }
         launch_panels(np, x0, x1, n, ld, pos, enc, st, lv);
         // a block per 16 pairs while that is what it takes to fill the chip, 16 pairs per wave until two
         // waves per SIMD are busy (one in 16 bits), then as many as the registers hold.  51,000 pairs at
