@@ -26,10 +26,10 @@ sys.path.insert(0, ROOT)
 
 GATHER_BYTES_PER_EVAL = 13312   # 2 points x 13 PE samples x 16 levels x 8 corners x 4 B (FP16 pair)
 GATHER_BYTES_PER_EVAL_C0 = 13312  # torus workload: 2 x 13 x 8 levels x 8 corners x 8 B (FP32 pair)
-# training step per sample: forward gathers 13,312 B + the backward's recomputed gathers 13,312 B
+# training step per sample: the encoding's gathers 13,312 B (once a step)
 # + the FP32 table-gradient payload (2 points x 13 samples x 16 levels x 8 corners x 8 B) 26,624 B
 # + dense Adam over all parameters (~570 MB per step at B = 2^18) 2,176 B
-TRAIN_BYTES_PER_SAMPLE = 13312 + 13312 + 26624 + 2176
+TRAIN_BYTES_PER_SAMPLE = 13312 + 26624 + 2176
 HBM_PEAK_GBS = 8000.0
 
 # HBM bytes that k_query moves per launch on the default workload, from two rocprofv3 --pmc runs
@@ -39,12 +39,12 @@ HBM_PEAK_GBS = 8000.0
 # traffic is reported as null.
 KQUERY_SOURCES = ["paper_2604_24666_amd/csrc/nif_query.hip", "paper_2604_24666_amd/csrc/nif_query.hpp",
                   "paper_2604_24666_amd/csrc/nif_query_fp32.hip", "paper_2604_24666_amd/csrc/nif_net.hpp", "paper_2604_24666_amd/csrc/nif_panels.hpp",
-                  "paper_2604_24666_amd/csrc/nif_trace.hpp", "paper_2604_24666_amd/csrc/nif_device.hpp",
+                  "paper_2604_24666_amd/csrc/nif_trace.hpp", "paper_2604_24666_amd/csrc/nif_deal.hpp", "paper_2604_24666_amd/csrc/nif_device.hpp",
                   "paper_2604_24666_amd/csrc/nif_internal.hpp", "paper_2604_24666_amd/build.py",
                   "nif_synth/__init__.py"]
 KQUERY_TRAFFIC = {
-    "sources_sha256": "bdf5d7f254312b64bdf9b4ca3160ae8f075bea281b05b1ab4800ffccb22c35e9",
-    "fetch_kib": 1.05251e8, "write_kib": 2.62779e6,         # per k_query<64, FP32, 64> launch, default workload
+    "sources_sha256": "a11d3a677c4426df47f7fa6971934326ab7c1b81df4ded82b66a15c9b33ace66",
+    "fetch_kib": 1.04874e8, "write_kib": 1.93728e6,         # per k_query<64, FP32, 64> launch, default workload
     "fetch_scale": 1048576 / 524303, "write_scale": 1048576 / 1048577,   # 1 GiB copy reads 524,303 / writes 1,048,577 KiB
 }
 
@@ -411,8 +411,8 @@ def train_leg(steps=5, B=1 << 18, variants=tuple(TRAIN_VARIANTS)):
                  "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                               "kernel": "training step (all kernels of one step)",
-                              "algorithmic_bytes": f"{TRAIN_BYTES_PER_SAMPLE} B per sample (gathers, recomputed "
-                                                   "gathers, FP32 table-gradient payload, dense Adam)"}}
+                              "algorithmic_bytes": f"{TRAIN_BYTES_PER_SAMPLE} B per sample (gathers, FP32 "
+                                                   "table-gradient payload, dense Adam)"}}
             if store:
                 res.setdefault("stored_encoding", {})[name] = r
             else:
@@ -423,7 +423,7 @@ def train_leg(steps=5, B=1 << 18, variants=tuple(TRAIN_VARIANTS)):
                         "rays through 8 random twist/bend poses, labelled on the GPU from the analytic scene, "
                         "MLP 832-128x4-12, 16-level 2^19 FP16 grid, Adam", "hit_ratio": hit_ratio,
             "label_ms": label_ms,
-            "encoding_policy": "bf16 / fp32: the backward recomputes the encoding (chunks of 2^17 samples); "
+            "encoding_policy": "bf16 / fp32: a chunk's encoding (2^17 samples) is kept until its weight gradient; "
                                "stored_encoding: the forward keeps the [B][832] FP32 encoding for the backward",
             **res}
 

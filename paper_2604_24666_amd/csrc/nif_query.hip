@@ -18,7 +18,8 @@ __global__ void k_reset_pose_times(int64_t* stats, int n_poses) {
 
 // SUB lanes a ray: the time of a launch is that of the longest rays' chains of bins and voxel tests
 // (2^17 random rays through 8 poses of the 128^3 blob scene: 5.3 ms with one lane, 1.66 with four,
-// 1.60 with eight, 1.78 with sixteen; 3,000 rays: 0.52, 0.38 and 0.27 with four, eight, sixteen).
+// 1.60 with eight, 1.78 with sixteen; 3,000 rays: 0.52, 0.38 and 0.27 with four, eight, sixteen; with
+// the walk's state in registers, as it is now, 1.33 with eight).
 // Four waves per SIMD: the form of 16 lanes takes 129 registers by itself, one above that line (16,300
 // rays 433 us, 395 with 128 registers and 12 bytes of scratch).
 // points: the rest-space end points are written here; else k_trace_points forms them from t_in, t_out.
@@ -325,7 +326,9 @@ static int query_staged(const nif_model* m, const GridArgs& G, RayArgs R, int64_
     const int64_t ld = stage_cap(m), chunk = stage_chunk(m);
     const int32_t cap = (int32_t)std::min(std::max<int64_t>(1, (n / 4 + chunk - 1) / chunk) * chunk, n);
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, st, m->counters, 16);
-    constexpr int SUB = 2;     // with 1, 2, 4, 8 a batch of 1.5 M mixed rays takes 4.75, 4.36, 4.79, 5.46 ms
+    // with 1, 2, 4, 8 lanes a ray a batch of 1.5 M mixed rays took 4.75, 4.36, 4.79, 5.46 ms (4.11 with two
+    // since the walk's state is in registers)
+    constexpr int SUB = 2;
     hipLaunchKernelGGL(k_first<SUB>, dim3((unsigned)((n * SUB + 255) / 256)), dim3(256), 0, st, G, R, *out, cap, m->q_list, ld, m->q_x,
                        n_list, m->q_rest, n_rest, stats);
     int rc;

@@ -838,7 +838,7 @@ __global__ void __launch_bounds__(64 * kDwSumGroups) k_dw_sum(DwArgs A, float* _
 //            level each) its additions fall into (LDS atomics) and stores the counts;
 //   scan   - an exclusive scan over (bucket, block) gives every block a private output range
 //            per bucket;
-//   fill   - the same block decomposition recomputes the additions and writes (entry within
+//   fill   - the same block decomposition forms the additions and writes (entry within
 //            the slice, value pair) into its ranges (LDS cursors, no global atomics);
 //   reduce - one block per part of a slice sums its additions in LDS and adds them to the
 //            FP32 table gradient.
