@@ -150,7 +150,6 @@ __global__ void __launch_bounds__(256) k_first(GridArgs G, RayArgs R, nif_hits o
             write_miss(out, r, 0, -INFINITY);
         }
     }
-    const bool done = lead && r < R.n && !has;
     has = has && lead;
     const uint64_t mask = ballot(has), below = (1ull << lane) - 1ull;
     if (lane == 0) s_n[w] = popc64(mask);
@@ -185,10 +184,12 @@ __global__ void __launch_bounds__(256) k_first(GridArgs G, RayArgs R, nif_hits o
     // every lane counts its own tests; those of a ray beyond the list are counted when it is searched again
     const uint64_t ray_lanes = SUB == 64 ? ~0ull : ((1ull << SUB) - 1ull) << (lane / SUB * SUB);
     if (om & ray_lanes) bad = 0;
-    if (stats) wave_add_stats(stats, done ? 1 : 0, 0, bad);
+    if (stats) wave_add_stat(&stats[2], bad);                        // the misses are counted by k_first_hits
 }
 
 // Results of the staged segments: hits are written, the other rays are left for the fused kernel.
+// Statistics: one set of atomics per block, and the rays without a segment in one sum (one atomic per
+// wave of k_first cost a frame of 2^20 rays 1.6 ms).
 __global__ void __launch_bounds__(256) k_first_hits(GridArgs G, RayArgs R, nif_hits out, int H, int dist_head, int32_t cap,
                                                     const int32_t* __restrict__ list, int64_t ld, const float* __restrict__ x,
                                                     const float* __restrict__ heads, const int32_t* __restrict__ n_list,
@@ -228,7 +229,18 @@ __global__ void __launch_bounds__(256) k_first_hits(GridArgs G, RayArgs R, nif_h
             }
         }
     }
-    if (stats) wave_add_stats(stats, n_done, n_eval, 0);
+    if (!stats) return;
+    __shared__ int64_t s_sum[2];
+    if (threadIdx.x < 2) s_sum[threadIdx.x] = 0;
+    __syncthreads();
+    wave_add_stat(&s_sum[0], n_done);
+    wave_add_stat(&s_sum[1], n_eval);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int64_t done = s_sum[0] + (blockIdx.x == 0 ? R.n - *n_list : 0);
+        if (done) atomicAdd((unsigned long long*)&stats[0], (unsigned long long)done);
+        if (s_sum[1]) atomicAdd((unsigned long long*)&stats[1], (unsigned long long)s_sum[1]);
+    }
 }
 
 // ------------------------------------------------------------------ host launchers

@@ -152,17 +152,18 @@ __device__ __forceinline__ void write_hit(const nif_hits& o, int64_t r, const Se
     }
 }
 
+// Adds a count of the wave to the statistics, if there is one: the atomics of a launch's waves on one
+// address go one after the other (about 18 ns each), so only few waves may add.
+__device__ __forceinline__ void wave_add_stat(int64_t* stat, int64_t v) {
+    if (!ballot(v != 0)) return;
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if (lane_id() == 0) atomicAdd((unsigned long long*)stat, (unsigned long long)v);
+}
+
 __device__ __forceinline__ void wave_add_stats(int64_t* stats, int64_t a, int64_t b, int64_t c) {
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
-        c += __shfl_xor(c, off);
-    }
-    if (lane_id() == 0) {
-        atomicAdd((unsigned long long*)&stats[0], (unsigned long long)a);
-        atomicAdd((unsigned long long*)&stats[1], (unsigned long long)b);
-        atomicAdd((unsigned long long*)&stats[2], (unsigned long long)c);
-    }
+    wave_add_stat(&stats[0], a);
+    wave_add_stat(&stats[1], b);
+    wave_add_stat(&stats[2], c);
 }
 
 // ------------------------------------------------------------------ fused first-hit query
