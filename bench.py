@@ -43,8 +43,8 @@ KQUERY_SOURCES = ["paper_2604_24666_amd/csrc/nif_query.hip", "paper_2604_24666_a
                   "paper_2604_24666_amd/csrc/nif_internal.hpp", "paper_2604_24666_amd/build.py",
                   "nif_synth/__init__.py"]
 KQUERY_TRAFFIC = {
-    "sources_sha256": "a11d3a677c4426df47f7fa6971934326ab7c1b81df4ded82b66a15c9b33ace66",
-    "fetch_kib": 1.04874e8, "write_kib": 1.93728e6,         # per k_query<64, FP32, 64> launch, default workload
+    "sources_sha256": "3f780529b52632cdd2801213b37251d9ddd3d2521cf303a2b73b08587eb82642",
+    "fetch_kib": 1.04903e8, "write_kib": 1.93696e6,         # per k_query<64, FP32, 64> launch, default workload
     "fetch_scale": 1048576 / 524303, "write_scale": 1048576 / 1048577,   # 1 GiB copy reads 524,303 / writes 1,048,577 KiB
 }
 
